@@ -59,8 +59,8 @@ int cclr_dbg_zgemm_group_f64(int variant, int nprob, const int* M, const int* N,
                              const cclr_c64* const* A, const cclr_c64* const* B, int btrans, cclr_c64* const* C);
 
 /* The same product (device pointers, the context's stream) through the
- * context's GEMM dispatch: the short-reduction vector-ALU kernel, the
- * short-output vector-ALU kernels (at most 16 columns with the long operand
+ * context's GEMM dispatch: the register kernel of small products, the
+ * short-reduction vector-ALU kernel, the short-output vector-ALU kernels (at most 16 columns with the long operand
  * contiguous in m, at most 8 with it contiguous in k), split-K, or the
  * autotuned MFMA kernels (a product with at most 32 rows and more columns
  * runs transposed), chosen by shape as for the contractions of a transform. */
@@ -127,7 +127,7 @@ int cclr_dbg_set_inner_tol(cclr_ctx* ctx, double tol);
  * -1 short-reduction VALU
  * kernel, -2 split-K, -3 reduced precision, -4 short-output VALU kernel, -5
  * reduced precision on pre-split FP32 planes, -6 short-output VALU kernel on
- * a long operand contiguous in k);
+ * a long operand contiguous in k, -7 small products straight from registers);
  * then, for enable >= 0, clears the record and switches timing on (1) or
  * off (0).  Timing synchronizes the stream after every product. */
 int cclr_dbg_gemm_trace(cclr_ctx* ctx, int enable, char* buf, long long cap);

@@ -507,8 +507,10 @@ void contract(cclr_ctx* c, cplx alpha, const Ten& A, const char* la, const Ten& 
 // form: the kernel that ran (FP64 variant >= 0, -1 short-reduction VALU
 // kernel, -2 split-K with the default variant, -3 reduced precision, -4
 // short-output VALU kernel, -5 reduced precision on pre-split FP32 planes, -6
-// short-output VALU kernel on a long operand contiguous in k)
+// short-output VALU kernel on a long operand contiguous in k, -7 small
+// products straight from registers)
 static void run_gemm_form(cclr_ctx* c, const GemmArgs& g, int& form);
+static bool narrow_may_pay(int N);
 void run_gemm(cclr_ctx* c, const GemmArgs& g) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.K <= 0) return;
   int form = 0;
@@ -569,6 +571,42 @@ static void copy4(cclr_ctx* c, const i64 (&dim)[4], cplx* dst, const i64 (&sd)[4
   launch_tcopy(a, c->stream);
 }
 
+constexpr int kFormFrag = -7;
+
+// Products for the register kernel (gemm_frag.hip), counted in 16 x 16 output
+// blocks f and 16-deep K tiles kt.  Times in us, this kernel against the one
+// that ran before:
+//  * up to 4096 block tiles, where every other kernel waits on one chain of
+//    loads per workgroup: 16x4x480 9 against 44 (64x32 tiles), 93x31x465 9
+//    against 76 (128x32), 465x93x31 4 against 37 (vector ALU), 558x186x186 8
+//    against 34 (64x64); at 7128 (45x3160x45, batch 4) 22 against 12;
+//  * long reductions with one side at most 48 and at most 128 blocks, or at
+//    most 40 blocks: 10x40x31600 16 against 59, 130x10x83850 57 against 195,
+//    80x40x31600 44 against 80 (63 evenly split); above that the operands are
+//    read too often: 144x144x10000 75 against 54 evenly split.  Up to 4
+//    columns the vector kernels stay: 80x4x800, batch 80, 27 against 31, but
+//    800x4x800 13 against 9;
+//  * short reductions with one side at most 16: 83850x10x10 11 against 31,
+//    14400x16x16, batch 32, 39 against 52.
+// Outputs 17 to 32 wide with more than 128 blocks stay on the 32-column tiles.
+static bool frag_may_pay(const GemmArgs& g) {
+  const i64 f = (i64)((g.M + 15) / 16) * ((g.N + 15) / 16) * g.batch, kt = (g.K + 15) / 16;
+  const int lo = std::min(g.M, g.N);
+  if (g.K > 32 && lo > 16 && lo <= 32 && f > 128) return false;
+  if (f * kt <= 4096) return true;
+  if (g.K >= 512) return lo > 4 && ((lo <= 48 && f <= 128) || f <= 40);
+  return g.K <= 32 && lo <= 16 && f < (i64(1) << 22);
+}
+
+// The short-reduction kernel runs 256 lanes along n: where they are mostly
+// idle the MFMA tiles are faster (3600x320x10: 9 us on 64x32 tiles against
+// 18; 120x120x16, batch 240: 21 on 64x64 tiles against 31), where they are
+// full it is (90x8100x12, batch 12: 37 against 43 us).
+static bool smallk_may_pay(const GemmArgs& g) {
+  const i64 n = (g.sCn != 1 && g.sCm == 1) ? g.M : g.N;
+  return 4 * n >= 3 * ((n + 255) / 256 * 256);
+}
+
 static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
   form = -1;
   // An operand or output whose unit stride is a batch index would have every
@@ -608,37 +646,53 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
       return;
     }
   }
-  if (g0.K <= 32 && launch_zgemm_smallk(g0, c->stream)) return;
+  // reduced-precision transforms take the small products in FP64 like the
+  // others: those are bound by latency and memory, not by the arithmetic
+  auto small = [&](const GemmArgs& h0) {
+    form = kFormFrag;
+    // lanes run along n: the unit-stride index of the output
+    const GemmArgs h = (h0.sCn != 1 && h0.sCm == 1) ? transposed(h0) : h0;
+    const FragPlan p = frag_plan(h);
+    Arena::Mark mk = c->arena.mark();
+    cplx* W = p.S > 1 ? (cplx*)c->arena.get(sizeof(cplx) * (size_t)h.batch * p.S * h.M * (size_t)h.N) : nullptr;
+    launch_zgemm_frag(h, p, W, c->stream);
+    c->arena.reset(mk);
+  };
+  const bool frag = g0.kchunk == 0 && g0.batch < 65536 && frag_may_pay(g0);
+  if (g0.K <= 32) {
+    if (frag) {
+      small(g0);
+      return;
+    }
+    // (the MFMA tiles of a reduced-precision transform are FP32)
+    if ((smallk_may_pay(g0) || c->sigma_prec != CCLR_FP64) && launch_zgemm_smallk(g0, c->stream)) return;
+  }
   // the MFMA tiles are at least 32 columns but 64 (FP64) or 128 (FP32) rows
   // high: a product with a short m side (at most 32) and a long n side runs
   // transposed, so that its short side can take the 32-column tiles
   const GemmArgs g = (g0.M <= 32 && g0.N > 32) ? transposed(g0) : g0;
   {
-    // at most 16 output columns: FP64 VALU rows instead of mostly empty MFMA tiles
-    GemmArgs h;
+    // at most 8 output columns, long operand contiguous in k: rows dotted along k
     int kc = 0, S = 0;
-    if (skinny_plan(g, h, kc, S)) {
-      form = -4;
-      if (S == 1) {
-        launch_zgemm_skinny(h, kc, 1, nullptr, c->stream);
-        return;
-      }
+    if (rowdot_plan(g, kc, S)) {
+      form = -6;
       Arena::Mark mk = c->arena.mark();
-      cplx* W = (cplx*)c->arena.get(sizeof(cplx) * (size_t)h.batch * S * h.M * (size_t)h.N);
-      launch_zgemm_skinny(h, kc, S, W, c->stream);
+      cplx* W = S > 1 ? (cplx*)c->arena.get(sizeof(cplx) * (size_t)g.batch * S * g.M * (size_t)g.N) : nullptr;
+      launch_zgemm_rowdot(g, kc, S, W, c->stream);
       c->arena.reset(mk);
       return;
     }
-    // at most 8 output columns, long operand contiguous in k: rows dotted along k
-    if (rowdot_plan(g, kc, S)) {
-      form = -6;
-      if (S == 1) {
-        launch_zgemm_rowdot(g, kc, 1, nullptr, c->stream);
-        return;
-      }
+    if (frag) {
+      small(g0);
+      return;
+    }
+    // at most 16 output columns: FP64 VALU rows instead of mostly empty MFMA tiles
+    GemmArgs h;
+    if (skinny_plan(g, h, kc, S)) {
+      form = -4;
       Arena::Mark mk = c->arena.mark();
-      cplx* W = (cplx*)c->arena.get(sizeof(cplx) * (size_t)g.batch * S * g.M * (size_t)g.N);
-      launch_zgemm_rowdot(g, kc, S, W, c->stream);
+      cplx* W = S > 1 ? (cplx*)c->arena.get(sizeof(cplx) * (size_t)h.batch * S * h.M * (size_t)h.N) : nullptr;
+      launch_zgemm_skinny(h, kc, S, W, c->stream);
       c->arena.reset(mk);
       return;
     }
@@ -669,7 +723,7 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
       form = lowp ? -3 : -2;
       if (lowp) launch_zgemm_lowp(h, CCLR_FP32, c->stream);
       else tuned_gemm(c, h);
-      launch_splitk_reduce(g.batch, (int)S, g.M, g.N, W, g.C, g.sCb, g.sCm, g.sCn, g.ar, g.ai, g.beta, c->stream);
+      launch_chunk_reduce(g, (int)S, W, c->stream);
       c->arena.reset(mk);
       return;
     }
@@ -743,7 +797,12 @@ static bool narrow_may_pay(int N) {
 // tile would be mostly empty)
 static int untimed_variant(const GemmArgs& g) {
   if (g.N <= 32) return g.M <= 64 ? GEMM_64x32_G4 : GEMM_128x32_G4_SB;
-  return g.M <= 64 ? GEMM_64x64_G4 : gemm_default_variant(g);
+  // 64x32 tiles where they pad less or 64x64 ones would not go round twice
+  // (3600x320x80: 24 us against 27; 5850x130x130: 27 against 42), else 64x64
+  // with one LDS buffer (120x7140x120, batch 2: 40 us; 42 with two buffers)
+  const i64 tiles = (i64)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
+  if (g.M > 64 && (narrow_may_pay(g.N) || tiles < 400)) return GEMM_64x32_G4;
+  return GEMM_64x64_G4_SB;
 }
 
 void launch_gemm_choice(const GemmArgs& g, int choice, hipStream_t s) {

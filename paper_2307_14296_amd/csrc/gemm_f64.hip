@@ -1,11 +1,7 @@
 // Complex GEMM kernels of libcclr for gfx950: FP64 MFMA (three or four real
-// products per complex block), FP32 MFMA, the short-reduction VALU form and the split-K reduction.
-#include "internal.h"
+// products per complex block), FP32 MFMA, the short-reduction VALU form.
+#include "gemm_dma.h"
 
-typedef double d4 __attribute__((ext_vector_type(4)));
-// last operand of the FP64 MFMA builtin: on CDNA3/CDNA4 its bits are the
-// DGEMM negate modifiers of the A, B and C operands; 1 negates A
-constexpr int kNegA = 1;
 // output row of v_mfma_f32_16x16x4_f32 for (lane, register)
 #define F32_ROW(lane, r) (4 * ((lane) >> 4) + (r))
 
@@ -20,18 +16,6 @@ constexpr int kNegA = 1;
 // --------------------------------------------------------------------------
 namespace {
 constexpr int GBM = 64, GBN = 64, GBK = 16, GPAD = 1;
-
-// complex value with the sign bit of its imaginary part xor-ed with sgn
-// (0 or 0x80000000): the conjugate, or the value itself, without arithmetic
-__device__ __forceinline__ cplx flip_im(cplx v, unsigned sgn) {
-  v.y = __hiloint2double(__double2hiint(v.y) ^ (int)sgn, __double2loint(v.y));
-  return v;
-}
-// element offset of batch bz (one or two batch indices)
-__device__ __forceinline__ i64 boff(const GemmArgs& g, i64 bz, i64 s1, i64 s2) {
-  if (g.nb2 <= 1) return bz * s1;
-  return (bz / g.nb2) * s1 + (bz % g.nb2) * s2;
-}
 
 __global__ __launch_bounds__(256) void k_zgemm(GemmArgs g) {
   __shared__ double sAr[GBK][GBM + GPAD], sAi[GBK][GBM + GPAD];
@@ -132,31 +116,6 @@ __global__ __launch_bounds__(256) void k_zgemm(GemmArgs g) {
           *dst = y;
         }
       }
-}
-
-// W[b][s][m][n] summed over s in a fixed order into C[b][m][n]
-__global__ __launch_bounds__(256) void k_splitk_reduce(int nb, int S, int M, int N, const cplx* __restrict__ W,
-                                                       cplx* __restrict__ C, i64 sCb, i64 sCm, i64 sCn, double ar,
-                                                       double ai, int beta) {
-  const i64 mn = (i64)M * N, total = mn * nb, stride = (i64)gridDim.x * blockDim.x;
-  for (i64 e = (i64)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-    const i64 b = e / mn, r = e % mn;
-    double sr = 0.0, si = 0.0;
-    for (int q = 0; q < S; ++q) {
-      const cplx w = W[(b * S + q) * mn + r];
-      sr += w.x;
-      si += w.y;
-    }
-    const i64 m = r / N, n = r % N;
-    cplx y = make_double2(ar * sr - ai * si, ar * si + ai * sr);
-    cplx* dst = C + b * sCb + m * sCm + n * sCn;
-    if (beta) {
-      const cplx o = *dst;
-      y.x += o.x;
-      y.y += o.y;
-    }
-    *dst = y;
-  }
 }
 
 // --------------------------------------------------------------------------
@@ -641,10 +600,6 @@ __device__ __forceinline__ int dma_row(int c, int lane) {
 template <bool KC, int R>
 __device__ __forceinline__ int dma_k(int c, int lane) {
   return KC ? (lane & 15) ^ ((4 * c + (lane >> 4)) & 15) : c / (R / 64);
-}
-__device__ __forceinline__ void dma16(const cplx* src, cplx* lds) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
 
 // tile shapes: BM x BN with eight waves of 64 x 32 (BM = 128: 2 x 4 waves,
@@ -1147,13 +1102,6 @@ __global__ __launch_bounds__(512, 2) void k_cgemm_f32w(GemmArgs g, int tm, int t
         }
       }
 }
-
-inline unsigned grid_for(i64 total) {
-  i64 g = (total + 255) / 256;
-  if (g > 65536) g = 65536;
-  if (g < 1) g = 1;
-  return (unsigned)g;
-}
 }  // namespace
 
 // FP64 GEMM variants: tile 128x64 or 64x64, three or four real products
@@ -1398,12 +1346,5 @@ void launch_zgemm_simple(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.K <= 0) return;
   dim3 grid((g.M + GBM - 1) / GBM, (g.N + GBN - 1) / GBN, g.batch);
   hipLaunchKernelGGL(k_zgemm, grid, dim3(256), 0, s, g);
-  HIPCHK(hipGetLastError());
-}
-
-void launch_splitk_reduce(int nb, int S, int M, int N, const cplx* W, cplx* C, i64 sCb, i64 sCm, i64 sCn, double ar,
-                          double ai, int beta, hipStream_t s) {
-  hipLaunchKernelGGL(k_splitk_reduce, dim3(grid_for((i64)M * N * nb)), dim3(256), 0, s, nb, S, M, N, W, C, sCb, sCm,
-                     sCn, ar, ai, beta);
   HIPCHK(hipGetLastError());
 }

@@ -8,7 +8,7 @@
 // index of the long operand (the product is transposed when that index is
 // n), so the loads of a wave are contiguous.  Long
 // reductions are split into chunks whose partial sums go to a workspace
-// that a second kernel sums in a fixed order.  A second kernel covers the
+// that launch_chunk_reduce sums in a fixed order.  A second kernel covers the
 // other layout of the long operand (rows contiguous in k, at most 8 output
 // columns): the threads of a workgroup run along k and their partial sums
 // are added at the end.  At 20 columns the broadcast
@@ -179,28 +179,6 @@ __global__ __launch_bounds__(256) void k_zgemm_rowdot(GemmArgs g, int kc, int S,
   *dst = y;
 }
 
-// C = alpha * (sum of the S chunk sums in W) (+ C): one element per thread, chunks in order
-__global__ __launch_bounds__(256) void k_skinny_reduce(GemmArgs g, int S, const cplx* __restrict__ W) {
-  const i64 mn = (i64)g.M * g.N, total = mn * g.batch, stride = (i64)gridDim.x * blockDim.x;
-  for (i64 e = (i64)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-    const i64 b = e / mn, r = e % mn;
-    double sr = 0.0, si = 0.0;
-    for (int q = 0; q < S; ++q) {
-      const cplx w = W[(b * S + q) * mn + r];
-      sr += w.x;
-      si += w.y;
-    }
-    const i64 m = r / g.N, n = r % g.N;
-    cplx y = make_double2(g.ar * sr - g.ai * si, g.ar * si + g.ai * sr);
-    cplx* dst = g.C + skn_off(g, b, g.sCb, g.sCb2) + m * g.sCm + n * g.sCn;
-    if (g.beta) {
-      const cplx o = *dst;
-      y.x += o.x;
-      y.y += o.y;
-    }
-    *dst = y;
-  }
-}
 }  // namespace
 
 bool skinny_plan(const GemmArgs& g0, GemmArgs& g, int& kc, int& S) {
@@ -271,11 +249,7 @@ void launch_zgemm_rowdot(const GemmArgs& g, int kc, int S, cplx* W, hipStream_t 
   else if (g.N <= 4) hipLaunchKernelGGL((k_zgemm_rowdot<4, 4>), grid, dim3(256), 0, s, g, kc, S, W);
   else hipLaunchKernelGGL((k_zgemm_rowdot<8, 4>), grid, dim3(256), 0, s, g, kc, S, W);
   HIPCHK(hipGetLastError());
-  if (S == 1) return;
-  const i64 total = (i64)g.batch * g.M * g.N;
-  const unsigned rgrid = (unsigned)std::min<i64>((total + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_skinny_reduce, dim3(rgrid), dim3(256), 0, s, g, S, W);
-  HIPCHK(hipGetLastError());
+  if (S > 1) launch_chunk_reduce(g, S, W, s);
 }
 
 void launch_zgemm_skinny(const GemmArgs& g, int kc, int S, cplx* W, hipStream_t s) {
@@ -291,9 +265,5 @@ void launch_zgemm_skinny(const GemmArgs& g, int kc, int S, cplx* W, hipStream_t 
   else if (g.N <= 12) hipLaunchKernelGGL(k_zgemm_skinny<12>, grid, dim3(SN_THREADS), 0, s, g, kc, S, W);
   else hipLaunchKernelGGL(k_zgemm_skinny<16>, grid, dim3(SN_THREADS), 0, s, g, kc, S, W);
   HIPCHK(hipGetLastError());
-  if (S == 1) return;
-  const i64 total = (i64)g.batch * g.M * g.N;
-  const unsigned rgrid = (unsigned)std::min<i64>((total + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_skinny_reduce, dim3(rgrid), dim3(256), 0, s, g, S, W);
-  HIPCHK(hipGetLastError());
+  if (S > 1) launch_chunk_reduce(g, S, W, s);
 }

@@ -194,7 +194,6 @@ void launch_small_eig(int n, const cplx* Hu, const cplx* Hl, int ld, cplx* work,
                       int ldc, cplx* theta, cplx* wall, int* status, hipStream_t st);
 // products with K <= 32 on the vector ALU (returns false if the form does not apply)
 bool launch_zgemm_smallk(const GemmArgs& g, hipStream_t s);
-// C[b][m][n] = (beta ? C : 0) + alpha * sum_s W[b][s][m][n]
 // products with at most 16 output columns (after transposing, if the unit-stride output index is n):
 // skinny_plan fills g (possibly the transposed product), the chunk length kc and the chunk count S,
 // or returns false; S > 1 needs a workspace W of batch*S*M*N elements (the launch also sums it into C)
@@ -205,8 +204,16 @@ void launch_zgemm_skinny(const GemmArgs& g, int kc, int S, cplx* W, hipStream_t 
 // elements when S > 1)
 bool rowdot_plan(const GemmArgs& g, int& kc, int& S);
 void launch_zgemm_rowdot(const GemmArgs& g, int kc, int S, cplx* W, hipStream_t s);
-void launch_splitk_reduce(int nb, int S, int M, int N, const cplx* W, cplx* C, i64 sCb, i64 sCm, i64 sCn, double ar,
-                          double ai, int beta, hipStream_t s);
+// small FP64 products (gemm_frag.hip): tiles of 16 fm x 16 fn blocks, the K
+// loop shared by the nw waves of a workgroup and cut in S chunks of kc; S > 1
+// needs a workspace of batch*S*M*N elements
+struct FragPlan {
+  int fm, fn, nw, kc, S;
+};
+FragPlan frag_plan(const GemmArgs& g);
+void launch_zgemm_frag(const GemmArgs& g, const FragPlan& p, cplx* W, hipStream_t s);
+// C[b][m][n] = (beta ? C : 0) + alpha * sum_s W[b][s][m][n], W [batch][S][M][N]
+void launch_chunk_reduce(const GemmArgs& g, int S, const cplx* W, hipStream_t s);
 // GEMM with automatic K splitting when the output has too few tiles to fill the GPU
 void run_gemm(cclr_ctx* c, const GemmArgs& g);
 // FP64 GEMM through the autotuner (large products: variant timed once per shape class)

@@ -1,0 +1,108 @@
+"""The engine's kernels for small and unevenly filling FP64 products, at the
+edges of their tiles and of the rules that choose them, against numpy.
+
+Tolerance: each of the two sides sums K complex products (four real ones
+each) in FP64 in some order, so an entry differs by at most
+2 (2 K + 16) 2^-53 |alpha| (|A| |B|) plus two roundings of the result."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+LL, P, I, D = ctypes.c_longlong, ctypes.c_void_p, ctypes.c_int, ctypes.c_double
+EPS = 2.0 ** -53
+
+
+@pytest.fixture(scope="module")
+def lib():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2307_14296_amd as cc
+    L = cc.lib()
+    L.cclr_dbg_run_gemm.argtypes = [P] + [I] * 4 + [P, LL, LL, LL, I, P, LL, LL, LL, I, P, LL, LL, LL, D, D, I]
+    L.cclr_dbg_run_gemm_b2.argtypes = [P] + [I] * 5 + [P, LL, LL, LL, LL, P, LL, LL, LL, LL, P, LL, LL, LL, LL, D, D, I]
+    L.cclr_dbg_gemm_trace.argtypes = [P, I, ctypes.c_char_p, LL]
+    ctx = cc.cclr_create(3, 6, cc.cclr_default_options())
+    yield L, ctx
+    cc.cclr_destroy(ctx)
+
+
+def crand(rng, *shape):
+    return rng.normal(size=shape) + 1j * rng.normal(size=shape)
+
+
+def dev(x):
+    return torch.as_tensor(np.ascontiguousarray(x)).cuda()
+
+
+def forms(L, ctx):
+    buf = ctypes.create_string_buffer(1 << 16)
+    assert L.cclr_dbg_gemm_trace(ctx, 0, buf, len(buf)) == 0
+    return [int(ln.split(" form ")[1].split()[0]) for ln in buf.value.decode().splitlines() if ln]
+
+
+def check(got, A, B, C0, alpha, K):
+    ref = alpha * (A @ B) + C0
+    bound = 2 * (2 * K + 16) * EPS * abs(alpha) * (np.abs(A) @ np.abs(B)) + 2 * EPS * (np.abs(ref) + np.abs(C0))
+    worst = (np.abs(got - ref) / bound).max()
+    print(f"worst entry at {worst:.2f} of its bound", flush=True)
+    assert worst <= 1.0
+
+
+def product(L, ctx, M, N, K, batch, ta, tb, tc, conjA, conjB, beta, form):
+    rng = np.random.default_rng(M + 3 * N + 7 * K + batch)
+    A, B, C0 = crand(rng, batch, M, K), crand(rng, batch, K, N), crand(rng, batch, M, N)
+    Ad = dev(A.transpose(0, 2, 1) if ta else A)
+    Bd = dev(B.transpose(0, 2, 1) if tb else B)
+    Cd = dev(C0.transpose(0, 2, 1) if tc else C0)
+    sA, sB, sC = (1, M) if ta else (K, 1), (1, K) if tb else (N, 1), (1, M) if tc else (N, 1)
+    alpha = 0.7 - 0.4j
+    print(f"{M}x{N}x{K} b{batch} ta={ta} tb={tb} tc={tc} conj=({conjA},{conjB}) beta={beta}", flush=True)
+    assert L.cclr_dbg_gemm_trace(ctx, 1, None, 0) == 0
+    rc = L.cclr_dbg_run_gemm(ctx, M, N, K, batch, Ad.data_ptr(), M * K, *sA, conjA, Bd.data_ptr(), K * N, *sB, conjB,
+                             Cd.data_ptr(), M * N, *sC, alpha.real, alpha.imag, beta)
+    assert rc == 0
+    assert forms(L, ctx) == [form]
+    got = Cd.cpu().numpy()
+    check(got.transpose(0, 2, 1) if tc else got, A.conj() if conjA else A, B.conj() if conjB else B,
+          C0 if beta else 0 * C0, alpha, K)
+
+
+LAYOUTS = [(False, False, False, 0, 1, 0), (True, False, True, 1, 0, 1), (False, True, False, 1, 1, 1)]
+
+# register kernel: one entry; one block and one beyond it; K of one tile, one
+# more, a ragged tile in a cut reduction; the last size of the 4096 block-tile
+# rule; tiles of 32 x 16, 16 x 32 and 32 x 32; long reductions at their limits
+FRAG = [(1, 1, 1, 1), (16, 16, 16, 1), (17, 15, 17, 3), (4, 4, 480, 1), (33, 16, 33, 2), (16, 256, 4096, 1),
+        (256, 256, 256, 1), (500, 40, 40, 1), (2, 3000, 31, 2), (48, 640, 601, 1), (80, 128, 5000, 1),
+        (10, 10, 70001, 1), (83850, 10, 10, 1), (9, 120, 20000, 2), (64, 64, 64, 16)]
+
+
+@pytest.mark.parametrize("M,N,K,batch", FRAG)
+@pytest.mark.parametrize("ta,tb,tc,conjA,conjB,beta", LAYOUTS)
+def test_register_kernel(lib, M, N, K, batch, ta, tb, tc, conjA, conjB, beta):
+    product(*lib, M, N, K, batch, ta, tb, tc, conjA, conjB, beta, -7)
+
+
+def test_register_kernel_two_level_batch(lib):
+    """b = b1 nb2 + b2 with B shared over b2; a cut reduction among them."""
+    L, ctx = lib
+    for M, N, K, nb1, nb2 in ((20, 12, 33, 3, 2), (12, 20, 3000, 2, 2)):
+        rng = np.random.default_rng(K)
+        A, B, C0 = crand(rng, nb1, nb2, M, K), crand(rng, nb1, 1, K, N), crand(rng, nb1, nb2, M, N)
+        Ad, Bd, Cd = dev(A), dev(B), dev(C0)
+        assert L.cclr_dbg_gemm_trace(ctx, 1, None, 0) == 0
+        rc = L.cclr_dbg_run_gemm_b2(ctx, M, N, K, nb1, nb2, Ad.data_ptr(), nb2 * M * K, M * K, K, 1, Bd.data_ptr(),
+                                    K * N, 0, N, 1, Cd.data_ptr(), nb2 * M * N, M * N, N, 1, 0.5, 0.25, 1)
+        assert rc == 0 and forms(L, ctx) == [-7]
+        check(Cd.cpu().numpy(), A, B, C0, 0.5 + 0.25j, K)
+
+
+# chunk sums: one to 32 threads per output, chunk counts that leave remainders
+# (the vector kernels' cut reductions and the split-K tiles)
+@pytest.mark.parametrize("M,N,K,batch,form", [(300, 1, 100003, 1, -6), (2000, 3, 9001, 2, -6), (3, 3000, 5000, 1, -4),
+                                              (70, 2, 40000, 3, -6)])
+def test_chunk_sums(lib, M, N, K, batch, form):
+    product(*lib, M, N, K, batch, False, False, False, 1, 0, 1, form)
