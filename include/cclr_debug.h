@@ -51,6 +51,14 @@ int cclr_dbg_tcopy(int nd, const long long* dim, const long long* sd, const long
 int cclr_dbg_zgemm_f64_splitk(int variant, int M, int N, int K, int kchunk, const cclr_c64* A, long long sAm,
                               long long sAk, const cclr_c64* B, long long sBk, long long sBn, cclr_c64* W);
 
+/* C[b] (+)= op(A[b]) B[b] on the evenly split FP64 kernel with tiles of 16 fm
+ * rows (fm 2 .. 6); the tiles that do not fill whole rounds of workgroups are
+ * cut into at most `cutters` runs (0: none is cut).  Device pointers, strides
+ * in elements. */
+int cclr_dbg_zgemm_even(int fm, int cutters, int M, int N, int K, int batch, const cclr_c64* A, long long sAb,
+                        long long sAm, long long sAk, const cclr_c64* B, long long sBb, long long sBk, long long sBn,
+                        cclr_c64* C, long long sCb, long long sCm, long long sCn, int conjA, int beta);
+
 /* Several independent products C[p] = A[p] B[p] (A[p] row-major M[p] x K[p];
  * B[p] row-major K[p] x N[p], or N[p] x K[p] when btrans; C[p] row-major
  * M[p] x N[p]; all device pointers) in the one persistent grouped launch of
@@ -59,8 +67,8 @@ int cclr_dbg_zgemm_group_f64(int variant, int nprob, const int* M, const int* N,
                              const cclr_c64* const* A, const cclr_c64* const* B, int btrans, cclr_c64* const* C);
 
 /* The same product (device pointers, the context's stream) through the
- * context's GEMM dispatch: the register kernel of small products, the
- * short-reduction vector-ALU kernel, the short-output vector-ALU kernels (at most 16 columns with the long operand
+ * context's GEMM dispatch: the register kernel of small products, the evenly
+ * split kernel, the short-reduction vector-ALU kernel, the short-output vector-ALU kernels (at most 16 columns with the long operand
  * contiguous in m, at most 8 with it contiguous in k), split-K, or the
  * autotuned MFMA kernels (a product with at most 32 rows and more columns
  * runs transposed), chosen by shape as for the contractions of a transform. */
@@ -127,7 +135,8 @@ int cclr_dbg_set_inner_tol(cclr_ctx* ctx, double tol);
  * -1 short-reduction VALU
  * kernel, -2 split-K, -3 reduced precision, -4 short-output VALU kernel, -5
  * reduced precision on pre-split FP32 planes, -6 short-output VALU kernel on
- * a long operand contiguous in k, -7 small products straight from registers);
+ * a long operand contiguous in k, -7 small products straight from registers, -8
+ * even split over the compute units);
  * then, for enable >= 0, clears the record and switches timing on (1) or
  * off (0).  Timing synchronizes the stream after every product. */
 int cclr_dbg_gemm_trace(cclr_ctx* ctx, int enable, char* buf, long long cap);

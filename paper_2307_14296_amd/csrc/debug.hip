@@ -92,6 +92,30 @@ int cclr_dbg_zgemm_f64(int variant, int batch, int M, int N, int K, const cclr_c
   return CCLR_OK;
 }
 
+int cclr_dbg_zgemm_even(int fm, int cutters, int M, int N, int K, int batch, const cclr_c64* A, long long sAb,
+                        long long sAm, long long sAk, const cclr_c64* B, long long sBb, long long sBk, long long sBn,
+                        cclr_c64* C, long long sCb, long long sCm, long long sCn, int conjA, int beta) {
+  void* W = nullptr;
+  int rc = CCLR_OK;
+  try {
+    REQUIRE(M > 0 && N > 0 && K > 0 && batch > 0 && fm >= 2 && fm <= 6 && cutters >= 0, CCLR_EINVAL, "empty product");
+    GemmArgs g{};
+    g.M = M; g.N = N; g.K = K; g.batch = batch;
+    g.A = (const cplx*)A; g.sAb = sAb; g.sAm = sAm; g.sAk = sAk; g.conjA = conjA;
+    g.B = (const cplx*)B; g.sBb = sBb; g.sBk = sBk; g.sBn = sBn;
+    g.C = (cplx*)C; g.sCb = sCb; g.sCm = sCm; g.sCn = sCn;
+    g.ar = 1.0; g.beta = beta;
+    const SkPlan p = sk_plan_for(g, fm, cutters);
+    if (p.cutters) HIPCHK(hipMalloc(&W, sk_workspace(p)));
+    launch_zgemm_sk(g, p, (cplx*)W, nullptr);
+    HIPCHK(hipDeviceSynchronize());
+  } catch (const CclrError& e) {
+    rc = e.code;
+  }
+  if (W) (void)hipFree(W);
+  return rc;
+}
+
 int cclr_dbg_tcopy(int nd, const long long* dim, const long long* sd, const long long* ss, cclr_c64* dst,
                    const cclr_c64* src, double ar, double ai, int conj, int acc) {
   try {

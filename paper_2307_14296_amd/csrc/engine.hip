@@ -78,6 +78,19 @@ void* Arena::get(size_t bytes) {
   return b->p;
 }
 
+void* Arena::try_get(size_t bytes) {
+  bytes = (bytes + 255) & ~size_t(255);
+  if (ext) return bytes <= ext_bytes - ext_used ? get(bytes) : nullptr;
+  bool room = false;
+  for (size_t k = cur; k < chunks.size() && !room; ++k) room = used[k] + bytes <= chunks[k]->bytes;
+  if (!room && ctx->opt.device_mem_cap) return nullptr;
+  try {
+    return get(bytes);
+  } catch (const CclrError&) {
+    return nullptr;
+  }
+}
+
 Arena::Mark Arena::mark() const {
   if (ext) return {size_t(-1), ext_used};
   return {cur, chunks.empty() ? 0 : used[cur]};
@@ -508,7 +521,7 @@ void contract(cclr_ctx* c, cplx alpha, const Ten& A, const char* la, const Ten& 
 // kernel, -2 split-K with the default variant, -3 reduced precision, -4
 // short-output VALU kernel, -5 reduced precision on pre-split FP32 planes, -6
 // short-output VALU kernel on a long operand contiguous in k, -7 small
-// products straight from registers)
+// products straight from registers, -8 even split over the compute units)
 static void run_gemm_form(cclr_ctx* c, const GemmArgs& g, int& form);
 static bool narrow_may_pay(int N);
 void run_gemm(cclr_ctx* c, const GemmArgs& g) {
@@ -571,7 +584,7 @@ static void copy4(cclr_ctx* c, const i64 (&dim)[4], cplx* dst, const i64 (&sd)[4
   launch_tcopy(a, c->stream);
 }
 
-constexpr int kFormFrag = -7;
+constexpr int kFormFrag = -7, kFormEven = -8;
 
 // Products for the register kernel (gemm_frag.hip), counted in 16 x 16 output
 // blocks f and 16-deep K tiles kt.  Times in us, this kernel against the one
@@ -605,6 +618,62 @@ static bool frag_may_pay(const GemmArgs& g) {
 static bool smallk_may_pay(const GemmArgs& g) {
   const i64 n = (g.sCn != 1 && g.sCm == 1) ? g.M : g.N;
   return 4 * n >= 3 * ((n + 255) / 256 * 256);
+}
+
+// Time of a product in us by the work it puts on the busiest compute unit;
+// the constants are fitted to measurements at o = 10 .. 20 (a K tile of 16 on
+// a 16 fm x 64 tile takes 0.478 fm us of a compute unit, 0.51 fm alone on it;
+// one on a 128x128 direct-load tile 7.27 us; a partial sum is written and read
+// at 4 TB/s).
+static double even_cost(const SkPlan& p) {
+  const double tau = (p.fm == 2 ? 0.495 : 0.478) * p.fm, alone = 0.51 * p.fm, round = 2.0 * p.nk * tau;
+  const i64 full = p.whole / 512, rem = p.whole % 512;
+  double t = (double)full * (round + 2.5);
+  if (rem) t += 2.5 + (rem <= 256 ? p.nk * alone : round);
+  if (p.cutters) {
+    const double rest = (double)(p.tiles - p.whole), run = rest * p.nk / p.cutters;
+    t += 2.5 + std::max(rest * p.nk * tau / 256.0, run * alone);
+    t += 6.0 + (p.cutters + rest) * 2.0 * (16.0 * 64 * 16) * p.fm / 4e6;
+  }
+  return t;
+}
+
+// FP64 products of some length on the evenly split kernel, in the orientation
+// and row count of least estimated time; false: not taken (short reductions,
+// where the other tiles are as fast, or large products that fill whole rounds
+// of 128x128 tiles)
+static bool even_split(cclr_ctx* c, const GemmArgs& g0) {
+  if (g0.K < (std::min(g0.M, g0.N) <= 32 ? 512 : 256) || g0.kchunk > 0) return false;
+  const i64 most = (i64)((g0.M + 31) / 32) * ((g0.N + 31) / 32) * g0.batch;
+  if (most >= (1ll << 30)) return false;
+  const i64 t128 = (i64)((g0.M + 127) / 128) * ((g0.N + 127) / 128) * g0.batch;
+  const double dma = (double)((t128 + 255) / 256) * (7.27 * ((g0.K + 15) / 16) + 3.0);
+  // with two workgroups per compute unit, with one where the partial sums of
+  // two have no room, and with whole tiles only
+  for (int cutters : {512, 256, 0}) {
+    double best = 1e300;
+    SkPlan plan;
+    bool trans = false;
+    for (int o = 0; o < 2; ++o) {
+      const GemmArgs g = o ? transposed(g0) : g0;
+      for (int fm = 2; fm <= 6; ++fm) {
+        const SkPlan p = sk_plan_for(g, fm, cutters);
+        // stores along the unit-stride index where both orientations are as good
+        const double t = even_cost(p) * (g.sCn == 1 ? 1.0 : 1.02);
+        if (t < best) best = t, plan = p, trans = o;
+      }
+    }
+    if (dma * 0.98 <= best) return false;
+    // a few whole tiles leave most of the chip idle: the split-K kernels
+    if (cutters == 0 && plan.tiles < 192) return false;
+    Arena::Mark mk = c->arena.mark();
+    cplx* W = nullptr;
+    if (plan.cutters > 0 && !(W = (cplx*)c->arena.try_get(sk_workspace(plan)))) continue;
+    launch_zgemm_sk(trans ? transposed(g0) : g0, plan, W, c->stream);
+    c->arena.reset(mk);
+    return true;
+  }
+  return false;
 }
 
 static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
@@ -699,6 +768,10 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
   }
   // inside reduced-precision transforms the remaining products run on FP32 MFMA as well
   const bool lowp = c->sigma_prec != CCLR_FP64;
+  if (!lowp && even_split(c, g)) {
+    form = kFormEven;
+    return;
+  }
   const i64 tiles = (i64)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
   if (g.nb2 <= 1 && tiles < 512 && g.K >= 512) {
     i64 S = std::min<i64>((1024 + tiles - 1) / tiles, g.K / 256);
@@ -813,6 +886,7 @@ static void launch_choice(const GemmArgs& g, int choice, hipStream_t s) { launch
 
 int tuned_gemm(cclr_ctx* c, const GemmArgs& g) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.K <= 0) return -1;
+  if (even_split(c, g)) return kFormEven;
   const double flops = 8.0 * g.M * (double)g.N * (g.kchunk > 0 ? g.kchunk : g.K) * g.batch;
   if (flops < 1e10) {
     const int v = untimed_variant(g);

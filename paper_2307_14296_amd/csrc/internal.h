@@ -72,6 +72,9 @@ struct Arena {
   size_t ext_bytes = 0, ext_used = 0, ext_peak = 0;
   ~Arena();
   void* get(size_t bytes);
+  // the same, or null where it does not fit (the external region, or what a
+  // context with a memory cap holds already; without a cap it may allocate)
+  void* try_get(size_t bytes);
   struct Mark { size_t chunk, top; };
   Mark mark() const;
   void reset(Mark m);
@@ -204,6 +207,17 @@ void launch_zgemm_skinny(const GemmArgs& g, int kc, int S, cplx* W, hipStream_t 
 // elements when S > 1)
 bool rowdot_plan(const GemmArgs& g, int& kc, int& S);
 void launch_zgemm_rowdot(const GemmArgs& g, int kc, int S, cplx* W, hipStream_t s);
+// FP64 products dealt evenly over the compute units (gemm_sk.hip): tiles of
+// 16 fm rows (fm = 2 .. 6) and 64 columns; tiles [0, whole) run whole, the K
+// loops of the others are cut into `cutters` equal runs whose partial sums go
+// to a workspace of sk_workspace(p) bytes (none when cutters = 0)
+struct SkPlan {
+  int fm = 4, tm = 0, tn = 0, gm = 1, nk = 0, grid = 0, cutters = 0;
+  i64 tiles = 0, whole = 0;
+};
+SkPlan sk_plan_for(const GemmArgs& g, int fm, int max_cutters);
+size_t sk_workspace(const SkPlan& p);
+void launch_zgemm_sk(const GemmArgs& g, const SkPlan& p, cplx* W, hipStream_t s);
 // small FP64 products (gemm_frag.hip): tiles of 16 fm x 16 fn blocks, the K
 // loop shared by the nw waves of a workgroup and cut in S chunks of kc; S > 1
 // needs a workspace of batch*S*M*N elements

@@ -106,3 +106,51 @@ def test_register_kernel_two_level_batch(lib):
                                               (70, 2, 40000, 3, -6)])
 def test_chunk_sums(lib, M, N, K, batch, form):
     product(*lib, M, N, K, batch, False, False, False, 1, 0, 1, form)
+
+
+# even split: every row count of the tile in both orientations (45, 66, 91,
+# 130, 180 rows against long sides), K tails and K of whole tiles, whole
+# rounds with a cut rest, fewer runs than workgroups, batches
+EVEN = [(45, 1000, 1030, 1), (1000, 66, 528, 1), (91, 700, 800, 1), (180, 513, 2047, 1), (130, 140, 9000, 1),
+        (1500, 1500, 300, 1), (65, 65, 2001, 2), (200, 200, 700, 3), (33, 2000, 900, 1), (500, 300, 260, 2)]
+
+
+@pytest.mark.parametrize("M,N,K,batch", EVEN)
+@pytest.mark.parametrize("ta,tb,tc,conjA,conjB,beta", LAYOUTS)
+def test_even_split(lib, M, N, K, batch, ta, tb, tc, conjA, conjB, beta):
+    product(*lib, M, N, K, batch, ta, tb, tc, conjA, conjB, beta, -8)
+
+
+@pytest.mark.parametrize("fm", [2, 3, 4, 5, 6])
+@pytest.mark.parametrize("M,N,K,batch,cutters", [(97, 70, 300, 1, 512), (97, 70, 300, 1, 0), (161, 1, 129, 2, 512),
+                                                 (16, 64, 4100, 1, 7), (700, 3000, 140, 1, 512),
+                                                 (700, 3000, 17, 1, 512), (33, 65, 15, 3, 512)])
+def test_even_split_tiles(lib, fm, M, N, K, batch, cutters):
+    """Each tile height with whole tiles only, a cut rest, a cut rest after
+    whole rounds, few runs, and K below one tile."""
+    L, _ = lib
+    L.cclr_dbg_zgemm_even.argtypes = [I] * 6 + [P, LL, LL, LL, P, LL, LL, LL, P, LL, LL, LL, I, I]
+    rng = np.random.default_rng(fm + M + K)
+    A, B, C0 = crand(rng, batch, M, K), crand(rng, batch, K, N), crand(rng, batch, M, N)
+    for ta, tb, conjA, beta in ((False, False, 1, 0), (True, True, 0, 1)):
+        Ad, Bd, Cd = dev(A.transpose(0, 2, 1) if ta else A), dev(B.transpose(0, 2, 1) if tb else B), dev(C0)
+        sA, sB = (1, M) if ta else (K, 1), (1, K) if tb else (N, 1)
+        print(f"fm={fm} {M}x{N}x{K} b{batch} cutters {cutters} ta={ta}", flush=True)
+        rc = L.cclr_dbg_zgemm_even(fm, cutters, M, N, K, batch, Ad.data_ptr(), M * K, *sA, Bd.data_ptr(), K * N, *sB,
+                                   Cd.data_ptr(), M * N, N, 1, conjA, beta)
+        assert rc == 0
+        check(Cd.cpu().numpy(), A.conj() if conjA else A, B, C0 if beta else 0 * C0, 1.0, K)
+
+
+def test_even_split_without_room():
+    """A context whose memory cap leaves no room for partial sums runs the
+    product in whole tiles."""
+    import paper_2307_14296_amd as cc
+    L = cc.lib()
+    opt = cc.cclr_default_options()
+    opt.device_mem_cap = 1 << 20
+    ctx = cc.cclr_create(3, 6, opt)
+    try:
+        product(L, ctx, 300, 5000, 300, 1, False, False, False, 0, 0, 1, -8)
+    finally:
+        cc.cclr_destroy(ctx)
