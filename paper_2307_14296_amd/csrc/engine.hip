@@ -589,7 +589,7 @@ constexpr int kFormFrag = -7, kFormEven = -8;
 // Products for the register kernel (gemm_frag.hip), counted in 16 x 16 output
 // blocks f and 16-deep K tiles kt.  Times in us, this kernel against the one
 // that ran before:
-//  * up to 4096 block tiles, where every other kernel waits on one chain of
+//  * up to 5120 block tiles, where every other kernel waits on one chain of
 //    loads per workgroup: 16x4x480 9 against 44 (64x32 tiles), 93x31x465 9
 //    against 76 (128x32), 465x93x31 4 against 37 (vector ALU), 558x186x186 8
 //    against 34 (64x64); at 7128 (45x3160x45, batch 4) 22 against 12;
@@ -603,12 +603,23 @@ constexpr int kFormFrag = -7, kFormEven = -8;
 //    14400x16x16, batch 32, 39 against 52.
 // Outputs 17 to 32 wide with more than 128 blocks stay on the 32-column tiles.
 static bool frag_may_pay(const GemmArgs& g) {
+  if (g.kchunk > 0 || g.batch >= 65536) return false;
   const i64 f = (i64)((g.M + 15) / 16) * ((g.N + 15) / 16) * g.batch, kt = (g.K + 15) / 16;
   const int lo = std::min(g.M, g.N);
   if (g.K > 32 && lo > 16 && lo <= 32 && f > 128) return false;
-  if (f * kt <= 4096) return true;
+  if (f * kt <= 5120) return true;
   if (g.K >= 512) return lo > 4 && ((lo <= 48 && f <= 128) || f <= 40);
   return g.K <= 32 && lo <= 16 && f < (i64(1) << 22);
+}
+
+static void small_product(cclr_ctx* c, const GemmArgs& g) {
+  // lanes run along n: the unit-stride index of the output
+  const GemmArgs h = (g.sCn != 1 && g.sCm == 1) ? transposed(g) : g;
+  const FragPlan p = frag_plan(h);
+  Arena::Mark mk = c->arena.mark();
+  cplx* W = p.S > 1 ? (cplx*)c->arena.get(sizeof(cplx) * (size_t)h.batch * p.S * h.M * (size_t)h.N) : nullptr;
+  launch_zgemm_frag(h, p, W, c->stream);
+  c->arena.reset(mk);
 }
 
 // The short-reduction kernel runs 256 lanes along n: where they are mostly
@@ -717,20 +728,11 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
   }
   // reduced-precision transforms take the small products in FP64 like the
   // others: those are bound by latency and memory, not by the arithmetic
-  auto small = [&](const GemmArgs& h0) {
-    form = kFormFrag;
-    // lanes run along n: the unit-stride index of the output
-    const GemmArgs h = (h0.sCn != 1 && h0.sCm == 1) ? transposed(h0) : h0;
-    const FragPlan p = frag_plan(h);
-    Arena::Mark mk = c->arena.mark();
-    cplx* W = p.S > 1 ? (cplx*)c->arena.get(sizeof(cplx) * (size_t)h.batch * p.S * h.M * (size_t)h.N) : nullptr;
-    launch_zgemm_frag(h, p, W, c->stream);
-    c->arena.reset(mk);
-  };
-  const bool frag = g0.kchunk == 0 && g0.batch < 65536 && frag_may_pay(g0);
+  const bool frag = frag_may_pay(g0);
   if (g0.K <= 32) {
     if (frag) {
-      small(g0);
+      form = kFormFrag;
+      small_product(c, g0);
       return;
     }
     // (the MFMA tiles of a reduced-precision transform are FP32)
@@ -752,7 +754,8 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
       return;
     }
     if (frag) {
-      small(g0);
+      form = kFormFrag;
+      small_product(c, g0);
       return;
     }
     // at most 16 output columns: FP64 VALU rows instead of mostly empty MFMA tiles
@@ -886,6 +889,10 @@ static void launch_choice(const GemmArgs& g, int choice, hipStream_t s) { launch
 
 int tuned_gemm(cclr_ctx* c, const GemmArgs& g) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.K <= 0) return -1;
+  if (frag_may_pay(g)) {
+    small_product(c, g);
+    return kFormFrag;
+  }
   if (even_split(c, g)) return kFormEven;
   const double flops = 8.0 * g.M * (double)g.N * (g.kchunk > 0 ? g.kchunk : g.K) * g.batch;
   if (flops < 1e10) {

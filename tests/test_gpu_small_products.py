@@ -73,10 +73,10 @@ def product(L, ctx, M, N, K, batch, ta, tb, tc, conjA, conjB, beta, form):
 LAYOUTS = [(False, False, False, 0, 1, 0), (True, False, True, 1, 0, 1), (False, True, False, 1, 1, 1)]
 
 # register kernel: one entry; one block and one beyond it; K of one tile, one
-# more, a ragged tile in a cut reduction; the last size of the 4096 block-tile
+# more, a ragged tile in a cut reduction; the last size of the 5120 block-tile
 # rule; tiles of 32 x 16, 16 x 32 and 32 x 32; long reductions at their limits
 FRAG = [(1, 1, 1, 1), (16, 16, 16, 1), (17, 15, 17, 3), (4, 4, 480, 1), (33, 16, 33, 2), (16, 256, 4096, 1),
-        (256, 256, 256, 1), (500, 40, 40, 1), (2, 3000, 31, 2), (48, 640, 601, 1), (80, 128, 5000, 1),
+        (256, 320, 256, 1), (500, 40, 40, 1), (2, 3000, 31, 2), (48, 640, 601, 1), (80, 128, 5000, 1),
         (10, 10, 70001, 1), (83850, 10, 10, 1), (9, 120, 20000, 2), (64, 64, 64, 16)]
 
 
