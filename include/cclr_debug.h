@@ -175,6 +175,12 @@ int cclr_dbg_fixed_ws_peak(const cclr_ctx* ctx, long long* bytes);
  * Host pointers.  CCLR_ENOTCONV if the QR iteration does not converge. */
 int cclr_dbg_small_eig(int n, const cclr_c64* H, int nroots, cclr_c64* w, cclr_c64* theta, cclr_c64* vecs);
 
+/* Smallest and largest |eigenvalue| of the leading m[r] x m[r] block of each
+ * of nr host matrices G[r] (ld x ld row-major, 1 <= ld <= 120, m[r] <= ld), the
+ * conditioning estimate of the damped solves: out[2 r], out[2 r + 1] (zeros
+ * for m[r] < 1).  Host pointers. */
+int cclr_dbg_ritz(int nr, int ld, const int* m, const cclr_c64* G, double* out);
+
 /* Autotuner record: writes up to cap bytes of text, one line per tuned
  * GEMM shape class: "MxNxK bB layoutL timed mxNxK bb: variant=ms ... -> chosen"
  * (the product's shape, then the part of it that was timed: at most 8192 rows

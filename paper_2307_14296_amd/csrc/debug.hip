@@ -414,6 +414,28 @@ int cclr_dbg_fixed_ws_peak(const cclr_ctx* c, long long* bytes) {
   return CCLR_OK;
 }
 
+int cclr_dbg_ritz(int nr, int ld, const int* m, const cclr_c64* G, double* out) {
+  void* d = nullptr;
+  int rc = CCLR_OK;
+  try {
+    REQUIRE(nr >= 1 && ld >= 1 && ld <= kSmallEigMax && m && G && out, CCLR_EINVAL, "ritz: bad arguments");
+    for (int r = 0; r < nr; ++r) REQUIRE(m[r] <= ld, CCLR_EINVAL, "ritz: block larger than the matrix");
+    const size_t ng = (size_t)nr * ld * ld, nw = (size_t)nr * ld * (ld + 1);
+    HIPCHK(hipMalloc(&d, sizeof(cplx) * (ng + nw) + sizeof(double) * 2 * nr + sizeof(int) * nr));
+    cplx *g = (cplx*)d, *w = g + ng;
+    double* o = (double*)(w + nw);
+    int* md = (int*)(o + 2 * nr);
+    HIPCHK(hipMemcpy(g, G, sizeof(cplx) * ng, hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(md, m, sizeof(int) * nr, hipMemcpyHostToDevice));
+    launch_ritz(nr, md, g, ld, w, o, nullptr);
+    HIPCHK(hipMemcpy(out, o, sizeof(double) * 2 * nr, hipMemcpyDeviceToHost));
+  } catch (const CclrError& e) {
+    rc = e.code;
+  }
+  if (d) (void)hipFree(d);
+  return rc;
+}
+
 int cclr_dbg_small_eig(int n, const cclr_c64* H, int nroots, cclr_c64* w, cclr_c64* theta, cclr_c64* vecs) {
   void* dev = nullptr;
   int rc = CCLR_OK;

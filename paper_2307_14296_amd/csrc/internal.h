@@ -195,6 +195,11 @@ constexpr int kSmallEigMax = 120;
 size_t small_eig_work_elems(int n);
 void launch_small_eig(int n, const cplx* Hu, const cplx* Hl, int ld, cplx* work, int nroots, cplx* coef, cplx* coef2,
                       int ldc, cplx* theta, cplx* wall, int* status, hipStream_t st);
+// smallest and largest |eigenvalue| of the leading m[r] x m[r] blocks of
+// G[r] (ld x ld, ld <= kSmallEigMax, m[r] <= ld), r < nr: out[2 r], out[2 r + 1]
+// (zeros where m[r] < 1 or without convergence); m, out and work (nr ld (ld + 1)
+// elements) on the device
+void launch_ritz(int nr, const int* m, const cplx* G, int ld, cplx* work, double* out, hipStream_t st);
 // products with K <= 32 on the vector ALU (returns false if the form does not apply)
 bool launch_zgemm_smallk(const GemmArgs& g, hipStream_t s);
 // products with at most 16 output columns (after transposing, if the unit-stride output index is n):

@@ -17,50 +17,96 @@
 #include <cmath>
 
 #include "internal.h"
-#include "eigen_small.h"
 
 namespace {
 constexpr int kThreads = 256;
-constexpr int kChunks = 512;
+constexpr int kChunks = 512;  // chunks of a dot product at most
 
-// vector (r, j) of a set with R slots per right-hand side
+// vector (r, j) of a set: position r rs + j js.  Trial vectors and transforms
+// are stored slot-major (rs = 1, js = right-hand sides): while every
+// right-hand side is active the transform reads slot j and writes its result
+// in place, without copies.
 struct VS {
   cplx* s;
   cplx* d;
-  int R;
+  int rs, js;
 };
 
-__device__ __forceinline__ const cplx* vs_s(const VS& v, int r, int j, i64 ov) { return v.s + ((i64)r * v.R + j) * ov; }
-__device__ __forceinline__ const cplx* vs_d(const VS& v, int r, int j, i64 nd) { return v.d + ((i64)r * v.R + j) * nd; }
+__device__ __forceinline__ const cplx* vs_s(const VS& v, int r, int j, i64 ov) {
+  return v.s + ((i64)r * v.rs + (i64)j * v.js) * ov;
+}
+__device__ __forceinline__ const cplx* vs_d(const VS& v, int r, int j, i64 nd) {
+  return v.d + ((i64)r * v.rs + (i64)j * v.js) * nd;
+}
 
 __device__ __forceinline__ cplx cmul(cplx a, cplx b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 __device__ __forceinline__ cplx cconjmul(cplx a, cplx b) { return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x); }
 
-__device__ cplx block_sum(cplx v) {
-  __shared__ double sr[kThreads], si[kThreads];
-  sr[threadIdx.x] = v.x;
-  si[threadIdx.x] = v.y;
-  __syncthreads();
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      sr[threadIdx.x] += sr[threadIdx.x + s];
-      si[threadIdx.x] += si[threadIdx.x + s];
+// sums over the block of N complex values per thread; the result is valid in
+// threads below N (value q in thread q).  Lane exchange within each wave, the
+// waves through LDS; the leading barrier lets calls follow one another.
+template <int N>
+__device__ __forceinline__ cplx block_sums(cplx (&v)[N]) {
+  __shared__ cplx ws[kThreads / 64][N];
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+    for (int off = 32; off > 0; off >>= 1) {
+      v[q].x += __shfl_xor(v[q].x, off, 64);
+      v[q].y += __shfl_xor(v[q].y, off, 64);
     }
-    __syncthreads();
-  }
-  cplx out = make_double2(sr[0], si[0]);
   __syncthreads();
-  return out;
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int q = 0; q < N; ++q) ws[threadIdx.x >> 6][q] = v[q];
+  __syncthreads();
+  cplx t = make_double2(0.0, 0.0);
+  if ((int)threadIdx.x < N)
+    for (int w = 0; w < kThreads / 64; ++w) {
+      t.x += ws[w][threadIdx.x].x;
+      t.y += ws[w][threadIdx.x].y;
+    }
+  return t;
 }
 
-// partial[(a*nj + j)*kChunks + chunk] = sum over chunk of conj(X[r][xj0+j]) * Y[r][yj],  r = act[a].
+// where the dot products of right-hand side r go: value j at p[r sr + j sj], conjugated if cj
+struct GramOut {
+  cplx* p;
+  i64 sr, sj;
+  int cj;
+};
+__device__ __forceinline__ void gram_put(const GramOut& o, int r, int j, cplx v) {
+  if (o.cj) v.y = -v.y;
+  o.p[r * o.sr + j * o.sj] = v;
+}
+
+// The second Gram-Schmidt pass of a right-hand side runs only where the first
+// took more than half of the correction's squared norm.  Same values and same
+// order in every block, so all blocks decide alike.
+struct Second {
+  const cplx* coef;  // coefficients of the first pass [r][ld]; null: no condition
+  const cplx* nrm2;  // squared norm before it [r]
+  int ld, nj;
+};
+__device__ __forceinline__ bool second_pass(const Second& q, int r) {
+  if (!q.coef) return true;
+  double p = 0.0;
+  for (int i = 0; i < q.nj; ++i) {
+    const cplx x = q.coef[(i64)r * q.ld + i];
+    p += x.x * x.x + x.y * x.y;
+  }
+  return !(p <= 0.5 * q.nrm2[r].x);
+}
+
+// conj(X[r][xj0+j]) . Y[r][yj] over chunk blockIdx.x, r = act[a]: to
+// partial[(a*nj + j)*chunks + chunk], or with one chunk straight to out.
 // One block takes kGramJ consecutive j, so each element of Y is read once for up to kGramJ vectors of X.
 constexpr int kGramJ = 4;
 __global__ __launch_bounds__(kThreads) void k_gram(VS X, int xj0, int nj, VS Y, int yj, const int* act, i64 ov, i64 nd,
-                                                   cplx* partial) {
-  const int a = blockIdx.z, j0 = blockIdx.y * kGramJ, chunk = blockIdx.x;
+                                                   cplx* partial, GramOut out, Second cond) {
+  const int a = blockIdx.z, j0 = blockIdx.y * kGramJ, chunk = blockIdx.x, chunks = gridDim.x;
   const int cnt = min(kGramJ, nj - j0);
   const int r = act[a];
+  if (!second_pass(cond, r)) return;
   const cplx* xs[kGramJ];
   const cplx* xd[kGramJ];
   for (int q = 0; q < kGramJ; ++q) {
@@ -71,10 +117,10 @@ __global__ __launch_bounds__(kThreads) void k_gram(VS X, int xj0, int nj, VS Y, 
   const cplx* ys = vs_s(Y, r, yj, ov);
   const cplx* yd = vs_d(Y, r, yj, nd);
   const i64 n = ov + nd;
-  const i64 per = (n + kChunks - 1) / kChunks;
+  const i64 per = (n + chunks - 1) / chunks;
   const i64 lo = chunk * per, hi = min(n, lo + per);
-  double accr[kGramJ], acci[kGramJ];
-  for (int q = 0; q < kGramJ; ++q) accr[q] = acci[q] = 0.0;
+  cplx acc[kGramJ];
+  for (int q = 0; q < kGramJ; ++q) acc[q] = make_double2(0.0, 0.0);
   for (i64 e = lo + threadIdx.x; e < hi; e += kThreads) {
     const bool single = e < ov;
     const cplx y = single ? ys[e] : yd[e - ov];
@@ -83,62 +129,120 @@ __global__ __launch_bounds__(kThreads) void k_gram(VS X, int xj0, int nj, VS Y, 
       if (q < cnt) {
         const cplx x = single ? xs[q][e] : xd[q][e - ov];
         const cplx p = cconjmul(x, y);
-        accr[q] += p.x;
-        acci[q] += p.y;
+        acc[q].x += p.x;
+        acc[q].y += p.y;
       }
     }
   }
-  // wave sums by lane exchange, then the four waves through LDS
-  __shared__ double ws[kThreads / 64][2 * kGramJ];
-#pragma unroll
-  for (int q = 0; q < kGramJ; ++q) {
-    for (int off = 32; off > 0; off >>= 1) {
-      accr[q] += __shfl_xor(accr[q], off, 64);
-      acci[q] += __shfl_xor(acci[q], off, 64);
-    }
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    for (int q = 0; q < kGramJ; ++q) {
-      ws[wave][2 * q] = accr[q];
-      ws[wave][2 * q + 1] = acci[q];
-    }
-  }
-  __syncthreads();
+  const cplx t = block_sums(acc);
   if ((int)threadIdx.x < cnt) {
-    const int q = threadIdx.x;
-    cplx t = make_double2(0.0, 0.0);
-    for (int w = 0; w < kThreads / 64; ++w) {
-      t.x += ws[w][2 * q];
-      t.y += ws[w][2 * q + 1];
-    }
-    partial[((i64)a * nj + j0 + q) * kChunks + chunk] = t;
+    const int j = j0 + threadIdx.x;
+    if (chunks == 1) gram_put(out, r, j, t);
+    else partial[((i64)a * nj + j) * chunks + chunk] = t;
   }
 }
 
-// out[r*ld + col0 + j] = sum of the chunk partials (conjugated if cj)
-__global__ __launch_bounds__(kThreads) void k_reduce(const cplx* partial, int nj, const int* act, cplx* out, int ld,
-                                                     int col0, int cj) {
-  const int p = blockIdx.x;
-  cplx acc = make_double2(0.0, 0.0);
-  for (int k = threadIdx.x; k < kChunks; k += kThreads) {
-    acc.x += partial[(i64)p * kChunks + k].x;
-    acc.y += partial[(i64)p * kChunks + k].y;
+// value j of active right-hand side a (blockIdx.x = a nj + j): the chunk partials summed, to out
+__global__ __launch_bounds__(kThreads) void k_reduce(const cplx* partial, int nj, int chunks, const int* act,
+                                                     GramOut out, Second cond) {
+  const int p = blockIdx.x, a = p / nj, r = act[a];
+  if (!second_pass(cond, r)) return;
+  cplx acc[1] = {make_double2(0.0, 0.0)};
+  for (int k = threadIdx.x; k < chunks; k += kThreads) {
+    acc[0].x += partial[(i64)p * chunks + k].x;
+    acc[0].y += partial[(i64)p * chunks + k].y;
   }
-  acc = block_sum(acc);
-  if (threadIdx.x == 0) {
-    const int a = p / nj, j = p % nj;
-    if (cj) acc.y = -acc.y;
-    out[(i64)act[a] * ld + col0 + j] = acc;
+  const cplx t = block_sums(acc);
+  if (threadIdx.x == 0) gram_put(out, r, p - a * nj, t);
+}
+
+// The products that extend the projected system by trial vector j, in one pass
+// over b_0 .. b_j and s_0 .. s_j: value 2 i is <b_i, s_j>, 2 i + 1 is
+// <s_i, b_j> (i < j), 2 j + 2 is <b_j, rhs>.  Block y takes kGramJ of the i,
+// the last one the right-hand side.
+struct Extend {
+  cplx *G, *C;  // G[r][i][j] (ld x ld), C[r][j]
+  int ld, j;
+};
+__device__ __forceinline__ void extend_put(const Extend& x, int r, int v, cplx t) {
+  const int j = x.j, i = v >> 1;
+  cplx* G = x.G + (i64)r * x.ld * x.ld;
+  if (v == 2 * j + 2) x.C[(i64)r * x.ld + j] = t;
+  else if (!(v & 1)) G[(i64)i * x.ld + j] = t;
+  else if (i < j) G[(i64)j * x.ld + i] = make_double2(t.x, -t.y);  // <b_j, s_i>
+}
+__global__ __launch_bounds__(kThreads) void k_extend(VS B, VS S, VS X, const int* act, i64 ov, i64 nd, cplx* partial,
+                                                     Extend out) {
+  const int a = blockIdx.z, chunk = blockIdx.x, chunks = gridDim.x, r = act[a], j = out.j, nv = 2 * j + 3;
+  const i64 n = ov + nd, per = (n + chunks - 1) / chunks, lo = chunk * per, hi = min(n, lo + per);
+  const cplx *bs = vs_s(B, r, j, ov), *bd = vs_d(B, r, j, nd);
+  cplx acc[2 * kGramJ];
+  for (int q = 0; q < 2 * kGramJ; ++q) acc[q] = make_double2(0.0, 0.0);
+  const bool last = blockIdx.y + 1 == gridDim.y;
+  const int i0 = blockIdx.y * kGramJ, cnt = last ? 1 : min(kGramJ, j + 1 - i0);
+  if (last) {
+    const cplx *xs = vs_s(X, r, 0, ov), *xd = vs_d(X, r, 0, nd);
+    for (i64 e = lo + threadIdx.x; e < hi; e += kThreads) {
+      const bool single = e < ov;
+      const cplx p = cconjmul(single ? bs[e] : bd[e - ov], single ? xs[e] : xd[e - ov]);
+      acc[0].x += p.x;
+      acc[0].y += p.y;
+    }
+  } else {
+    const cplx *ss = vs_s(S, r, j, ov), *sd = vs_d(S, r, j, nd);
+    const cplx *us[kGramJ], *ud[kGramJ], *ts[kGramJ], *td[kGramJ];
+    for (int q = 0; q < kGramJ; ++q) {
+      const int i = i0 + min(q, cnt - 1);
+      us[q] = vs_s(B, r, i, ov), ud[q] = vs_d(B, r, i, nd);
+      ts[q] = vs_s(S, r, i, ov), td[q] = vs_d(S, r, i, nd);
+    }
+    for (i64 e = lo + threadIdx.x; e < hi; e += kThreads) {
+      const bool single = e < ov;
+      const cplx b = single ? bs[e] : bd[e - ov], t = single ? ss[e] : sd[e - ov];
+#pragma unroll
+      for (int q = 0; q < kGramJ; ++q) {
+        if (q < cnt) {
+          const cplx p = cconjmul(single ? us[q][e] : ud[q][e - ov], t);
+          const cplx w = cconjmul(single ? ts[q][e] : td[q][e - ov], b);
+          acc[2 * q].x += p.x;
+          acc[2 * q].y += p.y;
+          acc[2 * q + 1].x += w.x;
+          acc[2 * q + 1].y += w.y;
+        }
+      }
+    }
   }
+  const cplx t = block_sums(acc);
+  if ((int)threadIdx.x < (last ? 1 : 2 * cnt)) {
+    const int v = last ? 2 * j + 2 : 2 * i0 + threadIdx.x;
+    if (chunks == 1) extend_put(out, r, v, t);
+    else partial[((i64)a * nv + v) * chunks + chunk] = t;
+  }
+}
+__global__ __launch_bounds__(kThreads) void k_extend_reduce(const cplx* partial, int chunks, const int* act,
+                                                            Extend out) {
+  const int p = blockIdx.x, nv = 2 * out.j + 3, a = p / nv;
+  cplx acc[1] = {make_double2(0.0, 0.0)};
+  for (int k = threadIdx.x; k < chunks; k += kThreads) {
+    acc[0].x += partial[(i64)p * chunks + k].x;
+    acc[0].y += partial[(i64)p * chunks + k].y;
+  }
+  const cplx t = block_sums(acc);
+  if (threadIdx.x == 0) extend_put(out, act[a], p - a * nv, t);
 }
 
 // out[r][oj] = (acc ? out : 0) + sign * sum_j coef[r][j] X[r][xj0 + j] + (use_y ? Y[r][yj] : 0)
-__global__ __launch_bounds__(kThreads) void k_lincomb(VS out, int oj, VS X, int xj0, int nj, const cplx* coef, int ldc,
-                                                      double sign, VS Y, int yj, int use_y, int acc_out,
-                                                      const int* act, i64 ov, i64 nd) {
+// over nj (or, if given, cnt[r]) vectors.  With partial, the squared norm of
+// the result of each block goes to partial[a][blockIdx.x] (straight to nrm[r]
+// with one block).
+__global__ __launch_bounds__(kThreads) void k_lincomb(VS out, int oj, VS X, int xj0, int nj, const int* cnt,
+                                                      const cplx* coef, int ldc, double sign, VS Y, int yj, int use_y,
+                                                      int acc_out, const int* act, i64 ov, i64 nd, cplx* partial,
+                                                      cplx* nrm, Second cond) {
   __shared__ cplx c[128];
   const int a = blockIdx.y, r = act[a];
+  if (!second_pass(cond, r)) return;
+  if (cnt) nj = cnt[r];
   for (int j = threadIdx.x; j < nj; j += kThreads) {
     const cplx t = coef[(i64)r * ldc + j];
     c[j] = make_double2(sign * t.x, sign * t.y);
@@ -147,6 +251,7 @@ __global__ __launch_bounds__(kThreads) void k_lincomb(VS out, int oj, VS X, int 
   const i64 n = ov + nd;
   cplx* os = (cplx*)vs_s(out, r, oj, ov);
   cplx* od = (cplx*)vs_d(out, r, oj, nd);
+  cplx nr[1] = {make_double2(0.0, 0.0)};
   for (i64 e = (i64)blockIdx.x * kThreads + threadIdx.x; e < n; e += (i64)gridDim.x * kThreads) {
     cplx y = make_double2(0.0, 0.0);
     if (acc_out) y = e < ov ? os[e] : od[e - ov];
@@ -165,6 +270,68 @@ __global__ __launch_bounds__(kThreads) void k_lincomb(VS out, int oj, VS X, int 
     }
     if (e < ov) os[e] = y;
     else od[e - ov] = y;
+    nr[0].x += y.x * y.x + y.y * y.y;
+  }
+  if (!partial) return;
+  const cplx t = block_sums(nr);
+  if (threadIdx.x == 0) {
+    if (gridDim.x == 1) nrm[r] = t;
+    else partial[(i64)a * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+// Residual R = rhs + sum_j beta[r][j] S[r][j] and correction E = (z - D)^-1 R
+// in one pass: E is stored, R itself is needed for its norm only.  |R|^2 and
+// |E|^2 of each block to partial[2 a gridDim.x ..] and the next gridDim.x,
+// or with one block to nrm[r] and nrm[ldn + r].
+__global__ __launch_bounds__(kThreads) void k_residual(VS E, VS S, int nj, const cplx* beta, int ldb, VS X,
+                                                       const cplx* z, const cplx* diag, const int* act, i64 ov, i64 nd,
+                                                       cplx* partial, cplx* nrm, int ldn) {
+  __shared__ cplx c[128];
+  const int a = blockIdx.y, r = act[a];
+  for (int j = threadIdx.x; j < nj; j += kThreads) c[j] = beta[(i64)r * ldb + j];
+  __syncthreads();
+  const i64 n = ov + nd;
+  cplx *es = (cplx*)vs_s(E, r, 0, ov), *ed = (cplx*)vs_d(E, r, 0, nd);
+  const cplx *xs = vs_s(X, r, 0, ov), *xd = vs_d(X, r, 0, nd);
+  const cplx zr = z[r];
+  cplx nr[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+  for (i64 e = (i64)blockIdx.x * kThreads + threadIdx.x; e < n; e += (i64)gridDim.x * kThreads) {
+    cplx y = make_double2(0.0, 0.0);
+#pragma unroll 4
+    for (int j = 0; j < nj; ++j) {
+      const cplx x = e < ov ? vs_s(S, r, j, ov)[e] : vs_d(S, r, j, nd)[e - ov];
+      const cplx p = cmul(c[j], x);
+      y.x += p.x;
+      y.y += p.y;
+    }
+    const cplx x = e < ov ? xs[e] : xd[e - ov], dd = diag[e];
+    y.x += x.x;
+    y.y += x.y;
+    const cplx w = make_double2(zr.x - dd.x, zr.y - dd.y);
+    const double den = w.x * w.x + w.y * w.y;
+    const cplx q = make_double2((y.x * w.x + y.y * w.y) / den, (y.y * w.x - y.x * w.y) / den);
+    if (e < ov) es[e] = q;
+    else ed[e - ov] = q;
+    nr[0].x += y.x * y.x + y.y * y.y;
+    nr[1].x += q.x * q.x + q.y * q.y;
+  }
+  const cplx t = block_sums(nr);
+  if (threadIdx.x < 2) {
+    if (gridDim.x == 1) nrm[(int)threadIdx.x * ldn + r] = t;
+    else partial[(2 * (i64)a + threadIdx.x) * gridDim.x + blockIdx.x] = t;
+  }
+}
+
+// copies between the active vectors X[act[a]][j] and the packed set p[a] (to_p: X -> p)
+__global__ __launch_bounds__(kThreads) void k_move(VS X, int j, VecSet p, int to_p, const int* act, i64 ov, i64 nd) {
+  const int a = blockIdx.y, r = act[a];
+  cplx *xs = (cplx*)vs_s(X, r, j, ov), *xd = (cplx*)vs_d(X, r, j, nd), *ps = p.s + a * ov, *pd = p.d + a * nd;
+  for (i64 e = (i64)blockIdx.x * kThreads + threadIdx.x; e < ov + nd; e += (i64)gridDim.x * kThreads) {
+    cplx* x = e < ov ? xs + e : xd + (e - ov);
+    cplx* y = e < ov ? ps + e : pd + (e - ov);
+    if (to_p) *y = *x;
+    else *x = *y;
   }
 }
 
@@ -235,45 +402,59 @@ __global__ __launch_bounds__(kThreads) void k_pivot(VS out, VS X, const int* act
 
 // Solve G[r] beta[r] = -C[r] (order m, leading dim ld) by Gaussian
 // elimination with partial pivoting; one block per active right-hand side.
-// W is scratch [nact][ld][ld+1].
+// The augmented matrix is in LDS up to order kSolveLds, else in the scratch W
+// [nact][ld][ld+1].  Bound by the latency of its m dependent steps: the first
+// wave finds the pivot by lane exchange and the back substitution takes one
+// column per step (26 us before, with both serial in one thread; 9 us now at
+// m = 20).
+constexpr int kSolveLds = 56;
 __global__ __launch_bounds__(kThreads) void k_small_solve(const cplx* G, const cplx* C, int m, int ld, cplx* W,
                                                           cplx* beta, int* singular, const int* act) {
-  const int a = blockIdx.x, r = act[a];
-  const int lw = ld + 1;
-  cplx* M = W + (i64)a * ld * lw;
-  for (int e = threadIdx.x; e < m * (m + 1); e += kThreads) {
+  __shared__ cplx sM[kSolveLds * (kSolveLds + 1)];
+  __shared__ int piv;
+  const int a = blockIdx.x, r = act[a], t = threadIdx.x;
+  const bool lds = m <= kSolveLds;
+  const int lw = lds ? m + 1 : ld + 1;
+  cplx* M = lds ? sM : W + (i64)a * ld * (ld + 1);
+  for (int e = t; e < m * (m + 1); e += kThreads) {
     const int i = e / (m + 1), j = e % (m + 1);
     cplx x = j < m ? G[((i64)r * ld + i) * ld + j] : C[(i64)r * ld + i];
     if (j == m) { x.x = -x.x; x.y = -x.y; }
     M[i * lw + j] = x;
   }
   __syncthreads();
-  __shared__ int piv;
   for (int k = 0; k < m; ++k) {
-    if (threadIdx.x == 0) {
+    if (t < 64) {  // largest entry of the column, the first one on ties
       double best = -1.0;
       int bi = k;
-      for (int i = k; i < m; ++i) {
+      for (int i = k + t; i < m; i += 64) {
         const cplx x = M[i * lw + k];
         const double mag = x.x * x.x + x.y * x.y;
         if (mag > best) { best = mag; bi = i; }
       }
-      piv = bi;
-      if (best == 0.0) singular[r] = 1;
+      for (int off = 32; off > 0; off >>= 1) {
+        const double ob = __shfl_xor(best, off, 64);
+        const int oi = __shfl_xor(bi, off, 64);
+        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+      }
+      if (t == 0) {
+        piv = bi;
+        if (best == 0.0) singular[r] = 1;
+      }
     }
     __syncthreads();
     const int p = piv;
     if (p != k)
-      for (int j = threadIdx.x; j <= m; j += kThreads) {
-        const cplx t = M[k * lw + j];
+      for (int j = k + t; j <= m; j += kThreads) {
+        const cplx x = M[k * lw + j];
         M[k * lw + j] = M[p * lw + j];
-        M[p * lw + j] = t;
+        M[p * lw + j] = x;
       }
     __syncthreads();
     const cplx d = M[k * lw + k];
     const double den = d.x * d.x + d.y * d.y;
     const int w = m - k;  // columns k+1 .. m (m = right-hand side column)
-    for (int e = threadIdx.x; e < (m - k - 1) * w; e += kThreads) {
+    for (int e = t; e < (m - k - 1) * w; e += kThreads) {
       const int i = k + 1 + e / w, j = k + 1 + e % w;
       const cplx lik = M[i * lw + k];
       const cplx f = make_double2((lik.x * d.x + lik.y * d.y) / den, (lik.y * d.x - lik.x * d.y) / den);
@@ -283,29 +464,19 @@ __global__ __launch_bounds__(kThreads) void k_small_solve(const cplx* G, const c
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    for (int i = m - 1; i >= 0; --i) {
-      cplx s = M[i * lw + m];
-      for (int j = i + 1; j < m; ++j) {
-        const cplx b = beta[(i64)r * ld + j];
-        const cplx g = M[i * lw + j];
-        s.x -= g.x * b.x - g.y * b.y;
-        s.y -= g.x * b.y + g.y * b.x;
-      }
-      const cplx d = M[i * lw + i];
-      const double den = d.x * d.x + d.y * d.y;
-      beta[(i64)r * ld + i] = make_double2((s.x * d.x + s.y * d.y) / den, (s.y * d.x - s.x * d.y) / den);
+  // back substitution by columns: x_i is known once columns i+1 .. m-1 are eliminated
+  for (int i = m - 1; i >= 0; --i) {
+    const cplx d = M[i * lw + i], y = M[i * lw + m];
+    const double den = d.x * d.x + d.y * d.y;
+    const cplx x = make_double2((y.x * d.x + y.y * d.y) / den, (y.y * d.x - y.x * d.y) / den);
+    __syncthreads();
+    if (t == 0) beta[(i64)r * ld + i] = x;
+    for (int k = t; k < i; k += kThreads) {
+      const cplx g = M[k * lw + i];
+      M[k * lw + m].x -= g.x * x.x - g.y * x.y;
+      M[k * lw + m].y -= g.x * x.y + g.y * x.x;
     }
-  }
-}
-
-// G[r][row q][j] = vals[r][j] (as_row) or G[r][j][col q] = vals[r][j]
-__global__ void k_put(const cplx* vals, int nj, cplx* G, int ld, int q, int as_row, const int* act) {
-  const int r = act[blockIdx.x];
-  for (int j = threadIdx.x; j < nj; j += blockDim.x) {
-    const cplx x = vals[(i64)r * ld + j];
-    if (as_row) G[((i64)r * ld + q) * ld + j] = x;
-    else G[((i64)r * ld + j) * ld + q] = x;
+    __syncthreads();
   }
 }
 
@@ -314,6 +485,12 @@ unsigned vgrid(i64 n) {
   if (g > 2048) g = 2048;
   return (unsigned)std::max<i64>(g, 1);
 }
+// blocks of an element-wise pass that also sums: one for short vectors, so that the sum needs no second launch
+unsigned sgrid(i64 n) { return n <= 2048 ? 1u : vgrid(n); }
+// chunks of a dot product over n elements: about four elements a thread, so
+// that short vectors (o = 4, v = 16: 784 elements) take one block and no
+// second launch
+unsigned chunks_of(i64 n) { return (unsigned)std::max<i64>(1, std::min<i64>(kChunks, n / 1024)); }
 }  // namespace
 
 // --------------------------------------------------------------- driver
@@ -344,12 +521,12 @@ int davidson(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rhs, c
     v.n = nvec;
     return v;
   };
-  VecSet Bv = vbuf(nr * ms), Sv = vbuf(nr * ms), Rv = vbuf(nr), Ev = vbuf(nr), Xin = vbuf(nr), Xout = vbuf(nr);
+  VecSet Bv = vbuf(nr * ms), Sv = vbuf(nr * ms), Ev = vbuf(nr), Xin = vbuf(nr), Xout = vbuf(nr);
   VecSet Yv = vbuf(nr);                      // restart scratch
   VecSet RCv = refine ? vbuf(nr) : rhs;      // current right-hand side (the true residual after refinement)
-  const VS B{Bv.s, Bv.d, ms}, S{Sv.s, Sv.d, ms}, R{Rv.s, Rv.d, 1}, E{Ev.s, Ev.d, 1};
-  const VS XI{RCv.s, RCv.d, 1}, X0{rhs.s, rhs.d, 1}, XO{xout.s, xout.d, 1}, T{Xout.s, Xout.d, 1};
-  const VS YT{Yv.s, Yv.d, 1};
+  const VS B{Bv.s, Bv.d, 1, nr}, S{Sv.s, Sv.d, 1, nr}, E{Ev.s, Ev.d, 1, 0};
+  const VS XI{RCv.s, RCv.d, 1, 0}, X0{rhs.s, rhs.d, 1, 0}, XO{xout.s, xout.d, 1, 0}, T{Xout.s, Xout.d, 1, 0};
+  const VS YT{Yv.s, Yv.d, 1, 0};
   if (refine) {
     HIPCHK(hipMemcpyAsync(RCv.s, rhs.s, sizeof(cplx) * (size_t)nr * ov, hipMemcpyDeviceToDevice, st));
     HIPCHK(hipMemcpyAsync(RCv.d, rhs.d, sizeof(cplx) * (size_t)nr * nd, hipMemcpyDeviceToDevice, st));
@@ -358,11 +535,15 @@ int davidson(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rhs, c
   cplx* Cp = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr * ms);
   cplx* beta = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr * ms);
   cplx* coef = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr * ms);
-  cplx* tmpv = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr * ms);
+  cplx* coef2 = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr * ms);
+  cplx* tmpv = (cplx*)c->arena.get(sizeof(cplx) * 2 * (size_t)nr);  // |R|^2 and |E|^2 of each right-hand side
+  cplx* nrm = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr);       // |E|^2 after orthogonalization
   cplx* W = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr * ms * (ms + 1));
-  cplx* partial = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr * ms * kChunks);
+  cplx* partial = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nr * (2 * ms + 3) * kChunks);
   int* act_d = (int*)c->arena.get(sizeof(int) * nr);
   int* sing_d = (int*)c->arena.get(sizeof(int) * nr);
+  int* msub_d = (int*)c->arena.get(sizeof(int) * nr);
+  double* ritz_d = (double*)c->arena.get(sizeof(double) * 2 * nr);
   cplx* z_d = (cplx*)c->arena.get(sizeof(cplx) * nr);     // by right-hand side
   cplx* za_d = (cplx*)c->arena.get(sizeof(cplx) * nr);    // by active position (for the transform)
   launch_fill(G, (i64)nr * ms * ms, cx(0.0), st);
@@ -370,29 +551,43 @@ int davidson(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rhs, c
   HIPCHK(hipMemcpyAsync(z_d, zh, sizeof(cplx) * nr, hipMemcpyHostToDevice, st));
 
   int na = 0;
-  // out[r*ld + col0 + j] = <X[r][xj0+j], Y[r][yj]> for active r
-  auto gram = [&](VS X, int xj0, int nj, VS Y, int yj, cplx* out, int ld, int col0, int cj) {
+  const unsigned chunks = chunks_of(n);
+  const Second always{nullptr, nullptr, 0, 0};
+  // <X[r][xj0+j], Y[r][yj]> for active r and j < nj, to o
+  auto gram = [&](VS X, int xj0, int nj, VS Y, int yj, GramOut o, Second cond) {
     if (nj <= 0 || na <= 0) return;
-    hipLaunchKernelGGL(k_gram, dim3(kChunks, (nj + kGramJ - 1) / kGramJ, na), dim3(kThreads), 0, st, X, xj0, nj, Y,
-                       yj, act_d, ov, nd, partial);
-    hipLaunchKernelGGL(k_reduce, dim3(na * nj), dim3(kThreads), 0, st, partial, nj, act_d, out, ld, col0, cj);
+    hipLaunchKernelGGL(k_gram, dim3(chunks, (nj + kGramJ - 1) / kGramJ, na), dim3(kThreads), 0, st, X, xj0, nj, Y, yj,
+                       act_d, ov, nd, partial, o, cond);
+    if (chunks > 1)
+      hipLaunchKernelGGL(k_reduce, dim3(na * nj), dim3(kThreads), 0, st, partial, nj, (int)chunks, act_d, o, cond);
   };
-  auto lincomb = [&](VS out, int oj, VS X, int xj0, int nj, const cplx* cf, int ldc, double sign, VS Y, int yj,
+  auto to_row = [&](cplx* p) { return GramOut{p, ms, 1, 0}; };  // p[r][j], rows of length ms
+  auto to_one = [&](cplx* p) { return GramOut{p, 1, 0, 0}; };   // p[r]
+  auto lincomb = [&](VS out, int oj, VS X, int xj0, int nj, const int* cnt, const cplx* cf, double sign, VS Y, int yj,
                      int use_y, int acc) {
-    hipLaunchKernelGGL(k_lincomb, dim3(vgrid(n), na), dim3(kThreads), 0, st, out, oj, X, xj0, nj, cf, ldc, sign, Y,
-                       yj, use_y, acc, act_d, ov, nd);
+    hipLaunchKernelGGL(k_lincomb, dim3(vgrid(n), na), dim3(kThreads), 0, st, out, oj, X, xj0, nj, cnt, cf, ms, sign, Y,
+                       yj, use_y, acc, act_d, ov, nd, (cplx*)nullptr, (cplx*)nullptr, always);
+  };
+  // E -= sum_j cf[r][j] B[r][j] and |E|^2 of the result to nrm
+  auto project_out = [&](int nj, const cplx* cf, Second cond) {
+    const unsigned g = sgrid(n);
+    hipLaunchKernelGGL(k_lincomb, dim3(g, na), dim3(kThreads), 0, st, E, 0, B, 0, nj, (const int*)nullptr, cf, ms,
+                       -1.0, E, 0, 0, 1, act_d, ov, nd, partial, nrm, cond);
+    if (g > 1)
+      hipLaunchKernelGGL(k_reduce, dim3(na), dim3(kThreads), 0, st, partial, 1, (int)g, act_d, to_one(nrm), cond);
   };
   auto scale = [&](VS out, int oj, VS X, int xj, const cplx* nrm2, int mode) {
     hipLaunchKernelGGL(k_scale, dim3(vgrid(n), na), dim3(kThreads), 0, st, out, oj, X, xj, z_d, c->diag.c(), nrm2,
                        mode, act_d, ov, nd);
   };
-  auto fetch = [&](const cplx* src, std::vector<cplx>& h, int ld) {
-    h.resize((size_t)nr * ld);
-    HIPCHK(hipMemcpyAsync(h.data(), src, sizeof(cplx) * (size_t)nr * ld, hipMemcpyDeviceToHost, st));
+  auto fetch = [&](const cplx* src, std::vector<cplx>& h) {
+    h.resize((size_t)nr);
+    HIPCHK(hipMemcpyAsync(h.data(), src, sizeof(cplx) * (size_t)nr, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
   };
   std::vector<int> act;
   auto set_active = [&](const std::vector<int>& a2) {
+    if (a2 == act) return;
     act = a2;
     na = (int)act.size();
     if (!na) return;
@@ -406,8 +601,8 @@ int davidson(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rhs, c
   for (int r = 0; r < nr; ++r) all[r] = r;
   set_active(all);
   std::vector<cplx> hv;
-  gram(XI, 0, 1, XI, 0, tmpv, 1, 0, 0);
-  fetch(tmpv, hv, 1);
+  gram(XI, 0, 1, XI, 0, to_one(tmpv), always);
+  fetch(tmpv, hv);
   std::vector<double> xinorm(nr), rcnorm(nr), res(nr, 0.0);
   std::vector<int> msub(nr, 0), done(nr, 0), outer(nr, 0), accumulated(nr, 0);
   for (int r = 0; r < nr; ++r) {
@@ -431,63 +626,55 @@ int davidson(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rhs, c
   auto sigma = (side == CCLR_RIGHT) ? sigma_right : sigma_left;
   const int maxit = std::max(1, maxit_in);
   c->sigma_prec = lowp;
-  // projected solve and residual R = sum_i beta_i s_i + rhs_cur for the active set; returns the
-  // relative residual of each active right-hand side (by rhs index)
+  // x_a <- the transforms of the active vectors of slot xj of X, to slot yj of Y
+  // (in place when every right-hand side is active: the slots are contiguous)
+  auto transform = [&](VS X, int xj, VS Y, int yj) {
+    VecSet in = Xin, out = Xout;
+    in.n = out.n = na;
+    const bool whole = na == nr;
+    if (whole) {
+      in.s = X.s + (i64)xj * X.js * ov, in.d = X.d + (i64)xj * X.js * nd;
+      out.s = Y.s + (i64)yj * Y.js * ov, out.d = Y.d + (i64)yj * Y.js * nd;
+    } else {
+      hipLaunchKernelGGL(k_move, dim3(vgrid(n), na), dim3(kThreads), 0, st, X, xj, in, 1, act_d, ov, nd);
+    }
+    sigma(c, in, out, za_d);
+    if (!whole) hipLaunchKernelGGL(k_move, dim3(vgrid(n), na), dim3(kThreads), 0, st, Y, yj, out, 0, act_d, ov, nd);
+    nsigma += na;
+  };
+  // projected solve, residual R = sum_i beta_i s_i + rhs_cur and correction E = (z - D)^-1 R for
+  // the active set; |R|^2 of each right-hand side in hv
   auto project = [&](int m) {
     hipLaunchKernelGGL(k_small_solve, dim3(na), dim3(kThreads), 0, st, G, Cp, m, ms, W, beta, sing_d, act_d);
-    lincomb(R, 0, S, 0, m, beta, ms, 1.0, XI, 0, 1, 0);
-    gram(R, 0, 1, R, 0, tmpv, 1, 0, 0);
-    fetch(tmpv, hv, 1);
+    const unsigned g = sgrid(n);
+    hipLaunchKernelGGL(k_residual, dim3(g, na), dim3(kThreads), 0, st, E, S, m, beta, ms, XI, z_d, c->diag.c(), act_d,
+                       ov, nd, partial, tmpv, nr);
+    if (g > 1)
+      hipLaunchKernelGGL(k_reduce, dim3(2 * na), dim3(kThreads), 0, st, partial, 2, (int)g, act_d,
+                         GramOut{tmpv, 1, nr, 0}, always);
+    fetch(tmpv, hv);
   };
   // x += sum beta b, then the FP64 true residual into the current right-hand side
   auto refine_step = [&](const std::vector<int>& cand, int m) {
     set_active(cand);
-    lincomb(XO, 0, B, 0, m, beta, ms, 1.0, XO, 0, 0, 1);
-    for (int a = 0; a < na; ++a) {
-      const int r = act[a];
-      HIPCHK(hipMemcpyAsync(Xin.s + a * ov, xout.s + (i64)r * ov, sizeof(cplx) * ov, hipMemcpyDeviceToDevice, st));
-      HIPCHK(hipMemcpyAsync(Xin.d + a * nd, xout.d + (i64)r * nd, sizeof(cplx) * nd, hipMemcpyDeviceToDevice, st));
-    }
-    VecSet vin = Xin, vout = Xout;
-    vin.n = vout.n = na;
+    lincomb(XO, 0, B, 0, m, nullptr, beta, 1.0, XO, 0, 0, 1);
     c->sigma_prec = CCLR_FP64;
-    sigma(c, vin, vout, za_d);
+    transform(XO, 0, XI, 0);
     c->sigma_prec = lowp;
-    nsigma += na;
-    for (int a = 0; a < na; ++a) {
-      const int r = act[a];
-      HIPCHK(hipMemcpyAsync(RCv.s + (i64)r * ov, Xout.s + a * ov, sizeof(cplx) * ov, hipMemcpyDeviceToDevice, st));
-      HIPCHK(hipMemcpyAsync(RCv.d + (i64)r * nd, Xout.d + a * nd, sizeof(cplx) * nd, hipMemcpyDeviceToDevice, st));
-    }
-    lincomb(XI, 0, B, 0, 0, beta, ms, 1.0, X0, 0, 1, 1);  // rhs_cur = (A - z) x + rhs
-    gram(XI, 0, 1, XI, 0, tmpv, 1, 0, 0);
-    fetch(tmpv, hv, 1);
+    lincomb(XI, 0, B, 0, 0, nullptr, beta, 1.0, X0, 0, 1, 1);  // rhs_cur = (A - z) x + rhs
+    gram(XI, 0, 1, XI, 0, to_one(tmpv), always);
+    fetch(tmpv, hv);
   };
   while (na > 0) {
     // batched transform of the newest trial vectors
-    for (int a = 0; a < na; ++a) {
-      const int r = act[a];
-      HIPCHK(hipMemcpyAsync(Xin.s + a * ov, Bv.s + ((i64)r * ms + j) * ov, sizeof(cplx) * ov, hipMemcpyDeviceToDevice, st));
-      HIPCHK(hipMemcpyAsync(Xin.d + a * nd, Bv.d + ((i64)r * ms + j) * nd, sizeof(cplx) * nd, hipMemcpyDeviceToDevice, st));
-    }
-    VecSet vin = Xin, vout = Xout;
-    vin.n = vout.n = na;
-    sigma(c, vin, vout, za_d);
-    nsigma += na;
-    for (int a = 0; a < na; ++a) {
-      const int r = act[a];
-      HIPCHK(hipMemcpyAsync(Sv.s + ((i64)r * ms + j) * ov, Xout.s + a * ov, sizeof(cplx) * ov, hipMemcpyDeviceToDevice, st));
-      HIPCHK(hipMemcpyAsync(Sv.d + ((i64)r * ms + j) * nd, Xout.d + a * nd, sizeof(cplx) * nd, hipMemcpyDeviceToDevice, st));
-    }
+    transform(B, j, S, j);
     ++iters;
-    // extend the projected matrix by column j, row j and C'_j
-    gram(B, 0, j + 1, S, j, tmpv, ms, 0, 0);  // <b_i, s_j>
-    hipLaunchKernelGGL(k_put, dim3(na), dim3(128), 0, st, tmpv, j + 1, G, ms, j, 0, act_d);
-    if (j > 0) {
-      gram(S, 0, j, B, j, tmpv, ms, 0, 1);    // conj <s_i, b_j> = <b_j, s_i>
-      hipLaunchKernelGGL(k_put, dim3(na), dim3(128), 0, st, tmpv, j, G, ms, j, 1, act_d);
-    }
-    gram(B, j, 1, XI, 0, Cp, ms, j, 0);       // C'_j = <b_j, rhs_cur>
+    // extend the projected matrix by column j, row j and C'_j = <b_j, rhs_cur>
+    const Extend ex{G, Cp, ms, j};
+    hipLaunchKernelGGL(k_extend, dim3(chunks, (j + 1 + kGramJ - 1) / kGramJ + 1, na), dim3(kThreads), 0, st, B, S, XI,
+                       act_d, ov, nd, partial, ex);
+    if (chunks > 1)
+      hipLaunchKernelGGL(k_extend_reduce, dim3(na * (2 * j + 3)), dim3(kThreads), 0, st, partial, (int)chunks, act_d, ex);
     const int m = j + 1;
     project(m);
     std::vector<int> still, cand;
@@ -519,7 +706,7 @@ int davidson(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rhs, c
       }
       if (again.empty()) break;
       set_active(again);
-      gram(B, 0, m, XI, 0, Cp, ms, 0, 0);     // C' for the new right-hand side
+      gram(B, 0, m, XI, 0, to_row(Cp), always);  // C' for the new right-hand side
       project(m);
       cand.clear();
       for (int r : again) {
@@ -531,82 +718,52 @@ int davidson(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rhs, c
     if (still.empty() || iters >= maxit) break;
     std::sort(still.begin(), still.end());
     set_active(still);
-    // correction (z - D)^-1 R
-    scale(E, 0, R, 0, nullptr, 0);
     int nj = m;
     if (m == ms) {
       // restart from the current solution: b0 = x/|x|, s0 = (sum beta s)/|x|
-      lincomb(YT, 0, B, 0, m, beta, ms, 1.0, YT, 0, 0, 0);
-      lincomb(T, 0, S, 0, m, beta, ms, 1.0, T, 0, 0, 0);
-      gram(YT, 0, 1, YT, 0, tmpv, 1, 0, 0);
-      scale(B, 0, YT, 0, tmpv, 1);
-      scale(S, 0, T, 0, tmpv, 1);
-      gram(B, 0, 1, S, 0, tmpv, ms, 0, 0);
-      hipLaunchKernelGGL(k_put, dim3(na), dim3(128), 0, st, tmpv, 1, G, ms, 0, 0, act_d);
-      gram(B, 0, 1, XI, 0, Cp, ms, 0, 0);
+      lincomb(YT, 0, B, 0, m, nullptr, beta, 1.0, YT, 0, 0, 0);
+      lincomb(T, 0, S, 0, m, nullptr, beta, 1.0, T, 0, 0, 0);
+      gram(YT, 0, 1, YT, 0, to_one(nrm), always);
+      scale(B, 0, YT, 0, nrm, 1);
+      scale(S, 0, T, 0, nrm, 1);
+      gram(B, 0, 1, S, 0, GramOut{G, (i64)ms * ms, 0, 0}, always);
+      gram(B, 0, 1, XI, 0, to_row(Cp), always);
       nj = 1;
     }
-    // classical Gram-Schmidt against the orthonormal subspace, with a second
-    // pass only for the right-hand sides whose correction lost more than half
+    // classical Gram-Schmidt of the corrections against the orthonormal
+    // subspace, with a second pass only for the right-hand sides whose correction lost more than half
     // of its squared norm in the first (|e'|^2 = |e|^2 - sum |c_i|^2): a
     // vector that is not nearly inside the subspace is orthogonal to working
-    // accuracy after one pass (Daniel, Gragg, Kaufman and Stewart's criterion)
-    gram(E, 0, 1, E, 0, tmpv, 1, 0, 0);
-    gram(B, 0, nj, E, 0, coef, ms, 0, 0);
-    lincomb(E, 0, B, 0, nj, coef, ms, -1.0, E, 0, 0, 1);
-    {
-      std::vector<cplx> ch((size_t)nr * ms), nh(nr);
-      HIPCHK(hipMemcpyAsync(ch.data(), coef, sizeof(cplx) * ch.size(), hipMemcpyDeviceToHost, st));
-      HIPCHK(hipMemcpyAsync(nh.data(), tmpv, sizeof(cplx) * nr, hipMemcpyDeviceToHost, st));
-      HIPCHK(hipStreamSynchronize(st));
-      std::vector<int> again;
-      for (int r : act) {
-        double p = 0.0;
-        for (int i = 0; i < nj; ++i) {
-          const cplx x = ch[(size_t)r * ms + i];
-          p += x.x * x.x + x.y * x.y;
-        }
-        if (!(p <= 0.5 * nh[r].x)) again.push_back(r);
-      }
-      if (!again.empty()) {
-        const std::vector<int> keep = act;
-        set_active(again);
-        gram(B, 0, nj, E, 0, coef, ms, 0, 0);
-        lincomb(E, 0, B, 0, nj, coef, ms, -1.0, E, 0, 0, 1);
-        set_active(keep);
-      }
-    }
-    gram(E, 0, 1, E, 0, tmpv, 1, 0, 0);
+    // accuracy after one pass (Daniel, Gragg, Kaufman and Stewart's
+    // criterion).  The kernels of the second pass decide that themselves.
+    gram(B, 0, nj, E, 0, to_row(coef), always);
+    project_out(nj, coef, always);
+    const Second second{coef, tmpv + nr, ms, nj};
+    gram(B, 0, nj, E, 0, to_row(coef2), second);
+    project_out(nj, coef2, second);
     j = nj;
-    scale(B, j, E, 0, tmpv, 1);
+    scale(B, j, E, 0, nrm, 1);
   }
   // solutions x_r = sum_i beta_i b_i over each right-hand side's final subspace
   // (added to the accumulated solution when refining)
-  for (int r = 0; r < nr; ++r) {
-    if (msub[r] == 0 || accumulated[r]) continue;
-    std::vector<int> one{r};
-    set_active(one);
-    lincomb(XO, 0, B, 0, msub[r], beta, ms, 1.0, XO, 0, 0, refine ? 1 : 0);
+  HIPCHK(hipMemcpyAsync(msub_d, msub.data(), sizeof(int) * nr, hipMemcpyHostToDevice, st));
+  {
+    std::vector<int> open;
+    for (int r = 0; r < nr; ++r)
+      if (msub[r] > 0 && !accumulated[r]) open.push_back(r);
+    set_active(open);
+    if (na) lincomb(XO, 0, B, 0, 0, msub_d, beta, 1.0, XO, 0, 0, refine ? 1 : 0);
   }
   c->sigma_prec = CCLR_FP64;
   // conditioning estimate: Ritz values of (A - z) on each final subspace
   double kappa = 0.0, ritz_min = 0.0;
   {
-    std::vector<cplx> Gh((size_t)nr * ms * ms);
-    HIPCHK(hipMemcpyAsync(Gh.data(), G, sizeof(cplx) * Gh.size(), hipMemcpyDeviceToHost, st));
+    launch_ritz(nr, msub_d, G, ms, W, ritz_d, st);
+    std::vector<double> rh(2 * (size_t)nr);
+    HIPCHK(hipMemcpyAsync(rh.data(), ritz_d, sizeof(double) * rh.size(), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     for (int r = 0; r < nr; ++r) {
-      const int m = msub[r];
-      if (m < 1) continue;
-      std::vector<eigsmall::zc> A((size_t)m * m), w, V;
-      for (int i = 0; i < m; ++i)
-        for (int jj = 0; jj < m; ++jj) {
-          const cplx g = Gh[((size_t)r * ms + i) * ms + jj];
-          A[(size_t)i * m + jj] = eigsmall::zc(g.x, g.y);
-        }
-      if (!eigsmall::eig(m, A, w, V)) continue;
-      double lo = 1e300, hi = 0.0;
-      for (const auto& x : w) lo = std::min(lo, std::abs(x)), hi = std::max(hi, std::abs(x));
+      const double lo = rh[2 * r], hi = rh[2 * r + 1];
       if (!(lo > 0.0) || !std::isfinite(hi)) continue;
       kappa = std::max(kappa, hi / lo);
       ritz_min = ritz_min > 0.0 ? std::min(ritz_min, lo) : lo;
@@ -711,8 +868,8 @@ int eom_davidson(cclr_ctx* c, int side, int nroots, double tol, int maxit_in, st
     return v;
   };
   VecSet Bv = vbuf(ms), Sv = vbuf(ms), Rv = vbuf(nroots), Ev = vbuf(nroots);
-  const VS B{Bv.s, Bv.d, 0}, S{Sv.s, Sv.d, 0};  // shared by every root (slot stride 0)
-  const VS R{Rv.s, Rv.d, 1}, E{Ev.s, Ev.d, 1}, X{xout.s, xout.d, 1};
+  const VS B{Bv.s, Bv.d, 0, 1}, S{Sv.s, Sv.d, 0, 1};  // shared by every root (stride 0)
+  const VS R{Rv.s, Rv.d, 1, 0}, E{Ev.s, Ev.d, 1, 0}, X{xout.s, xout.d, 1, 0};
   cplx* tmpv = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nroots * ms);
   cplx* coef = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nroots * ms);
   cplx* coef2 = (cplx*)c->arena.get(sizeof(cplx) * (size_t)nroots * ms);
@@ -729,15 +886,20 @@ int eom_davidson(cclr_ctx* c, int side, int nroots, double tol, int maxit_in, st
     na = (int)a.size();
     if (na) HIPCHK(hipMemcpyAsync(act_d, a.data(), sizeof(int) * na, hipMemcpyHostToDevice, st));
   };
+  const unsigned chunks = chunks_of(n);
+  const Second always{nullptr, nullptr, 0, 0};
+  // out[r ld + col0 + j] = <X[r][xj0+j], Y[r][yj]> for active r (conjugated if cj)
   auto gram = [&](VS Xs, int xj0, int nj, VS Ys, int yj, cplx* out, int ld, int col0, int cj) {
     if (nj <= 0 || na <= 0) return;
-    hipLaunchKernelGGL(k_gram, dim3(kChunks, (nj + kGramJ - 1) / kGramJ, na), dim3(kThreads), 0, st, Xs, xj0, nj,
-                       Ys, yj, act_d, ov, nd, partial);
-    hipLaunchKernelGGL(k_reduce, dim3(na * nj), dim3(kThreads), 0, st, partial, nj, act_d, out, ld, col0, cj);
+    const GramOut o{out + col0, ld, 1, cj};
+    hipLaunchKernelGGL(k_gram, dim3(chunks, (nj + kGramJ - 1) / kGramJ, na), dim3(kThreads), 0, st, Xs, xj0, nj, Ys,
+                       yj, act_d, ov, nd, partial, o, always);
+    if (chunks > 1)
+      hipLaunchKernelGGL(k_reduce, dim3(na * nj), dim3(kThreads), 0, st, partial, nj, (int)chunks, act_d, o, always);
   };
   auto lincomb = [&](VS out, int oj, VS Xs, int xj0, int nj, const cplx* cf, int ldc, int acc) {
-    hipLaunchKernelGGL(k_lincomb, dim3(vgrid(n), na), dim3(kThreads), 0, st, out, oj, Xs, xj0, nj, cf, ldc, 1.0, Xs, 0,
-                       0, acc, act_d, ov, nd);
+    hipLaunchKernelGGL(k_lincomb, dim3(vgrid(n), na), dim3(kThreads), 0, st, out, oj, Xs, xj0, nj, (const int*)nullptr,
+                       cf, ldc, 1.0, Xs, 0, 0, acc, act_d, ov, nd, (cplx*)nullptr, (cplx*)nullptr, always);
   };
   auto fetch = [&](const cplx* src, std::vector<cplx>& h, size_t count) {
     h.resize(count);
@@ -763,8 +925,8 @@ int eom_davidson(cclr_ctx* c, int side, int nroots, double tol, int maxit_in, st
     const double n0 = std::sqrt(std::max(hv[0].x, 0.0));
     for (int pass = 0; pass < 2 && m > 0; ++pass) {
       gram(B, 0, m, E, 0, coef, ms, 0, 0);
-      hipLaunchKernelGGL(k_lincomb, dim3(vgrid(n), 1), dim3(kThreads), 0, st, E, 0, B, 0, m, coef, ms, -1.0, E, 0, 0, 1,
-                         act_d, ov, nd);
+      hipLaunchKernelGGL(k_lincomb, dim3(vgrid(n), 1), dim3(kThreads), 0, st, E, 0, B, 0, m, (const int*)nullptr, coef,
+                         ms, -1.0, E, 0, 0, 1, act_d, ov, nd, (cplx*)nullptr, (cplx*)nullptr, always);
     }
     gram(E, 0, 1, E, 0, tmpv, 1, 0, 0);
     fetch(tmpv + k, hv, 1);
