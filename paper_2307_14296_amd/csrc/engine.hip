@@ -289,6 +289,106 @@ Group merge(const Ten& t, const char* l, const std::string& g) {
 }
 
 i64 labsize(const Ten& t, const char* l, char ch) { return t.dim[lpos(l, ch)]; }
+
+// One label of a group: its extent and its strides in the operand (a) and in
+// the output (c).
+struct Lab {
+  i64 dim, a, c;
+};
+struct Span {
+  i64 size = 1, stride = 0;
+  bool ok = true;
+  bool unit() const { return size == 1 || stride == 1; }
+};
+// the labels of `mask` merged into one index (as merge() does), by operand (what 0) or output strides
+Span span(const Lab* l, int n, unsigned mask, int what) {
+  Span r;
+  i64 expect = -1;
+  for (int q = n - 1; q >= 0; --q) {
+    if (!((mask >> q) & 1) || l[q].dim == 1) continue;
+    const i64 st = what ? l[q].c : l[q].a;
+    if (expect < 0) r.stride = st;
+    else if (st != expect) r.ok = false;
+    expect = st * l[q].dim;
+    r.size *= l[q].dim;
+  }
+  return r;
+}
+
+// Chooses how contract() lowers a product whose tensors do not nest: 0 for
+// one product with copies of the tensors that do not, else bit 0 / 1: copy A /
+// B, bits 2-7 the M labels and bits 8-13 the N labels that become batch
+// indices.  Estimated time in us: 3.5 for the product plus its padded work (16
+// x 16 blocks at 45 TFLOP/s) or its bytes at 4 TB/s, a tensor without a unit
+// stride in rows, columns or k counted four times (a 64-byte sector per
+// element); 4 plus its bytes for each copy.  At o=10, v=80, four vectors, the
+// copies of the doubles-sized outputs and of the W^ab_ej operand took 130 us of
+// a 1150 us transform.
+int cheapest_plan(const Ten& A, const char* la, const Ten& B, const char* lb, const Ten& C, const char* lc,
+                  const std::string& Lm, const std::string& Ln, const std::string& Lk, bool okA0, bool okB0, bool okC0,
+                  bool accumulate) {
+  const int nm = (int)Lm.size(), nn = (int)Ln.size(), nk = (int)Lk.size();
+  Lab M[6], N[6], KA[6], KB[6];
+  for (int q = 0; q < nm; ++q) {
+    const int d = lpos(la, Lm[q]);
+    M[q] = {A.dim[d], A.st[d], C.st[lpos(lc, Lm[q])]};
+  }
+  for (int q = 0; q < nn; ++q) {
+    const int d = lpos(lb, Ln[q]);
+    N[q] = {B.dim[d], B.st[d], C.st[lpos(lc, Ln[q])]};
+  }
+  for (int q = 0; q < nk; ++q) {
+    const int d = lpos(la, Lk[q]), e = lpos(lb, Lk[q]);
+    KA[q] = {A.dim[d], A.st[d], 0};
+    KB[q] = {B.dim[e], B.st[e], 0};
+  }
+  const unsigned am = (1u << nm) - 1, an = (1u << nn) - 1, ak = (1u << nk) - 1;
+  const Span ka = span(KA, nk, ak, 0), kb = span(KB, nk, ak, 0);
+  const double nA = (double)A.size(), nB = (double)B.size(), nC = (double)C.size(), k = (double)ka.size;
+  const double us = 16.0 / 4e6;  // of one element at 4 TB/s
+  auto up16 = [](i64 x) { return (double)((x + 15) / 16 * 16); };
+  auto product = [&](i64 m, i64 n, double nb, double bytes) {
+    return 3.5 + std::max(nb * up16(m) * up16(n) * k * 8.0 / 45e6, bytes * us);
+  };
+  const double cw = accumulate ? 2.0 : 1.0;  // reads and writes of an output element
+  double best;
+  {
+    const Span m = span(M, nm, am, 0), n = span(N, nn, an, 0), mc = span(M, nm, am, 1), nc = span(N, nn, an, 1);
+    const double fa = !okA0 || m.unit() || ka.unit() ? 1.0 : 4.0, fb = !okB0 || n.unit() || kb.unit() ? 1.0 : 4.0;
+    const double fc = !okC0 ? 1.0 : cw * (mc.unit() || nc.unit() ? 1.0 : 4.0);
+    best = product(m.size, n.size, 1.0, nA * fa + nB * fb + nC * fc);
+    if (!okA0) best += 4.0 + 2.0 * nA * us;
+    if (!okB0) best += 4.0 + 2.0 * nB * us;
+    if (!okC0) best += 4.0 + (1.0 + cw) * nC * us;
+  }
+  int pick = 0;
+  for (unsigned mm = 0; mm <= am; ++mm) {
+    const Span mc = span(M, nm, am & ~mm, 1), bc = span(M, nm, mm, 1), ma = span(M, nm, am & ~mm, 0),
+               ba = span(M, nm, mm, 0);
+    if (!mc.ok || !bc.ok) continue;
+    for (unsigned mn = 0; mn <= an; ++mn) {
+      const Span nc = span(N, nn, an & ~mn, 1), dc = span(N, nn, mn, 1), nb = span(N, nn, an & ~mn, 0),
+                 db = span(N, nn, mn, 0);
+      if (!nc.ok || !dc.ok || bc.size * dc.size >= 65536) continue;
+      for (int cp = 0; cp < 4; ++cp) {
+        const bool ca = cp & 1, cb = cp & 2;
+        if (!ca && !(ka.ok && ma.ok && ba.ok)) continue;
+        if (!cb && !(kb.ok && nb.ok && db.ok)) continue;
+        if (!mm && !mn && !cp) continue;
+        const double fa = ca || ma.unit() || ka.unit() ? 1.0 : 4.0, fb = cb || nb.unit() || kb.unit() ? 1.0 : 4.0;
+        const double fc = cw * (mc.unit() || nc.unit() ? 1.0 : 4.0);
+        double t = product(mc.size, nc.size, (double)(bc.size * dc.size), nA * fa + nB * fb + nC * fc);
+        if (ca) t += 4.0 + 2.0 * nA * us;
+        if (cb) t += 4.0 + 2.0 * nB * us;
+        if (t < best) {
+          best = t;
+          pick = cp | (int)(mm << 2) | (int)(mn << 8);
+        }
+      }
+    }
+  }
+  return pick;
+}
 }  // namespace
 
 void contract(cclr_ctx* c, cplx alpha, const Ten& A, const char* la, const Ten& B, const char* lb, const Ten& C,
@@ -325,49 +425,24 @@ void contract(cclr_ctx* c, cplx alpha, const Ten& A, const char* la, const Ten& 
 
   // Without shared batch labels, output labels of one operand that break the
   // nesting of the M (or N) group can become a batch index of their own (the
-  // other operand gets stride 0), which avoids copying large operands.  A
-  // small operand may be copied into the order the plan wants.
+  // other operand gets stride 0), which avoids copying operands or the output;
+  // an operand may also be copied into the order the plan wants.  Where the
+  // tensors as they are do not give one product, the plan of least estimated
+  // time is taken.
   if (Lb.empty()) {
-    const i64 small = (i64)1 << 22;
     struct Plan {
       std::string sm, rm, sn, rn;
       bool ca = false, cb = false;
-      double score = -1;
     } best;
-    const int nm = (int)Lm.size(), nn = (int)Ln.size();
-    const bool kshort = merge(A, la, Lk).size <= 32;
-    for (int ca = 0; ca < 2; ++ca)
-      for (int cbq = 0; cbq < 2; ++cbq) {
-        if ((ca && A.size() > small) || (cbq && B.size() > small)) continue;
-        if (best.score > 0 && (ca + cbq) > (int)best.ca + (int)best.cb) continue;  // fewer copies first
-        for (int mm = 0; mm < (1 << nm); ++mm)
-          for (int mn = 0; mn < (1 << nn); ++mn) {
-            std::string sm, rm, sn, rn;
-            for (int q = 0; q < nm; ++q) ((mm >> q) & 1 ? sm : rm) += Lm[q];
-            for (int q = 0; q < nn; ++q) ((mn >> q) & 1 ? sn : rn) += Ln[q];
-            const bool okA = ca || (merge(A, la, Lk).ok && merge(A, la, rm).ok && merge(A, la, sm).ok);
-            const bool okB = cbq || (merge(B, lb, Lk).ok && merge(B, lb, rn).ok && merge(B, lb, sn).ok);
-            if (!okA || !okB) continue;
-            if (!(merge(C, lc, rm).ok && merge(C, lc, rn).ok && merge(C, lc, sm).ok && merge(C, lc, sn).ok)) continue;
-            if (mm == 0 && mn == 0 && !ca && !cbq) continue;  // the plain plan below handles it
-            const i64 nbat = merge(C, lc, sm).size * merge(C, lc, sn).size;
-            if (nbat >= 65536) continue;
-            double score = (double)merge(C, lc, rm).size * (double)merge(C, lc, rn).size;
-            // a short reduction runs on the vector ALU and is bound by its output
-            // traffic: prefer plans whose output has a unit-stride M or N index
-            if (kshort) {
-              const Group gm = merge(C, lc, rm), gn = merge(C, lc, rn);
-              if ((gm.size > 1 && gm.stride == 1) || (gn.size > 1 && gn.stride == 1)) score *= 64.0;
-            }
-            const bool fewer = (ca + cbq) < (int)best.ca + (int)best.cb;
-            if (best.score < 0 || fewer || score > best.score) best = Plan{sm, rm, sn, rn, ca != 0, cbq != 0, score};
-          }
-      }
     const bool okA0 = merge(A, la, Lk).ok && merge(A, la, Lm).ok, okB0 = merge(B, lb, Lk).ok && merge(B, lb, Ln).ok,
                okC0 = merge(C, lc, Lm).ok && merge(C, lc, Ln).ok;
-    // bytes the plain path would copy
-    const i64 copied = (okA0 ? 0 : A.size()) + (okB0 ? 0 : B.size()) + (okC0 ? 0 : 2 * C.size());
-    if (!(okA0 && okB0 && okC0) && copied > small && best.score > 0) {
+    const int pick = okA0 && okB0 && okC0 ? 0 : cheapest_plan(A, la, B, lb, C, lc, Lm, Ln, Lk, okA0, okB0, okC0, accumulate);
+    if (pick) {
+      const unsigned mm = (pick >> 2) & 63, mn = (pick >> 8) & 63;
+      for (int q = 0; q < (int)Lm.size(); ++q) ((mm >> q) & 1 ? best.sm : best.rm) += Lm[q];
+      for (int q = 0; q < (int)Ln.size(); ++q) ((mn >> q) & 1 ? best.sn : best.rn) += Ln[q];
+      best.ca = pick & 1;
+      best.cb = pick & 2;
       Arena::Mark mk = c->arena.mark();
       Ten Aw = A, Bw = B;
       std::string law = la, lbw = lb;
