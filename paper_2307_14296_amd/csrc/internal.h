@@ -55,8 +55,8 @@ struct DevBuf {
 };
 
 // Bump allocator for temporaries.  Chunks are kept for reuse after a reset
-// (device allocation is slow and synchronizing); trim() releases the unused
-// ones at a quiet point.
+// (device allocation is slow and synchronizing); trim(keep) releases the
+// unused ones at a quiet point, down to `keep` bytes.
 struct Arena {
   cclr_ctx* ctx = nullptr;
   std::vector<DevBuf*> chunks;
@@ -78,7 +78,7 @@ struct Arena {
   struct Mark { size_t chunk, top; };
   Mark mark() const;
   void reset(Mark m);
-  void trim();
+  void trim(size_t keep = 0);
 };
 
 // ----------------------------------------------------------- tensor views
@@ -450,6 +450,8 @@ int solve_system(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rh
 void merge_conditioning(cclr_solve_info& dst, const cclr_solve_info& src);
 // nvec packed vectors from the arena
 VecSet packed_buf(cclr_ctx* c, int n);
+// idle arena memory (bytes) a context keeps at quiet points
+size_t arena_keep(const cclr_ctx* c);
 // how many of n vectors with the given working memory each fit in free device memory (>= 1)
 int fit_vectors(cclr_ctx* c, double bytes_per_vec, int n);
 void build_xi(cclr_ctx* c, const cplx* X, const VecSet& out);
