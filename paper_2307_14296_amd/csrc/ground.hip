@@ -245,7 +245,6 @@ std::complex<double> ccsd_residual(cclr_ctx* c, const VecSet& t, const VecSet& o
     g.ar = 1.0; g.ai = 0.0; g.beta = 0;
     tuned_gemm(c, g);
   }
-  launch_fill(out.s, o * v, cx(0.0), c->stream);
   launch_pack_sigma(1, (int)o, (int)v, X0.p, Xa.p, Xi.p, Xai.p, S1.p, out.s, out.d, nullptr, nullptr, nullptr,
                     c->stream, false);
   // energy: sum f_ia t^a_i + sum_(i>j,a>b) <ij||ab> tau^ab_ij

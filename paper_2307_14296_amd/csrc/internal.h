@@ -262,8 +262,9 @@ struct VecSet {
 };
 
 void launch_unpack(int nvec, int o, int v, const cplx* s, const cplx* d, cplx* r1, cplx* r2, hipStream_t st);
-// packed doubles -> ring layout rr[k][i][a][m][e] = r^ae_im
-void launch_unpack_ring(int nvec, int o, int v, const cplx* d, cplx* rr, hipStream_t st);
+// packed doubles -> the views a transform reads: ring[k][i][a][m][e] = r^ae_im,
+// hp[k][P][a][b] = r^ab_ij (pairs P = i > j), vp[k][i][j][Q] = r^ab_ij (pairs Q = a > b)
+void launch_unpack_views(int nvec, int o, int v, const cplx* d, cplx* ring, cplx* hp, cplx* vp, hipStream_t st);
 void launch_pack_full(int nvec, int o, int v, const cplx* r1, const cplx* r2, cplx* s, cplx* d, hipStream_t st);
 // pair packing of the last two indices: dst[r][AB] = src[r][a][b] (a > b)
 // X[P][Q] += alpha (d(p1,q1) F[p2][q2] - d(p1,q2) F[p2][q1] - d(p2,q1) F[p1][q2] + d(p2,q2) F[p1][q1])
@@ -273,8 +274,6 @@ void launch_pair_fold(int n, const cplx* F, cplx* X, double alpha, hipStream_t s
 void launch_fold_ov(int o, int v, const cplx* F, cplx* W, hipStream_t s);
 // dst[b][P][x] = src[b][p1][p2][x] for P = (p1 > p2) (src [nb][n][n][rest] -> dst [nb][n(n-1)/2][rest])
 void launch_pack_first_pair(i64 nb, int n, i64 rest, const cplx* src, cplx* dst, hipStream_t s);
-// the inverse for antisymmetric data: dst[b][i][j][x] = +-src[b][pair(i,j)][x], 0 on i == j
-void launch_unpack_first_pair(i64 nb, int n, i64 rest, const cplx* src, cplx* dst, hipStream_t s);
 struct cclr_ctx;
 // adds (sign = +1) or removes (sign = -1) the doubles' one-body term P(ab) F^b_e r^ae_ij
 // folded into the packed particle-ladder operator c->Wp
@@ -287,14 +286,15 @@ void launch_pair_antisym_acc(int v, int nc, const cplx* Y, cplx* W, i64 ldw, dou
 // dst[e][f][a][b] = W^ef_ab from Wp[EF][AB]
 void launch_unpack_vvvv(int v, const cplx* Wp, cplx* dst, hipStream_t s);
 void launch_pack_vvvv(int v, const cplx* W, cplx* Wp, hipStream_t s);
-// out(packed) += X0 + P(ab)Xa + P(ij)Xi + P(ab)P(ij)Xai  (any X may be null),
-// singles out += S1; then out -= z_k * r_k  (z may be null).  X0, Xa, Xi are
+// doubles out(packed) = (add ? out : 0) + X0 + P(ab)Xa + P(ij)Xi + P(ab)P(ij)Xai
+// (any X may be null), singles out = S1; then out -= z_k * r_k  (z may be null).  X0, Xa, Xi are
 // [k][i][j][a][b]; Xai is [k][i][j][a][b], or [k][i][a][j][b] if xai_ring; Xa
 // is [k][IJ][a][b] (pairs i > j only) if xa_half; Xi is [k][i][j][AB] (pairs
 // a > b only) if xi_vpacked.
 void launch_pack_sigma(int nvec, int o, int v, const cplx* X0, const cplx* Xa, const cplx* Xi, const cplx* Xai,
                        const cplx* S1, cplx* outs, cplx* outd, const cplx* zk, const cplx* rs, const cplx* rd,
-                       hipStream_t st, bool xai_ring = false, bool xa_half = false, bool xi_vpacked = false);
+                       hipStream_t st, bool xai_ring = false, bool xa_half = false, bool xi_vpacked = false,
+                       bool add = true);
 
 // ------------------------------------------------------------ context
 struct cclr_ctx {
@@ -426,7 +426,8 @@ void sigma_right(cclr_ctx* c, const VecSet& in, const VecSet& out, const cplx* z
 // other term and returns the ring and ladder products (not yet launched);
 // finish adds the hole ladder and packs the result once both have run.
 struct SigmaAcc {
-  Ten X0, Xa, Xi, Xai, S1, R1, R2;
+  Ten Xa, Xi, Xai, S1, R1;  // accumulators and the singles of the vectors
+  Ten ring, hp, vp;         // the doubles of the vectors (launch_unpack_views)
 };
 struct SigmaWork {
   Arena::Mark mk;

@@ -123,8 +123,7 @@ __device__ __forceinline__ void occ_pair(i64 P, int& hi, int& lo) {
 
 __device__ __forceinline__ cplx cneg(cplx x) { return make_double2(-x.x, -x.y); }
 
-// RING = false: out[k][p][q][a][b] (full r2); RING = true: out[k][p][a][q][b] (ring layout rr)
-template <bool RING>
+// out[k][i][j][a][b], the full antisymmetric r2
 __global__ __launch_bounds__(256) void k_unpack_t(int o, int v, const cplx* __restrict__ d, cplx* __restrict__ out) {
   __shared__ cplx s[PT][PT + 1];
   const i64 O2 = (i64)o * (o - 1) / 2, V2 = (i64)v * (v - 1) / 2;
@@ -132,9 +131,7 @@ __global__ __launch_bounds__(256) void k_unpack_t(int o, int v, const cplx* __re
   int ta, tb;
   tile_pair(blockIdx.x, ta, tb);
   const int a0 = ta * PT, b0 = tb * PT;
-  auto off = [&](int p, int q, int a, int b) -> i64 {
-    return RING ? ((((i64)k * o + p) * v + a) * o + q) * v + b : ((((i64)k * o + p) * o + q) * v + a) * v + b;
-  };
+  auto off = [&](int p, int q, int a, int b) -> i64 { return ((((i64)k * o + p) * o + q) * v + a) * v + b; };
   const cplx zero = make_double2(0.0, 0.0);
   if (y >= O2) {  // i == j: zeros on the tile and its transpose
     const int i = (int)(y - O2);
@@ -172,6 +169,69 @@ __global__ __launch_bounds__(256) void k_unpack_t(int o, int v, const cplx* __re
   }
 }
 
+// The three views of the packed doubles that a transform reads, in one pass:
+//   ring[k][i][a][j][b], hp[k][P][a][b] for the pairs P = (i > j) and
+//   vp[k][i][j][Q] for the pairs Q = (a > b), each with the signs of the
+//   antisymmetric images.  Every packed element is read once and written
+//   eight times (16 B + 128 B); with a pass per view, one of them through the
+//   full layout, it was four launches and 272 B.
+__global__ __launch_bounds__(256) void k_unpack_views(int o, int v, const cplx* __restrict__ d, cplx* __restrict__ ring,
+                                                      cplx* __restrict__ hp, cplx* __restrict__ vp) {
+  __shared__ cplx s[PT][PT + 1];
+  const i64 O2 = (i64)o * (o - 1) / 2, V2 = (i64)v * (v - 1) / 2;
+  const int k = blockIdx.z, y = blockIdx.y, tid = threadIdx.x;
+  int ta, tb;
+  tile_pair(blockIdx.x, ta, tb);
+  const int a0 = ta * PT, b0 = tb * PT;
+  auto ro = [&](int p, int q, int a, int b) -> i64 { return ((((i64)k * o + p) * v + a) * o + q) * v + b; };
+  auto vo = [&](int p, int q, i64 Q) -> i64 { return (((i64)k * o + p) * o + q) * V2 + Q; };
+  const cplx zero = make_double2(0.0, 0.0);
+  if (y >= O2) {  // i == j: zeros on the tile and its transpose
+    const int i = (int)(y - O2);
+    for (int e = tid; e < PT * PT; e += 256) {
+      const int r = e / PT, c = e % PT, a = a0 + r, b = b0 + c;
+      if (a < v && b < v) {
+        ring[ro(i, i, a, b)] = zero;
+        if (a > b) vp[vo(i, i, pair_index(a, b))] = zero;
+      }
+      if (ta != tb && b0 + r < v && a0 + c < v) ring[ro(i, i, b0 + r, a0 + c)] = zero;
+    }
+    return;
+  }
+  int i, j;
+  occ_pair(y, i, j);
+  const i64 row = (i64)k * O2 + y;
+  const cplx* __restrict__ dr = d + row * V2;
+  for (int e = tid; e < PT * PT; e += 256) {
+    const int r = e / PT, c = e % PT, a = a0 + r, b = b0 + c;
+    cplx x = zero;
+    if (a < v && b < v && a > b) {
+      const i64 Q = pair_index(a, b);
+      x = dr[Q];
+      vp[vo(i, j, Q)] = x;
+      vp[vo(j, i, Q)] = cneg(x);
+    }
+    s[r][c] = x;
+  }
+  __syncthreads();
+  auto put = [&](int a, int b, cplx x) {
+    ring[ro(i, j, a, b)] = x;
+    ring[ro(j, i, a, b)] = cneg(x);
+    hp[(row * v + a) * v + b] = x;
+  };
+  for (int e = tid; e < PT * PT; e += 256) {
+    const int r = e / PT, c = e % PT, a = a0 + r, b = b0 + c;
+    // a < b only on a diagonal tile, where s[c][r] holds the entry (b, a)
+    if (a < v && b < v) put(a, b, a > b ? s[r][c] : (a < b ? cneg(s[c][r]) : zero));
+  }
+  if (ta != tb) {
+    for (int e = tid; e < PT * PT; e += 256) {
+      const int r = e / PT, c = e % PT, b = b0 + r, a = a0 + c;
+      if (a < v && b < v) put(b, a, cneg(s[c][r]));  // entry (b, a) = -(a, b)
+    }
+  }
+}
+
 // full -> packed (takes the i>j, a>b entries)
 __global__ __launch_bounds__(256) void k_pack_full(int nvec, int o, int v, const cplx* __restrict__ r1,
                                                    const cplx* __restrict__ r2, cplx* __restrict__ s,
@@ -201,19 +261,36 @@ __global__ __launch_bounds__(256) void k_pack_full(int nvec, int o, int v, const
 }
 
 // packed sigma assembly with the antisymmetrizers applied on the fly:
-// out += X0 + P(ab) Xa + P(ij) Xi + P(ab)P(ij) Xai - z r (Xa, having no P(ij),
+// doubles out = (add ? out : 0) + X0 + P(ab) Xa + P(ij) Xi + P(ab)P(ij) Xai - z r (Xa, having no P(ij),
 // may hold the pairs i > j only: xa_half, layout [k][IJ][a][b]; Xi, having no
 // P(ab), the pairs a > b only: xi_vpacked, layout [k][i][j][AB]).  Doubles: one
 // workgroup per (vector, occupied pair i > j, tile pair); the images with
-// exchanged virtual indices are read with unit stride along a into LDS.
+// exchanged virtual indices are read with unit stride along a into LDS.  One
+// more row of workgroups (y = O2) writes the singles, outs = S1 - z r.
 __global__ __launch_bounds__(256) void k_pack_sigma_t(int o, int v, const cplx* __restrict__ X0,
                                                       const cplx* __restrict__ Xa, const cplx* __restrict__ Xi,
                                                       const cplx* __restrict__ Xai, cplx* __restrict__ outd,
                                                       const cplx* __restrict__ zk, const cplx* __restrict__ rd,
-                                                      int xai_ring, int xa_half, int xi_vpacked) {
+                                                      int xai_ring, int xa_half, int xi_vpacked, int add,
+                                                      const cplx* __restrict__ S1, const cplx* __restrict__ rs,
+                                                      cplx* __restrict__ outs) {
   __shared__ cplx s[PT][PT + 1];
   const i64 O2 = (i64)o * (o - 1) / 2, V2 = (i64)v * (v - 1) / 2;
   const int k = blockIdx.z, y = blockIdx.y, tid = threadIdx.x;
+  if (y >= O2) {
+    const i64 ov = (i64)o * v;
+    for (i64 e = (i64)blockIdx.x * 256 + tid; e < ov; e += (i64)gridDim.x * 256) {
+      const i64 q = k * ov + e;
+      cplx t = S1[q];
+      if (zk) {
+        const cplx z = zk[k], x = rs[q];
+        t.x -= z.x * x.x - z.y * x.y;
+        t.y -= z.x * x.y + z.y * x.x;
+      }
+      outs[q] = t;
+    }
+    return;
+  }
   int ta, tb, i, j;
   tile_pair(blockIdx.x, ta, tb);
   occ_pair(y, i, j);
@@ -246,7 +323,7 @@ __global__ __launch_bounds__(256) void k_pack_sigma_t(int o, int v, const cplx* 
     const int r = e / PT, c = e % PT, a = a0 + r, b = b0 + c;
     if (a >= v || b >= v || a <= b) continue;
     const i64 q = ((i64)k * O2 + y) * V2 + pair_index(a, b);
-    cplx t = outd[q];
+    cplx t = add ? outd[q] : make_double2(0.0, 0.0);
     const cplx sx = s[c][r];
     t.x += sx.x; t.y += sx.y;
     if (X0) { const cplx u = X0[at(i, j, a, b)]; t.x += u.x; t.y += u.y; }
@@ -267,23 +344,6 @@ __global__ __launch_bounds__(256) void k_pack_sigma_t(int o, int v, const cplx* 
       t.y -= z.x * x.y + z.y * x.x;
     }
     outd[q] = t;
-  }
-}
-
-// singles: outs += S1 - z r
-__global__ __launch_bounds__(256) void k_pack_sigma_s(int nvec, i64 ov, const cplx* __restrict__ S1,
-                                                      cplx* __restrict__ outs, const cplx* __restrict__ zk,
-                                                      const cplx* __restrict__ rs) {
-  const i64 total = (i64)nvec * ov;
-  for (i64 e = (i64)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (i64)gridDim.x * blockDim.x) {
-    cplx y = outs[e];
-    if (S1) { y.x += S1[e].x; y.y += S1[e].y; }
-    if (zk) {
-      const cplx z = zk[e / ov], x = rs[e];
-      y.x -= z.x * x.x - z.y * x.y;
-      y.y -= z.x * x.y + z.y * x.x;
-    }
-    outs[e] = y;
   }
 }
 
@@ -365,9 +425,10 @@ void launch_fill(cplx* p, i64 n, cplx val, hipStream_t s) {
   HIPCHK(hipGetLastError());
 }
 
-static dim3 perm_grid(int nvec, int o, int v, bool diag) {
+// one row of workgroups per occupied pair i > j and `more` further ones
+static dim3 perm_grid(int nvec, int o, int v, int more) {
   const int nt = (v + PT - 1) / PT;
-  const i64 rows = (i64)o * (o - 1) / 2 + (diag ? o : 0);
+  const i64 rows = (i64)o * (o - 1) / 2 + more;
   REQUIRE(nvec <= 65535 && rows <= 65535, CCLR_EINVAL, "too many vectors or occupied pairs for one permutation launch");
   return dim3((unsigned)(nt * (nt + 1) / 2), (unsigned)rows, (unsigned)nvec);
 }
@@ -375,7 +436,7 @@ static dim3 perm_grid(int nvec, int o, int v, bool diag) {
 void launch_unpack(int nvec, int o, int v, const cplx* s, const cplx* d, cplx* r1, cplx* r2, hipStream_t st) {
   if (nvec <= 0) return;
   if (r1) HIPCHK(hipMemcpyAsync(r1, s, sizeof(cplx) * (size_t)nvec * o * v, hipMemcpyDeviceToDevice, st));
-  hipLaunchKernelGGL(k_unpack_t<false>, perm_grid(nvec, o, v, true), dim3(256), 0, st, o, v, d, r2);
+  hipLaunchKernelGGL(k_unpack_t, perm_grid(nvec, o, v, o), dim3(256), 0, st, o, v, d, r2);
   HIPCHK(hipGetLastError());
 }
 
@@ -387,18 +448,16 @@ void launch_pack_full(int nvec, int o, int v, const cplx* r1, const cplx* r2, cp
 
 void launch_pack_sigma(int nvec, int o, int v, const cplx* X0, const cplx* Xa, const cplx* Xi, const cplx* Xai,
                        const cplx* S1, cplx* outs, cplx* outd, const cplx* zk, const cplx* rs, const cplx* rd,
-                       hipStream_t st, bool xai_ring, bool xa_half, bool xi_vpacked) {
+                       hipStream_t st, bool xai_ring, bool xa_half, bool xi_vpacked, bool add) {
   if (nvec <= 0) return;
-  const i64 ov = (i64)o * v;
-  hipLaunchKernelGGL(k_pack_sigma_s, dim3(grid_for((i64)nvec * ov)), dim3(256), 0, st, nvec, ov, S1, outs, zk, rs);
-  hipLaunchKernelGGL(k_pack_sigma_t, perm_grid(nvec, o, v, false), dim3(256), 0, st, o, v, X0, Xa, Xi, Xai, outd, zk,
-                     rd, xai_ring ? 1 : 0, xa_half ? 1 : 0, xi_vpacked ? 1 : 0);
+  hipLaunchKernelGGL(k_pack_sigma_t, perm_grid(nvec, o, v, 1), dim3(256), 0, st, o, v, X0, Xa, Xi, Xai, outd, zk, rd,
+                     xai_ring ? 1 : 0, xa_half ? 1 : 0, xi_vpacked ? 1 : 0, add ? 1 : 0, S1, rs, outs);
   HIPCHK(hipGetLastError());
 }
 
-void launch_unpack_ring(int nvec, int o, int v, const cplx* d, cplx* rr, hipStream_t st) {
+void launch_unpack_views(int nvec, int o, int v, const cplx* d, cplx* ring, cplx* hp, cplx* vp, hipStream_t st) {
   if (nvec <= 0) return;
-  hipLaunchKernelGGL(k_unpack_t<true>, perm_grid(nvec, o, v, true), dim3(256), 0, st, o, v, d, rr);
+  hipLaunchKernelGGL(k_unpack_views, perm_grid(nvec, o, v, o), dim3(256), 0, st, o, v, d, ring, hp, vp);
   HIPCHK(hipGetLastError());
 }
 

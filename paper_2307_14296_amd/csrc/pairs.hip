@@ -121,24 +121,6 @@ __global__ __launch_bounds__(256) void k_pack_first_pair(i64 nb, int n, i64 rest
   }
 }
 
-// dst[b][i][j][x] = src[b][IJ][x] (i > j), -src[b][JI][x] (i < j), 0 (i == j):
-// a leading packed pair unpacked (src [nb][n2][rest], dst [nb][n][n][rest])
-__global__ __launch_bounds__(256) void k_unpack_first_pair(i64 nb, int n, i64 rest, const cplx* __restrict__ src,
-                                                           cplx* __restrict__ dst) {
-  const i64 n2 = (i64)n * (n - 1) / 2, total = nb * n * n * rest;
-  for (i64 e = (i64)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (i64)gridDim.x * blockDim.x) {
-    const i64 x = e % rest, ij = e / rest % ((i64)n * n), b = e / (rest * n * n);
-    const int i = (int)(ij / n), j = (int)(ij % n);
-    cplx y = make_double2(0.0, 0.0);
-    if (i > j) y = src[(b * n2 + pair_index(i, j)) * rest + x];
-    else if (i < j) {
-      const cplx t = src[(b * n2 + pair_index(j, i)) * rest + x];
-      y = make_double2(-t.x, -t.y);
-    }
-    dst[e] = y;
-  }
-}
-
 // W[a][m][pair(a,x)] += (a > x ? 1 : -1) F[m][x] for x != a (W [v][o][V2], F [o][v]):
 // the singles term -sum_me F^m_e r^ea_im as a v-pair operator, added to the
 // pair-packed W^am_ef of the term 1/2 W^am_ef r^ef_im
@@ -167,13 +149,6 @@ void launch_pack_first_pair(i64 nb, int n, i64 rest, const cplx* src, cplx* dst,
   const i64 total = nb * ((i64)n * (n - 1) / 2) * rest;
   if (total <= 0) return;
   hipLaunchKernelGGL(k_pack_first_pair, dim3(grid_for(total)), dim3(256), 0, s, nb, n, rest, src, dst);
-  HIPCHK(hipGetLastError());
-}
-
-void launch_unpack_first_pair(i64 nb, int n, i64 rest, const cplx* src, cplx* dst, hipStream_t s) {
-  const i64 total = nb * n * (i64)n * rest;
-  if (total <= 0) return;
-  hipLaunchKernelGGL(k_unpack_first_pair, dim3(grid_for(total)), dim3(256), 0, s, nb, n, rest, src, dst);
   HIPCHK(hipGetLastError());
 }
 

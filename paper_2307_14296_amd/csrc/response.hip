@@ -23,10 +23,8 @@ Groups groups(cclr_ctx* c, i64 nv) {
 }
 
 void finish(cclr_ctx* c, const Groups& g, i64 nv, const VecSet& out) {
-  launch_fill(out.s, nv * c->ns(), cx(0.0), c->stream);
-  launch_fill(out.d, nv * c->nd(), cx(0.0), c->stream);
   launch_pack_sigma((int)nv, c->o, c->v, g.X0.p, g.Xa.p, g.Xi.p, g.Xai.p, g.S1.p, out.s, out.d, nullptr, nullptr,
-                    nullptr, c->stream);
+                    nullptr, c->stream, false, false, false, false);
 }
 
 Ten xblk(const cplx* X, cclr_ctx* c, const char* kinds) {

@@ -19,21 +19,23 @@
 
 namespace {
 
-// xi_vpacked: the P(ij) group only for the pairs a > b ([k][i][j][AB]; no P(ab) acts on it)
-SigmaAcc prepare(cclr_ctx* c, const VecSet& in, bool xi_vpacked) {
+// The accumulators are written whole by the first term of each group.  No
+// group without a permutation operator remains outside the packed ladders.
+SigmaAcc prepare(cclr_ctx* c, const VecSet& in) {
   const i64 o = c->o, v = c->v, k = in.n;
   SigmaAcc a;
   a.R1 = ten(in.s, {k, o, v});
-  a.R2 = tmp(c, {k, o, o, v, v});
-  launch_unpack((int)k, (int)o, (int)v, in.s, in.d, nullptr, a.R2.p, c->stream);
-  // no group without a permutation operator remains outside the packed ladders (X0 stays empty)
-  // P(ab) group of the pairs i > j only ([k][IJ][a][b]): no P(ij) acts on it
+  a.ring = tmp(c, {k, o, v, o, v});
+  a.hp = tmp(c, {k, c->O2(), v, v});
+  a.vp = tmp(c, {k, o, o, c->V2()});
+  launch_unpack_views((int)k, (int)o, (int)v, in.d, a.ring.p, a.hp.p, a.vp.p, c->stream);
+  // P(ab) group of the pairs i > j only ([k][IJ][a][b]): no P(ij) acts on it;
+  // P(ij) group of the pairs a > b only ([k][i][j][AB])
   a.Xa = tmp(c, {k, c->O2(), v, v});
-  a.Xi = xi_vpacked ? tmp(c, {k, o, o, c->V2()}) : tmp(c, {k, o, o, v, v});
-  // P(ab)P(ij) group in the ring layout [k][i][a][j][b], seen through a kijab view
-  a.Xai = reorder(tmp(c, {k, o, v, o, v}), "kiajb", "kijab");
+  a.Xi = tmp(c, {k, o, o, c->V2()});
+  // P(ab)P(ij) group in the ring layout [k][i][a][j][b]
+  a.Xai = tmp(c, {k, o, v, o, v});
   a.S1 = tmp(c, {k, o, v});
-  for (Ten* t : {&a.Xa, &a.Xi, &a.S1}) launch_fill(t->p, t->size(), cx(0.0), c->stream);
   return a;
 }
 
@@ -65,22 +67,19 @@ void op_gemm(cclr_ctx* c, const GemmArgs& g, int which) {
 }
 
 // Ring term  Z[(k,i,a),(j,b)] = sum_(m,e) R[(k,i,a),(m,e)] W[(m,e),(j,b)]  written into the
-// [k][i][a][j][b] accumulator (first writer: overwrites).  Right: W^mb_ej r^ae_im;
-// left: l^im_ae W^je_bm.  Unpacks the vectors into the ring layout (arena) and
-// returns the product; the caller launches it.
-GemmArgs ring_args(cclr_ctx* c, const VecSet& in, const Ten& Xai, bool right) {
-  const i64 o = c->o, v = c->v, ov = o * v, nv = in.n;
-  cplx* rr = (cplx*)c->arena.get(sizeof(cplx) * (size_t)(nv * ov * ov));
-  launch_unpack_ring((int)nv, (int)o, (int)v, in.d, rr, c->stream);
+// [k][i][a][j][b] accumulator (its only term).  Right: W^mb_ej r^ae_im;
+// left: l^im_ae W^je_bm.  The caller launches the product.
+GemmArgs ring_args(cclr_ctx* c, const VecSet& in, const SigmaAcc& a, bool right) {
+  const i64 ov = (i64)c->o * c->v, nv = in.n;
   GemmArgs g{};
   g.M = (int)(nv * ov);
   g.N = (int)ov;
   g.K = (int)ov;
   g.batch = 1;
-  g.A = rr; g.sAm = ov; g.sAk = 1;
+  g.A = a.ring.p; g.sAm = ov; g.sAk = 1;
   if (right) { g.B = c->WR.c(); g.sBk = 1; g.sBn = ov; }
   else { g.B = c->WL.c(); g.sBk = ov; g.sBn = 1; }
-  g.C = Xai.p; g.sCm = ov; g.sCn = 1;
+  g.C = a.Xai.p; g.sCm = ov; g.sCn = 1;
   g.ar = 1.0; g.ai = 0.0; g.beta = 0;
   return g;
 }
@@ -146,36 +145,26 @@ double gemm_flops(const GemmArgs& g) { return 8.0 * (double)g.M * (double)g.N * 
 namespace {
 // every term of the right transform except the ring and the two ladders
 void right_terms(cclr_ctx* c, const VecSet& in, SigmaAcc& a) {
-  const i64 o = c->o, v = c->v, nv = in.n;
+  const i64 o = c->o, v = c->v, nv = in.n, O2 = c->O2();
   const cplx one = cx(1.0), mone = cx(-1.0);
-  Ten Foo = ten(c->Foo, {o, o}), Fvv = ten(c->Fvv, {v, v}), Fov = ten(c->Fov, {o, v});
+  Ten Foo = ten(c->Foo, {o, o}), Fvv = ten(c->Fvv, {v, v});
   Ten Wooov = ten(c->Wooov, {o, o, o, v}), Wvovv = ten(c->Wvovv, {v, o, v, v});
   Ten WR = ten(c->WR, {o, v, o, v});
   // singles
-  contract(c, one, Fvv, "ae", a.R1, "kie", a.S1, "kia");
+  contract(c, one, Fvv, "ae", a.R1, "kie", a.S1, "kia", false);
   contract(c, mone, Foo, "mi", a.R1, "kma", a.S1, "kia");
   // W^ma_ei read from the ring operator WR[i][a][m][e]
   contract(c, one, WR, "iame", a.R1, "kme", a.S1, "kia");
   // r^ef_im with (i, m) unpacked and (e, f) packed, and r^ea_mn on the rows m > n: the pair
   // sums below run over each antisymmetric pair once
-  const bool pairs = o >= 2 && v >= 2;
-  Ten R2v, R2h;
-  if (pairs) {
-    R2h = tmp(c, {nv, c->O2(), v, v});
-    launch_pack_first_pair(nv, (int)o, v * v, a.R2.p, R2h.p, c->stream);
-    R2v = tmp(c, {nv, o, o, c->V2()});
-    launch_unpack_first_pair(nv, (int)o, c->V2(), in.d, R2v.p, c->stream);
-    // 1/2 W^am_ef r^ef_im - F^m_e r^ea_im = sum_(m, e>f) (W + X)^am_ef r^ef_im (X folded into WvovvP)
-    contract(c, one, ten(c->WvovvP, {v, o, c->V2()}), "amQ", R2v, "kimQ", a.S1, "kia");
-  } else {
-    contract(c, mone, Fov, "me", a.R2, "kimea", a.S1, "kia");
-  }
+  const Ten &R2v = a.vp, &R2h = a.hp;
+  // 1/2 W^am_ef r^ef_im - F^m_e r^ea_im = sum_(m, e>f) (W + X)^am_ef r^ef_im (X folded into WvovvP)
+  contract(c, one, ten(c->WvovvP, {v, o, c->V2()}), "amQ", R2v, "kimQ", a.S1, "kia");
   // 1/2 W^mn_ie r^ea_mn = sum_(m>n, e) W^mn_ie r^ea_mn
-  if (pairs) contract(c, one, ten(c->WooovH, {c->O2(), o, v}), "Pie", R2h, "kPea", a.S1, "kia");
+  contract(c, one, ten(c->WooovH, {O2, o, v}), "Pie", R2h, "kPea", a.S1, "kia");
   // doubles (the P(ij) group Xi holds the pairs a > b only: [k][i][j][AB])
-  const i64 O2 = c->O2();
-  if (O2 > 0) contract(c, mone, ten(c->WovooH, {o, v, O2}), "mbP", a.R1, "kma", a.Xa, "kPab");
-  if (pairs) contract(c, one, ten(c->WvvvoTP, {o, v, c->V2()}), "jeQ", a.R1, "kie", a.Xi, "kijQ");
+  contract(c, mone, ten(c->WovooH, {o, v, O2}), "mbP", a.R1, "kma", a.Xa, "kPab", false);
+  contract(c, one, ten(c->WvvvoTP, {o, v, c->V2()}), "jeQ", a.R1, "kie", a.Xi, "kijQ", false);
   {
     // P(ab) [W^bm_fe r^e_m t^af_ij - 1/2 V^nm_fe r^ea_mn t^fb_ij] = P(ab) t^af_ij Y_bf with
     // Y_bf = W^bm_fe r^e_m - 1/2 V^nm_fe r^eb_mn, and likewise
@@ -185,13 +174,13 @@ void right_terms(cclr_ctx* c, const VecSet& in, SigmaAcc& a) {
     // antisymmetry relabellings W^bm_fe = -W^bm_ef, V^nm_fe = V^mn_ef keep the reductions unit-stride
     contract(c, mone, Wvovv, "bmef", a.R1, "kme", Y, "kbf", false);
     // -1/2 V^mn_ef r^eb_mn = -sum_(m>n, e) V^mn_ef r^eb_mn on the (m>n) rows of r
-    if (pairs) contract(c, mone, ten(c->VoovvH, {c->O2(), v, v}), "Pef", R2h, "kPeb", Y, "kbf");
-    if (O2 > 0) contract(c, one, ten(c->t2H, {O2, v, v}), "Paf", Y, "kbf", a.Xa, "kPab");
+    contract(c, mone, ten(c->VoovvH, {O2, v, v}), "Pef", R2h, "kPeb", Y, "kbf");
+    contract(c, one, ten(c->t2H, {O2, v, v}), "Paf", Y, "kbf", a.Xa, "kPab");
     Ten Z = tmp(c, {nv, o, o});
     contract(c, one, Wooov, "nmje", a.R1, "kme", Z, "knj", false);
     // 1/2 V^nm_fe r^fe_jm = sum_(m, f>e) V^nm_fe r^fe_jm
-    if (pairs) contract(c, one, ten(c->VoovvP, {o, o, c->V2()}), "nmQ", R2v, "kjmQ", Z, "knj");
-    if (pairs) contract(c, mone, ten(c->t2P, {o, o, c->V2()}), "inQ", Z, "knj", a.Xi, "kijQ");
+    contract(c, one, ten(c->VoovvP, {o, o, c->V2()}), "nmQ", R2v, "kjmQ", Z, "knj");
+    contract(c, mone, ten(c->t2P, {o, o, c->V2()}), "inQ", Z, "knj", a.Xi, "kijQ");
   }
 }
 
@@ -213,19 +202,17 @@ struct SideStream {
 SigmaWork sigma_right_begin(cclr_ctx* c, const VecSet& in, const VecSet& out) {
   SigmaWork w;
   w.mk = c->arena.mark();
-  w.a = prepare(c, in, c->o >= 2 && c->v >= 2);
+  w.a = prepare(c, in);
   right_terms(c, in, w.a);
-  w.ring = ring_args(c, in, w.a.Xai, true);
+  w.ring = ring_args(c, in, w.a, true);
   w.ladder = ladder_args(c, in, out, true);
   return w;
 }
 
 void sigma_finish(cclr_ctx* c, SigmaWork& w, const VecSet& in, const VecSet& out, const cplx* z) {
-  const i64 o = c->o, v = c->v, nv = in.n;
   hole_ladder(c, in, out, true);
-  launch_fill(out.s, nv * o * v, cx(0.0), c->stream);
-  launch_pack_sigma((int)nv, (int)o, (int)v, w.a.X0.p, w.a.Xa.p, w.a.Xi.p, w.a.Xai.p, w.a.S1.p, out.s, out.d, z, in.s,
-                    in.d, c->stream, true, true, o >= 2 && v >= 2);
+  launch_pack_sigma(in.n, c->o, c->v, nullptr, w.a.Xa.p, w.a.Xi.p, w.a.Xai.p, w.a.S1.p, out.s, out.d, z, in.s, in.d,
+                    c->stream, true, true, true);
   c->arena.reset(w.mk);
 }
 
@@ -247,12 +234,12 @@ void sigma_right(cclr_ctx* c, const VecSet& in, const VecSet& out, const cplx* z
   }
   SigmaWork w;
   w.mk = c->arena.mark();
-  w.a = prepare(c, in, c->o >= 2 && c->v >= 2);
+  w.a = prepare(c, in);
   HIPCHK(hipEventRecord(c->ev_fork, c->stream));
   HIPCHK(hipStreamWaitEvent(c->side, c->ev_fork, 0));
   {
     SideStream on_side(c);
-    w.ring = ring_args(c, in, w.a.Xai, true);
+    w.ring = ring_args(c, in, w.a, true);
     op_gemm(c, w.ring, 2);
     w.ladder = ladder_args(c, in, out, true);
     timed(c, gemm_flops(w.ladder), [&]() { op_gemm(c, w.ladder, 0); });
@@ -264,60 +251,44 @@ void sigma_right(cclr_ctx* c, const VecSet& in, const VecSet& out, const cplx* z
 }
 
 void sigma_left(cclr_ctx* c, const VecSet& in, const VecSet& out, const cplx* z) {
-  const i64 o = c->o, v = c->v, nv = in.n;
+  const i64 o = c->o, v = c->v, nv = in.n, O2 = c->O2(), V2 = c->V2();
   Arena::Mark mk = c->arena.mark();
   const cplx one = cx(1.0), mone = cx(-1.0);
-  SigmaAcc a = prepare(c, in, false);
+  SigmaAcc a = prepare(c, in);
   // l^ef_im with (e, f) packed and l^ea_mn on the rows m > n, as in the right transform
-  const bool pairs = o >= 2 && v >= 2;
-  Ten R2v, R2h;
-  if (pairs) {
-    R2v = tmp(c, {nv, o, o, c->V2()});
-    launch_unpack_first_pair(nv, (int)o, c->V2(), in.d, R2v.p, c->stream);
-    R2h = tmp(c, {nv, c->O2(), v, v});
-    launch_pack_first_pair(nv, (int)o, v * v, a.R2.p, R2h.p, c->stream);
-  }
-  Ten Foo = ten(c->Foo, {o, o}), Fvv = ten(c->Fvv, {v, v}), Fov = ten(c->Fov, {o, v});
-  Ten Wooov = ten(c->Wooov, {o, o, o, v}), Wvovv = ten(c->Wvovv, {v, o, v, v});
-  Ten Voovv = Vblk(c, "oovv");
+  const Ten &R2v = a.vp, &R2h = a.hp;
+  Ten Foo = ten(c->Foo, {o, o}), Fvv = ten(c->Fvv, {v, v});
+  Ten Wooov = ten(c->Wooov, {o, o, o, v});
   Ten WL = ten(c->WL, {o, v, o, v});
   // G^e_a = -1/2 l^mn_af t^ef_mn ; G^i_m = 1/2 l^in_ef t^ef_mn  (SI, eqs. G_ea, G_mi)
   Ten Gvv = tmp(c, {nv, v, v}), Goo = tmp(c, {nv, o, o});
   // over the pairs once: -sum_(m>n, f) l^fa_mn t^fe_mn and sum_(n, e>f) l^ef_in t^ef_mn
-  if (pairs) {
-    contract(c, mone, R2h, "kPfa", ten(c->t2H, {c->O2(), v, v}), "Pfe", Gvv, "kea", false);
-    contract(c, one, R2v, "kinQ", ten(c->t2P, {o, o, c->V2()}), "mnQ", Goo, "kim", false);
-  } else {
-    launch_fill(Gvv.p, Gvv.size(), cx(0.0), c->stream);
-    launch_fill(Goo.p, Goo.size(), cx(0.0), c->stream);
-  }
+  contract(c, mone, R2h, "kPfa", ten(c->t2H, {O2, v, v}), "Pfe", Gvv, "kea", false);
+  contract(c, one, R2v, "kinQ", ten(c->t2P, {o, o, V2}), "mnQ", Goo, "kim", false);
   // singles
-  contract(c, one, a.R1, "kie", Fvv, "ea", a.S1, "kia");
+  contract(c, one, a.R1, "kie", Fvv, "ea", a.S1, "kia", false);
   contract(c, mone, a.R1, "kma", Foo, "im", a.S1, "kia");
-  if (pairs) {
-    // 1/2 l^im_ef W^ef_am over e > f; 1/2 l^mn_ae W^ie_mn = 1/2 l^ea_mn W^ie_mn over m > n
-    contract(c, one, R2v, "kimQ", ten(c->WvvvoLP, {v, o, c->V2()}), "amQ", a.S1, "kia");
-    contract(c, one, R2h, "kPea", ten(c->WovooH, {o, v, c->O2()}), "ieP", a.S1, "kia");
-  }
+  // 1/2 l^im_ef W^ef_am over e > f; 1/2 l^mn_ae W^ie_mn = 1/2 l^ea_mn W^ie_mn over m > n
+  contract(c, one, R2v, "kimQ", ten(c->WvvvoLP, {v, o, V2}), "amQ", a.S1, "kia");
+  contract(c, one, R2h, "kPea", ten(c->WovooH, {o, v, O2}), "ieP", a.S1, "kia");
   contract(c, mone, Gvv, "kfe", ten(c->WvovvL, {o, v, v, v}), "iafe", a.S1, "kia");  // W^ei_fa as [i][a][f][e]
   contract(c, mone, Goo, "knm", Wooov, "mina", a.S1, "kia");
   contract(c, one, a.R1, "kme", WL, "meia", a.S1, "kia");  // W^ie_am = WL[m][e][i][a]
   // doubles
-  op_gemm(c, ring_args(c, in, a.Xai, false), 3);
-  if (c->O2() > 0) {
-    contract(c, one, ten(c->VoovvH, {c->O2(), v, v}), "Pae", Gvv, "keb", a.Xa, "kPab");
-    contract(c, mone, a.R1, "kma", ten(c->WooovH, {c->O2(), o, v}), "Pmb", a.Xa, "kPab");
-  }
-  contract(c, mone, Voovv, "imab", Goo, "kjm", a.Xi, "kijab");
-  contract(c, one, a.R1, "kie", Wvovv, "ejab", a.Xi, "kijab");
-  contract(c, one, a.R1, "kia", Fov, "jb", a.Xai, "kijab");
+  op_gemm(c, ring_args(c, in, a, false), 3);
+  contract(c, one, ten(c->VoovvH, {O2, v, v}), "Pae", Gvv, "keb", a.Xa, "kPab", false);
+  contract(c, mone, a.R1, "kma", ten(c->WooovH, {O2, o, v}), "Pmb", a.Xa, "kPab");
+  // P(ij) group over the pairs a > b: -V^im_ab G^j_m + l^i_e W^ej_ab, and with the operator that
+  // carries the singles' F term folded in, W + X, X^ej_ab = d_ae F^j_b - d_be F^j_a, also
+  // P(ij)P(ab) l^i_a F^j_b = P(ij) l^i_e X^ej_ab
+  contract(c, mone, ten(c->VoovvP, {o, o, V2}), "imQ", Goo, "kjm", a.Xi, "kijQ", false);
+  contract(c, one, a.R1, "kie", ten(c->WvovvP, {v, o, V2}), "ejQ", a.Xi, "kijQ");
   {
     const GemmArgs g = ladder_args(c, in, out, false);
     timed(c, gemm_flops(g), [&]() { op_gemm(c, g, 1); });
   }
   hole_ladder(c, in, out, false);
-  launch_fill(out.s, nv * o * v, cx(0.0), c->stream);
-  launch_pack_sigma((int)nv, (int)o, (int)v, a.X0.p, a.Xa.p, a.Xi.p, a.Xai.p, a.S1.p, out.s, out.d, z, in.s, in.d,
-                    c->stream, true, true);
+  launch_pack_sigma((int)nv, (int)o, (int)v, nullptr, a.Xa.p, a.Xi.p, a.Xai.p, a.S1.p, out.s, out.d, z, in.s, in.d,
+                    c->stream, true, true, true);
   c->arena.reset(mk);
 }
