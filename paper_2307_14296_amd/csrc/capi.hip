@@ -4,6 +4,7 @@
 #include <complex>
 #include <cstring>
 #include <algorithm>
+#include <limits>
 #include <map>
 #include <mutex>
 
@@ -94,14 +95,40 @@ void check_finite(cclr_ctx* c, const cplx* p, i64 n, const char* what) {
   REQUIRE(!h, CCLR_EINVAL, std::string("non-finite value in ") + what);
 }
 
-void copy_in(cclr_ctx* c, DevBuf& dst, const cclr_c64* src, i64 n, const char* what) {
-  check_ptr(src, what);
-  dst.alloc(c, sizeof(cplx) * (size_t)n);
-  HIPCHK(hipMemcpyAsync(dst.p, src, sizeof(cplx) * (size_t)n, hipMemcpyDeviceToDevice, c->stream));
-  Arena::Mark mk = c->arena.mark();
-  check_finite(c, dst.c(), n, what);
-  c->arena.reset(mk);
+constexpr int kInputMarks = 8;
+
+// a new call's input check (marks of earlier calls mean nothing to it)
+InputCheck new_check(cclr_ctx* c) {
+  if (c->input_call == std::numeric_limits<int>::max()) {  // start over with clean marks
+    HIPCHK(hipMemsetAsync(c->input_bad, 0, sizeof(int) * kInputMarks, c->stream));
+    c->input_call = 0;
+  }
+  return InputCheck{c->input_bad, ++c->input_call, c->input_host};
 }
+
+// copies of several input arrays into the context, each checked while it is
+// copied; finish() waits for the stream and rejects the first array found
+// non-finite
+struct CheckedCopies {
+  cclr_ctx* c;
+  InputCheck chk;
+  std::vector<const char*> names;
+  explicit CheckedCopies(cclr_ctx* ctx) : c(ctx), chk(new_check(ctx)) {}
+  void copy(DevBuf& dst, const cclr_c64* src, i64 n, const char* what) {
+    check_ptr(src, what);
+    REQUIRE((int)names.size() < kInputMarks, CCLR_EINVAL, "too many input arrays");
+    dst.alloc(c, sizeof(cplx) * (size_t)n);
+    launch_copy_check((const cplx*)src, dst.c(), n, InputCheck{chk.bad + names.size(), chk.call, nullptr}, c->stream);
+    names.push_back(what);
+  }
+  void finish() {
+    int h[kInputMarks];
+    HIPCHK(hipMemcpyAsync(h, chk.bad, sizeof(h), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+    for (size_t q = 0; q < names.size(); ++q)
+      REQUIRE(h[q] != chk.call, CCLR_EINVAL, std::string("non-finite value in ") + names[q]);
+  }
+};
 
 void check_freqs(int n, const double* omega, const double* gamma) {
   REQUIRE(n >= 0, CCLR_EINVAL, "negative count");
@@ -113,21 +140,46 @@ void check_freqs(int n, const double* omega, const double* gamma) {
   }
 }
 
-// full (r1[n][o][v], r2[n][o][o][v][v]) -> packed
-void pack_in(cclr_ctx* c, int n, const cclr_c64* r1, const cclr_c64* r2, const VecSet& out, const char* what) {
+// full (r1[n][o][v], r2[n][o][o][v][v]) -> packed, marking chk if an entry is not finite
+void pack_in(cclr_ctx* c, int n, const cclr_c64* r1, const cclr_c64* r2, const VecSet& out, const char* what,
+             const InputCheck& chk, const Shifts& z = Shifts()) {
   check_ptr(r1, what);
   check_ptr(r2, what);
-  const i64 oovv = (i64)c->o * c->o * c->v * c->v;
-  launch_pack_full(n, c->o, c->v, (const cplx*)r1, (const cplx*)r2, out.s, out.d, c->stream);
-  check_finite(c, out.s, n * c->ns(), what);
-  check_finite(c, out.d, n * c->nd(), what);
-  (void)oovv;
+  launch_pack_full(n, c->o, c->v, (const cplx*)r1, (const cplx*)r2, out.s, out.d, c->stream, chk, z);
 }
 
-void unpack_out(cclr_ctx* c, const VecSet& in, cclr_c64* s1, cclr_c64* s2, const char* what) {
+// the same for a call that needs the outcome at once
+void pack_in_checked(cclr_ctx* c, int n, const cclr_c64* r1, const cclr_c64* r2, const VecSet& out,
+                     const char* what) {
+  const InputCheck chk = new_check(c);
+  pack_in(c, n, r1, r2, out, what, chk);
+  int h = 0;
+  HIPCHK(hipMemcpyAsync(&h, chk.bad, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
+  REQUIRE(h != chk.call, CCLR_EINVAL, std::string("non-finite value in ") + what);
+}
+
+// the call's shifts, with the launch that packs its vectors where they fit its arguments
+Shifts shifts_of(cclr_ctx* c, int n, const double* omega, const double* gamma) {
+  Shifts z;
+  z.dst = (cplx*)c->arena.get(sizeof(cplx) * n);
+  std::vector<cplx> h(n);
+  for (int k = 0; k < n; ++k) h[k] = cx(omega[k], gamma[k]);
+  if (n <= kShiftArgs) {
+    z.n = n;
+    std::copy(h.begin(), h.end(), z.z);
+  } else {
+    HIPCHK(hipMemcpyAsync(z.dst, h.data(), sizeof(cplx) * n, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));  // h goes out of scope
+  }
+  return z;
+}
+
+void unpack_out(cclr_ctx* c, const VecSet& in, cclr_c64* s1, cclr_c64* s2, const char* what,
+                const InputCheck& chk = InputCheck()) {
   check_ptr(s1, what);
   check_ptr(s2, what);
-  launch_unpack(in.n, c->o, c->v, in.s, in.d, (cplx*)s1, (cplx*)s2, c->stream);
+  launch_unpack(in.n, c->o, c->v, in.s, in.d, (cplx*)s1, (cplx*)s2, c->stream, chk);
 }
 
 void require_t(cclr_ctx* c) {
@@ -195,7 +247,13 @@ int cclr_create(int o, int v, const cclr_options* opt, cclr_ctx** out) {
     c->arena.ctx = c;
     try {
       c->fixed_ws = fixed_ws_address(c->device);
+      HIPCHK(hipMalloc((void**)&c->input_bad, sizeof(int) * kInputMarks));
+      HIPCHK(hipHostMalloc((void**)&c->input_host, sizeof(int), hipHostMallocDefault));
+      *c->input_host = 0;
+      HIPCHK(hipMemset(c->input_bad, 0, sizeof(int) * kInputMarks));
     } catch (...) {
+      if (c->input_bad) (void)hipFree(c->input_bad);
+      if (c->input_host) (void)hipHostFree(c->input_host);
       delete c;
       throw;
     }
@@ -214,6 +272,8 @@ int cclr_destroy(cclr_ctx* c) {
   }
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);
+  if (c->input_bad) (void)hipFree(c->input_bad);
+  if (c->input_host) (void)hipHostFree(c->input_host);
   delete c;
   return CCLR_OK;
 }
@@ -227,14 +287,15 @@ int cclr_set_hamiltonian(cclr_ctx* c, const cclr_c64* f, const cclr_c64* oooo, c
     const i64 o = c->o, v = c->v, n = o + v;
     c->have_H = c->have_t = c->have_lam = false;
     c->Vpk.release();
-    copy_in(c, c->f, f, n * n, "f");
-    copy_in(c, c->Voooo, oooo, o * o * o * o, "oooo");
-    copy_in(c, c->Vooov, ooov, o * o * o * v, "ooov");
-    copy_in(c, c->Voovv, oovv, o * o * v * v, "oovv");
-    copy_in(c, c->Vovov, ovov, o * v * o * v, "ovov");
-    copy_in(c, c->Vovvv, ovvv, o * v * v * v, "ovvv");
-    copy_in(c, c->Vvvvv, vvvv, v * v * v * v, "vvvv");
-    HIPCHK(hipStreamSynchronize(c->stream));
+    CheckedCopies in(c);
+    in.copy(c->f, f, n * n, "f");
+    in.copy(c->Voooo, oooo, o * o * o * o, "oooo");
+    in.copy(c->Vooov, ooov, o * o * o * v, "ooov");
+    in.copy(c->Voovv, oovv, o * o * v * v, "oovv");
+    in.copy(c->Vovov, ovov, o * v * o * v, "ovov");
+    in.copy(c->Vovvv, ovvv, o * v * v * v, "ovvv");
+    in.copy(c->Vvvvv, vvvv, v * v * v * v, "vvvv");
+    in.finish();
     c->have_H = true;
     return CCLR_OK;
   });
@@ -247,7 +308,9 @@ int cclr_set_hamiltonian_cholesky(cclr_ctx* c, const cclr_c64* f, int nchol, con
     REQUIRE(nchol >= 1, CCLR_EINVAL, "need nchol >= 1");
     c->have_H = c->have_t = c->have_lam = false;
     c->Vpk.release();
-    copy_in(c, c->f, f, n * n, "f");
+    CheckedCopies in(c);
+    in.copy(c->f, f, n * n, "f");
+    in.finish();
     check_ptr(L, "L");
     {
       Arena::Mark mk = c->arena.mark();
@@ -268,11 +331,13 @@ int cclr_ccsd_residual(cclr_ctx* c, const cclr_c64* t1, const cclr_c64* t2, cclr
     REQUIRE(c->have_H, CCLR_ESTATE, "cclr_set_hamiltonian has not been called");
     Arena::Mark mk = c->arena.mark();
     VecSet t = packed_buf(c, 1), out = packed_buf(c, 1);
-    pack_in(c, 1, t1, t2, t, "t");
+    const InputCheck chk = new_check(c);
+    pack_in(c, 1, t1, t2, t, "t", chk);
     const std::complex<double> E = ccsd_residual(c, t, out);
-    unpack_out(c, out, o1, o2, "output");
+    unpack_out(c, out, o1, o2, "output", chk);
     HIPCHK(hipStreamSynchronize(c->stream));
     c->arena.reset(mk);
+    REQUIRE(*c->input_host != chk.call, CCLR_EINVAL, "non-finite value in t");
     if (energy) *energy = cclr_c64{E.real(), E.imag()};
     return CCLR_OK;
   });
@@ -286,17 +351,18 @@ int cclr_solve_ccsd(cclr_ctx* c, double tol, int maxiter, int nsub, cclr_c64* t1
     const i64 o = c->o, v = c->v;
     Arena::Mark mk = c->arena.mark();
     VecSet t = packed_buf(c, 1);
-    pack_in(c, 1, t1, t2, t, "t");
+    pack_in_checked(c, 1, t1, t2, t, "t");
     std::complex<double> E;
     const int rc = ccsd_crop(c, tol, maxiter, nsub, t, &E, info);
     unpack_out(c, t, t1, t2, "t");
     c->arena.reset(mk);
     // the solution becomes the context's amplitudes
     c->have_t = c->have_lam = false;
-    copy_in(c, c->t1, t1, o * v, "t1");
-    copy_in(c, c->t2, t2, o * o * v * v, "t2");
+    CheckedCopies in(c);
+    in.copy(c->t1, t1, o * v, "t1");
+    in.copy(c->t2, t2, o * o * v * v, "t2");
+    in.finish();
     build_intermediates(c);
-    HIPCHK(hipStreamSynchronize(c->stream));
     c->have_t = true;
     if (energy) *energy = cclr_c64{E.real(), E.imag()};
     return rc;
@@ -309,8 +375,10 @@ int cclr_set_amplitudes(cclr_ctx* c, const cclr_c64* t1, const cclr_c64* t2) {
     REQUIRE(c->have_H, CCLR_ESTATE, "cclr_set_hamiltonian has not been called");
     const i64 o = c->o, v = c->v;
     c->have_t = c->have_lam = false;
-    copy_in(c, c->t1, t1, o * v, "t1");
-    copy_in(c, c->t2, t2, o * o * v * v, "t2");
+    CheckedCopies in(c);
+    in.copy(c->t1, t1, o * v, "t1");
+    in.copy(c->t2, t2, o * o * v * v, "t2");
+    in.finish();
     build_intermediates(c);
     c->have_t = true;
     return CCLR_OK;
@@ -325,16 +393,16 @@ static int jacobian(cclr_ctx* c, int side, int nvec, const double* omega, const 
     if (nvec == 0) return CCLR_OK;
     Arena::Mark mk = c->arena.mark();
     VecSet in = packed_buf(c, nvec), out = packed_buf(c, nvec);
-    pack_in(c, nvec, r1, r2, in, side == CCLR_RIGHT ? "r" : "l");
-    std::vector<cplx> z(nvec);
-    for (int k = 0; k < nvec; ++k) z[k] = cx(omega[k], gamma[k]);
-    cplx* zd = (cplx*)c->arena.get(sizeof(cplx) * nvec);
-    HIPCHK(hipMemcpyAsync(zd, z.data(), sizeof(cplx) * nvec, hipMemcpyHostToDevice, c->stream));
-    if (side == CCLR_RIGHT) sigma_right(c, in, out, zd);
-    else sigma_left(c, in, out, zd);
-    unpack_out(c, out, s1, s2, "output");
+    const char* what = side == CCLR_RIGHT ? "r" : "l";
+    const InputCheck chk = new_check(c);
+    const Shifts z = shifts_of(c, nvec, omega, gamma);
+    pack_in(c, nvec, r1, r2, in, what, chk, z);
+    if (side == CCLR_RIGHT) sigma_right(c, in, out, z.dst);
+    else sigma_left(c, in, out, z.dst);
+    unpack_out(c, out, s1, s2, "output", chk);
     HIPCHK(hipStreamSynchronize(c->stream));
     c->arena.reset(mk);
+    REQUIRE(*c->input_host != chk.call, CCLR_EINVAL, std::string("non-finite value in ") + what);
     return CCLR_OK;
   });
 }
@@ -468,6 +536,9 @@ int cclr_jacobian_right_multi(int nctx, cclr_ctx* const* ctx, const int* nvec, c
       REQUIRE(ctx[i]->sigma_prec == CCLR_FP64, CCLR_EINVAL, "grouped transforms are FP64");
       check_freqs(nvec[i], omega[i], gamma[i]);
     }
+    // one check for all: no result is written if any context's input is not finite
+    const InputCheck chk = new_check(c0);
+    bool any = false;
     std::vector<VecSet> in(nctx), out(nctx);
     std::vector<cplx*> zd(nctx, nullptr);
     std::vector<SigmaWork> w(nctx);
@@ -479,11 +550,10 @@ int cclr_jacobian_right_multi(int nctx, cclr_ctx* const* ctx, const int* nvec, c
       marked[i] = true;
       in[i] = packed_buf(c, nvec[i]);
       out[i] = packed_buf(c, nvec[i]);
-      pack_in(c, nvec[i], r1[i], r2[i], in[i], "r");
-      std::vector<cplx> z(nvec[i]);
-      for (int k = 0; k < nvec[i]; ++k) z[k] = cx(omega[i][k], gamma[i][k]);
-      zd[i] = (cplx*)c->arena.get(sizeof(cplx) * nvec[i]);
-      HIPCHK(hipMemcpyAsync(zd[i], z.data(), sizeof(cplx) * nvec[i], hipMemcpyHostToDevice, c->stream));
+      const Shifts z = shifts_of(c, nvec[i], omega[i], gamma[i]);
+      pack_in(c, nvec[i], r1[i], r2[i], in[i], "r", chk, z);
+      zd[i] = z.dst;
+      any = true;
       w[i] = sigma_right_begin(c, in[i], out[i]);
       rings.push_back(w[i].ring);
       ladders.push_back(w[i].ladder);
@@ -493,9 +563,10 @@ int cclr_jacobian_right_multi(int nctx, cclr_ctx* const* ctx, const int* nvec, c
     for (int i = 0; i < nctx; ++i) {
       if (nvec[i] == 0) continue;
       sigma_finish(ctx[i], w[i], in[i], out[i], zd[i]);
-      unpack_out(ctx[i], out[i], s1[i], s2[i], "output");
+      unpack_out(ctx[i], out[i], s1[i], s2[i], "output", chk);
     }
     HIPCHK(hipStreamSynchronize(c0->stream));
+    REQUIRE(!any || *c0->input_host != chk.call, CCLR_EINVAL, "non-finite value in r");
     return CCLR_OK;
   });
   for (int i = 0; i < nctx; ++i)
@@ -519,7 +590,7 @@ int cclr_solve_damped(cclr_ctx* c, int side, int nrhs, const double* omega, cons
     if (nrhs == 0) return CCLR_OK;
     Arena::Mark mk = c->arena.mark();
     VecSet rhs = packed_buf(c, nrhs), x = packed_buf(c, nrhs);
-    pack_in(c, nrhs, b1, b2, rhs, "b");
+    pack_in_checked(c, nrhs, b1, b2, rhs, "b");
     std::vector<cplx> z(nrhs);
     for (int k = 0; k < nrhs; ++k) z[k] = cx(omega[k], gamma[k]);
     const int rc = solve_system(c, side, nrhs, z.data(), rhs, x, info);

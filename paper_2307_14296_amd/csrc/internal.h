@@ -261,11 +261,31 @@ struct VecSet {
   int n = 0;
 };
 
-void launch_unpack(int nvec, int o, int v, const cplx* s, const cplx* d, cplx* r1, cplx* r2, hipStream_t st);
+// Finiteness of a call's inputs without a host round trip per array: the
+// kernels that read them raise *bad to the call's number, the one that writes
+// the results leaves them alone then and stores the outcome to *host (pinned
+// memory, read once the stream is drained).  The number grows with every call,
+// so a mark of an earlier call means nothing.  bad = null: no check.
+struct InputCheck {
+  int* bad = nullptr;
+  int call = 0;
+  int* host = nullptr;
+};
+// up to kShiftArgs frequencies of a call, passed with a launch to device memory
+constexpr int kShiftArgs = 16;
+struct Shifts {
+  cplx* dst = nullptr;
+  int n = 0;
+  cplx z[kShiftArgs] = {};
+};
+void launch_unpack(int nvec, int o, int v, const cplx* s, const cplx* d, cplx* r1, cplx* r2, hipStream_t st,
+                   const InputCheck& chk = InputCheck());
 // packed doubles -> the views a transform reads: ring[k][i][a][m][e] = r^ae_im,
 // hp[k][P][a][b] = r^ab_ij (pairs P = i > j), vp[k][i][j][Q] = r^ab_ij (pairs Q = a > b)
 void launch_unpack_views(int nvec, int o, int v, const cplx* d, cplx* ring, cplx* hp, cplx* vp, hipStream_t st);
-void launch_pack_full(int nvec, int o, int v, const cplx* r1, const cplx* r2, cplx* s, cplx* d, hipStream_t st);
+void launch_pack_full(int nvec, int o, int v, const cplx* r1, const cplx* r2, cplx* s, cplx* d, hipStream_t st,
+                      const InputCheck& chk = InputCheck(), const Shifts& z = Shifts());
+void launch_copy_check(const cplx* src, cplx* dst, i64 n, const InputCheck& chk, hipStream_t st);
 // pair packing of the last two indices: dst[r][AB] = src[r][a][b] (a > b)
 // X[P][Q] += alpha (d(p1,q1) F[p2][q2] - d(p1,q2) F[p2][q1] - d(p2,q1) F[p1][q2] + d(p2,q2) F[p1][q1])
 // for pairs P = (p1 > p2), Q = (q1 > q2) of n indices; X is [n(n-1)/2][n(n-1)/2], F is n x n
@@ -355,6 +375,11 @@ struct cclr_ctx {
   // no new timing runs (they create events and take scratch outputs); cached
   // choices are still used
   bool no_timing = false;
+  // input checks (see InputCheck): kInputMarks marks on the device, the outcome
+  // in pinned host memory, and the number of the current call
+  int* input_bad = nullptr;
+  int* input_host = nullptr;
+  int input_call = 0;
   // this device's copy of the library's fixed work space (see capi.hip)
   void* fixed_ws = nullptr;
   size_t fixed_ws_peak = 0;  // bytes of it the last such call took at most

@@ -123,11 +123,24 @@ __device__ __forceinline__ void occ_pair(i64 P, int& hi, int& lo) {
 
 __device__ __forceinline__ cplx cneg(cplx x) { return make_double2(-x.x, -x.y); }
 
-// out[k][i][j][a][b], the full antisymmetric r2
-__global__ __launch_bounds__(256) void k_unpack_t(int o, int v, const cplx* __restrict__ d, cplx* __restrict__ out) {
+// out[k][i][j][a][b], the full antisymmetric r2, and in one more row of
+// workgroups the singles (if r1 is given).  Writes nothing if the call's inputs
+// were found non-finite, and tells the host so either way.
+__global__ __launch_bounds__(256) void k_unpack_t(int o, int v, const cplx* __restrict__ d, cplx* __restrict__ out,
+                                                  const cplx* __restrict__ s1, cplx* __restrict__ r1, InputCheck chk) {
   __shared__ cplx s[PT][PT + 1];
   const i64 O2 = (i64)o * (o - 1) / 2, V2 = (i64)v * (v - 1) / 2;
   const int k = blockIdx.z, y = blockIdx.y, tid = threadIdx.x;
+  if (chk.bad) {
+    const bool bad = *chk.bad == chk.call;
+    if (chk.host && tid == 0 && blockIdx.x == 0 && y == 0 && k == 0) *chk.host = bad ? chk.call : 0;
+    if (bad) return;
+  }
+  if (y >= O2 + o) {
+    const i64 ov = (i64)o * v;
+    for (i64 e = (i64)blockIdx.x * 256 + tid; e < ov; e += (i64)gridDim.x * 256) r1[k * ov + e] = s1[k * ov + e];
+    return;
+  }
   int ta, tb;
   tile_pair(blockIdx.x, ta, tb);
   const int a0 = ta * PT, b0 = tb * PT;
@@ -232,10 +245,15 @@ __global__ __launch_bounds__(256) void k_unpack_views(int o, int v, const cplx* 
   }
 }
 
-// full -> packed (takes the i>j, a>b entries)
+__device__ __forceinline__ bool finite_c(cplx x) { return isfinite(x.x) && isfinite(x.y); }
+
+// full -> packed (takes the i>j, a>b entries); marks the call if one of them
+// is not finite, and puts the call's shifts in place
 __global__ __launch_bounds__(256) void k_pack_full(int nvec, int o, int v, const cplx* __restrict__ r1,
                                                    const cplx* __restrict__ r2, cplx* __restrict__ s,
-                                                   cplx* __restrict__ d) {
+                                                   cplx* __restrict__ d, InputCheck chk, Shifts z) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < z.n) z.dst[threadIdx.x] = z.z[threadIdx.x];
+  bool fine = true;
   const i64 ov = (i64)o * v, O2 = (i64)o * (o - 1) / 2, V2 = (i64)v * (v - 1) / 2;
   const i64 nd = O2 * V2;
   const i64 total = (i64)nvec * (ov + nd);
@@ -243,7 +261,9 @@ __global__ __launch_bounds__(256) void k_pack_full(int nvec, int o, int v, const
   for (i64 e = (i64)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
     const i64 k = e / (ov + nd), q = e % (ov + nd);
     if (q < ov) {
-      s[k * ov + q] = r1[k * ov + q];
+      const cplx x = r1[k * ov + q];
+      s[k * ov + q] = x;
+      fine = fine && finite_c(x);
     } else {
       const i64 p = q - ov, IJ = p / V2, AB = p % V2;
       // invert the pair index
@@ -255,9 +275,24 @@ __global__ __launch_bounds__(256) void k_pack_full(int nvec, int o, int v, const
       while ((i64)a * (a - 1) / 2 > AB) --a;
       while ((i64)(a + 1) * a / 2 <= AB) ++a;
       const int b = (int)(AB - (i64)a * (a - 1) / 2);
-      d[k * nd + p] = r2[(((k * o + i) * o + j) * v + a) * v + b];
+      const cplx x = r2[(((k * o + i) * o + j) * v + a) * v + b];
+      d[k * nd + p] = x;
+      fine = fine && finite_c(x);
     }
   }
+  if (chk.bad && !fine) atomicMax(chk.bad, chk.call);
+}
+
+// dst = src; marks the call if an element is not finite
+__global__ __launch_bounds__(256) void k_copy_check(const cplx* __restrict__ src, cplx* __restrict__ dst, i64 n,
+                                                    InputCheck chk) {
+  bool fine = true;
+  for (i64 e = (i64)blockIdx.x * 256 + threadIdx.x; e < n; e += (i64)gridDim.x * 256) {
+    const cplx x = src[e];
+    dst[e] = x;
+    fine = fine && finite_c(x);
+  }
+  if (!fine) atomicMax(chk.bad, chk.call);
 }
 
 // packed sigma assembly with the antisymmetrizers applied on the fly:
@@ -433,16 +468,23 @@ static dim3 perm_grid(int nvec, int o, int v, int more) {
   return dim3((unsigned)(nt * (nt + 1) / 2), (unsigned)rows, (unsigned)nvec);
 }
 
-void launch_unpack(int nvec, int o, int v, const cplx* s, const cplx* d, cplx* r1, cplx* r2, hipStream_t st) {
+void launch_unpack(int nvec, int o, int v, const cplx* s, const cplx* d, cplx* r1, cplx* r2, hipStream_t st,
+                   const InputCheck& chk) {
   if (nvec <= 0) return;
-  if (r1) HIPCHK(hipMemcpyAsync(r1, s, sizeof(cplx) * (size_t)nvec * o * v, hipMemcpyDeviceToDevice, st));
-  hipLaunchKernelGGL(k_unpack_t, perm_grid(nvec, o, v, o), dim3(256), 0, st, o, v, d, r2);
+  hipLaunchKernelGGL(k_unpack_t, perm_grid(nvec, o, v, o + (r1 ? 1 : 0)), dim3(256), 0, st, o, v, d, r2, s, r1, chk);
   HIPCHK(hipGetLastError());
 }
 
-void launch_pack_full(int nvec, int o, int v, const cplx* r1, const cplx* r2, cplx* s, cplx* d, hipStream_t st) {
+void launch_pack_full(int nvec, int o, int v, const cplx* r1, const cplx* r2, cplx* s, cplx* d, hipStream_t st,
+                      const InputCheck& chk, const Shifts& z) {
   const i64 total = (i64)nvec * ((i64)o * v + (i64)o * (o - 1) / 2 * ((i64)v * (v - 1) / 2));
-  hipLaunchKernelGGL(k_pack_full, dim3(grid_for(total)), dim3(256), 0, st, nvec, o, v, r1, r2, s, d);
+  hipLaunchKernelGGL(k_pack_full, dim3(grid_for(total)), dim3(256), 0, st, nvec, o, v, r1, r2, s, d, chk, z);
+  HIPCHK(hipGetLastError());
+}
+
+void launch_copy_check(const cplx* src, cplx* dst, i64 n, const InputCheck& chk, hipStream_t st) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL(k_copy_check, dim3(grid_for(n)), dim3(256), 0, st, src, dst, n, chk);
   HIPCHK(hipGetLastError());
 }
 
