@@ -460,65 +460,6 @@ int cclr_jacobian_right_noalloc(cclr_ctx* c, int nvec, const double* omega, cons
   });
 }
 
-namespace {
-// One persistent launch for products of several contexts that share operand
-// layouts; the kernel variant is timed once per set of shapes and kept.
-void grouped_products(cclr_ctx* c0, std::vector<GemmArgs> g) {
-  g.erase(std::remove_if(g.begin(), g.end(), [](const GemmArgs& x) { return x.M <= 0 || x.N <= 0 || x.K <= 0; }),
-          g.end());
-  if (g.empty()) return;
-  const bool ak = g[0].sAk == 1, bn = g[0].sBn == 1;
-  for (const GemmArgs& x : g)
-    REQUIRE((x.sAk == 1) == ak && (x.sBn == 1) == bn && x.kchunk == 0, CCLR_EINVAL, "grouped products: layouts differ");
-  // longest reductions first: the tiles are dealt round-robin to the workgroups
-  std::stable_sort(g.begin(), g.end(), [](const GemmArgs& a, const GemmArgs& b) { return a.K > b.K; });
-  std::string key = ak ? "A1" : "A0";
-  key += bn ? "B1" : "B0";
-  for (const GemmArgs& x : g) key += ":" + std::to_string(x.M) + "x" + std::to_string(x.N) + "x" + std::to_string(x.K);
-  Arena::Mark mk = c0->arena.mark();
-  GemmArgs* pd = (GemmArgs*)c0->arena.get(sizeof(GemmArgs) * g.size());
-  int* td = (int*)c0->arena.get(sizeof(int) * (g.size() + 1));
-  HIPCHK(hipMemcpyAsync(pd, g.data(), sizeof(GemmArgs) * g.size(), hipMemcpyHostToDevice, c0->stream));
-  auto launch = [&](int variant) {
-    std::vector<int> ts(g.size() + 1, 0);
-    const int bm = gemm_tile_rows(variant), bn_ = gemm_tile_cols(variant);
-    for (size_t p = 0; p < g.size(); ++p) {
-      const i64 tiles = (i64)((g[p].M + bm - 1) / bm) * ((g[p].N + bn_ - 1) / bn_) * g[p].batch;
-      REQUIRE(ts[p] + tiles < (1ll << 31), CCLR_EINVAL, "grouped products: too many tiles");
-      ts[p + 1] = ts[p] + (int)tiles;
-    }
-    HIPCHK(hipMemcpyAsync(td, ts.data(), sizeof(int) * ts.size(), hipMemcpyHostToDevice, c0->stream));
-    launch_zgemm_group(pd, td, (int)g.size(), ts.back(), variant, ak, bn, c0->stream);
-  };
-  auto it = c0->group_choice.find(key);
-  if (it == c0->group_choice.end()) {
-    int best = GEMM_128x64_G4;
-    double best_ms = -1;
-    std::vector<std::pair<int, double>> ms_all;
-    for (int var : {GEMM_128x64_G3, GEMM_64x64_G3, GEMM_128x64_G4, GEMM_64x64_G4, GEMM_128x128_G4, GEMM_128x128_DMA}) {
-      hipEvent_t e0, e1;
-      HIPCHK(hipEventCreate(&e0));
-      HIPCHK(hipEventCreate(&e1));
-      HIPCHK(hipEventRecord(e0, c0->stream));
-      launch(var);
-      HIPCHK(hipEventRecord(e1, c0->stream));
-      HIPCHK(hipEventSynchronize(e1));
-      float ms = 0;
-      HIPCHK(hipEventElapsedTime(&ms, e0, e1));
-      (void)hipEventDestroy(e0);
-      (void)hipEventDestroy(e1);
-      ms_all.push_back({var, ms});
-      if (best_ms < 0 || ms < best_ms) best_ms = ms, best = var;
-    }
-    c0->group_choice[key] = best;
-    c0->gemm_tuning_log.push_back({"group " + key, ms_all, best});
-    it = c0->group_choice.find(key);
-  }
-  launch(it->second);
-  c0->arena.reset(mk);
-}
-}  // namespace
-
 int cclr_jacobian_right_multi(int nctx, cclr_ctx* const* ctx, const int* nvec, const double* const* omega,
                               const double* const* gamma, const cclr_c64* const* r1, const cclr_c64* const* r2,
                               cclr_c64* const* s1, cclr_c64* const* s2) {
@@ -542,7 +483,6 @@ int cclr_jacobian_right_multi(int nctx, cclr_ctx* const* ctx, const int* nvec, c
     std::vector<VecSet> in(nctx), out(nctx);
     std::vector<cplx*> zd(nctx, nullptr);
     std::vector<SigmaWork> w(nctx);
-    std::vector<GemmArgs> rings, ladders;
     for (int i = 0; i < nctx; ++i) {
       cclr_ctx* c = ctx[i];
       if (nvec[i] == 0) continue;
@@ -555,11 +495,16 @@ int cclr_jacobian_right_multi(int nctx, cclr_ctx* const* ctx, const int* nvec, c
       zd[i] = z.dst;
       any = true;
       w[i] = sigma_right_begin(c, in[i], out[i]);
-      rings.push_back(w[i].ring);
-      ladders.push_back(w[i].ladder);
     }
-    grouped_products(c0, rings);
-    grouped_products(c0, ladders);
+    // every context's ring and ladder in its own launch, split evenly over the
+    // compute units: a persistent launch over all of them in 128x128 tiles took
+    // 7.1 ms for (8,60), (12,91) and (16,120), three vectors each, where the six
+    // launches take 5.7
+    for (int i = 0; i < nctx; ++i)
+      if (nvec[i] > 0) {
+        run_gemm(ctx[i], w[i].ring);
+        run_gemm(ctx[i], w[i].ladder);
+      }
     for (int i = 0; i < nctx; ++i) {
       if (nvec[i] == 0) continue;
       sigma_finish(ctx[i], w[i], in[i], out[i], zd[i]);

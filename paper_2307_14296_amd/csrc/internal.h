@@ -383,8 +383,6 @@ struct cclr_ctx {
   // this device's copy of the library's fixed work space (see capi.hip)
   void* fixed_ws = nullptr;
   size_t fixed_ws_peak = 0;  // bytes of it the last such call took at most
-  // kernel variant of grouped multi-context launches, per set of product shapes
-  std::map<std::string, int> group_choice;
   // the ring and ladder products of an FP64 right transform run on a second
   // stream of default priority (`side`, created on first use) while the other
   // products run on `stream`; joined before the result is packed
@@ -446,8 +444,8 @@ void with_plain_wp(cclr_ctx* c, F&& f) {
 }
 // sigma for nvec packed vectors in `in` -> `out` (packed); z per vector (may be null)
 void sigma_right(cclr_ctx* c, const VecSet& in, const VecSet& out, const cplx* z_dev);
-// The right sigma in two halves around its two large products, so that the
-// products of several contexts can be launched together: begin runs every
+// The right sigma in two halves around its two large products, which the
+// caller launches in between (also those of several contexts): begin runs every
 // other term and returns the ring and ladder products (not yet launched);
 // finish adds the hole ladder and packs the result once both have run.
 struct SigmaAcc {
