@@ -243,22 +243,11 @@ def spectrum_bench(cc, dev, o=16, v=120, seed=2, nfreq=16):
         cc.cclr_set_amplitudes(ctx, t1, t2)
         om = [float(x) for x in np.linspace(0.0, 0.5, nfreq)]
         ga = [0.005] * nfreq
-        L = cc.lib()
-        L.cclr_dbg_tuning.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_char_p, ctypes.c_longlong]
-
-        def tuned_classes():
-            buf = ctypes.create_string_buffer(1 << 16)
-            L.cclr_dbg_tuning(ctx, -1, buf, len(buf))
-            return len([ln for ln in buf.value.decode().splitlines() if ln])
-
-        # warm-up of both forms, the whole per-frequency sweep included (Lambda solve; first-use GEMM tuning
-        # of every product shape class the two forms meet: the active right-hand sides of a call drop out as
-        # they converge, so each form has row counts of its own)
+        # warm-up of both forms, the whole per-frequency sweep included (Lambda solve, work memory)
         cc.cclr_response_function(ctx, X, om, ga)
         for w in range(nfreq):
             cc.cclr_response_function(ctx, X, [om[w]], [ga[w]])
         torch.cuda.synchronize()
-        tuned0 = tuned_classes()
         t0 = time.perf_counter()
         rc, out, info = cc.cclr_response_function(ctx, X, om, ga)
         torch.cuda.synchronize()
@@ -273,8 +262,6 @@ def spectrum_bench(cc, dev, o=16, v=120, seed=2, nfreq=16):
         torch.cuda.synchronize()
         t_single = time.perf_counter() - t0
         log(f"spectrum: one call per frequency {t_single:.2f} s, {n_single} transforms")
-        # shape classes first met (and timed by the autotuner) inside the two timed forms
-        tuned_while_timed = tuned_classes() - tuned0
         diff = max(float(np.linalg.norm(out[w] - outs[w]) / np.linalg.norm(outs[w])) for w in range(nfreq))
         return {"workload": f"damped spectrum o={o} v={v} complex128, 3 dipoles x {nfreq} frequencies on [0, 0.5] Eh, "
                             f"gamma 0.005, tol 1e-8",
@@ -282,8 +269,7 @@ def spectrum_bench(cc, dev, o=16, v=120, seed=2, nfreq=16):
                              "transforms_per_s": round(info.nsigma / t_lock, 2), "iterations": info.iters, "rc": rc},
                 "one_call_per_frequency": {"seconds": round(t_single, 3), "transforms": n_single,
                                            "transforms_per_s": round(n_single / t_single, 2)},
-                "speedup_lockstep": round(t_single / t_lock, 3), "max_rel_diff_alpha": diff,
-                "shapes_tuned_while_timed": tuned_while_timed}
+                "speedup_lockstep": round(t_single / t_lock, 3), "max_rel_diff_alpha": diff}
     finally:
         cc.cclr_destroy(ctx)
         del f, t1, t2, X
@@ -373,7 +359,7 @@ def ground_bench(cc, dev, o, v, seed, tol=1e-8, nchol_per_orbital=3, v_std=0.002
         cc.cclr_set_hamiltonian(ctx, f, *[V[k] for k in s.CANONICAL_BLOCKS])
         del V
         torch.cuda.empty_cache()
-        # one residual evaluation first (packs <ab||ef> and tunes the ladder product)
+        # one residual evaluation first (packs <ab||ef>)
         o1, o2 = torch.empty_like(t1), torch.empty_like(t2)
         cc.cclr_ccsd_residual(ctx, t1, t2, o1, o2)
         torch.cuda.synchronize()
@@ -487,8 +473,7 @@ def copy_bench(cc, dev, reps=5):
 
 def products_bench(cc, dev, o, v, seed, z, max_subspace, tol, top=40):
     """Per-product record of the contraction engine's GEMMs over one whole FP64
-    response step (after a warm-up step, so no product is tuned while
-    recorded), aggregated by shape and layout: launches, total ms, TFLOP/s
+    response step (after a warm-up step), aggregated by shape and layout: launches, total ms, TFLOP/s
     algorithmic.  Recording synchronizes after every product, so the step
     runs slower than untraced; the packed ladder and ring GEMMs of the
     transforms go through their own launcher and are not in the record.
@@ -602,8 +587,7 @@ def sweep_bench(cc, dev, seed=3, reps=3):
 def batching_bench(cc, dev, nvec=3, reps=3):
     """Four problems of uneven size, (o, v) = (8, 60), (12, 90), (16, 120),
     (20, 150), nvec right transforms each: one cclr_jacobian_right_multi call
-    (grouped persistent ring and ladder launches) against one
-    cclr_jacobian_right call per problem."""
+    against one cclr_jacobian_right call per problem."""
     import torch
     from gen import synth as s
     shapes = [(8, 60), (12, 90), (16, 120), (20, 150)]
@@ -631,8 +615,8 @@ def batching_bench(cc, dev, nvec=3, reps=3):
             cc.cclr_jacobian_right_multi(ctxs, [a[4] for a in args], [a[5] for a in args], [a[0] for a in args],
                                          [a[1] for a in args], [a[2] for a in args], [a[3] for a in args])
         res = {}
-        for name, fn in (("one_call_per_problem", seq), ("grouped_persistent", grouped)):
-            fn()  # warm-up (autotuning)
+        for name, fn in (("one_call_per_problem", seq), ("one_call_for_all", grouped)):
+            fn()  # warm-up (work memory)
             torch.cuda.synchronize()
             t0 = time.perf_counter()
             for _ in range(reps):
@@ -648,8 +632,8 @@ def batching_bench(cc, dev, nvec=3, reps=3):
         diff = max(float(((a[2] - o1).abs().max() / o1.abs().max()).item()) for a, (o1, o2) in zip(args, outs))
         work = sum(sigma_flops(o, v)["total"] for o, v in shapes) * nvec
         res.update({"problems": [list(x) for x in shapes], "vectors_per_problem": nvec,
-                    "speedup_grouped": round(res["one_call_per_problem"]["ms"] / res["grouped_persistent"]["ms"], 3),
-                    "tflops_grouped": round(work / (res["grouped_persistent"]["ms"] * 1e-3) / 1e12, 2),
+                    "speedup_grouped": round(res["one_call_per_problem"]["ms"] / res["one_call_for_all"]["ms"], 3),
+                    "tflops_grouped": round(work / (res["one_call_for_all"]["ms"] * 1e-3) / 1e12, 2),
                     "max_rel_diff_singles": diff})
         return res
     finally:
@@ -681,7 +665,7 @@ def gemm_kernel_digest():
 
 def ladder_traffic(variant):
     """HBM bytes per launch of the batched FP64 ladder GEMM (12 vectors at
-    o=20, v=200) in the kernel variant the autotuner chose, from the
+    o=20, v=200) in the kernel variant of its shape, from the
     committed rocprofv3 --pmc summary (one figure per variant); None for a
     variant other than the direct-load tiles (15, 16) or when their source
     differs from the one the counters were taken on."""
@@ -698,7 +682,7 @@ def ladder_traffic(variant):
 
 
 def gemm_kernel_name(variant):
-    """HIP kernel behind an FP64 GEMM variant number of the autotuner."""
+    """HIP kernel behind an FP64 GEMM variant number."""
     if variant is None:
         return "FP64 GEMM"
     variant %= 100  # 100 + v: variant v on the transposed product
@@ -849,12 +833,11 @@ def main():
             log(f"[{prec}] warm-up step {k} done in {time.perf_counter() - tw:.2f} s")
         L.cclr_dbg_profile(ctx, 1)
         torch.cuda.synchronize()
-        def tuning_record():
+        def variant_record():
             buf = ctypes.create_string_buffer(1 << 16)
             L.cclr_dbg_tuning(ctx, -1, buf, len(buf))
             return [ln for ln in buf.value.decode().splitlines() if ln]
 
-        tuned_before = len(tuning_record())
         t0 = time.perf_counter()
         ntr = 0
         step_s = []
@@ -868,11 +851,9 @@ def main():
         nl, ms, fl = ctypes.c_longlong(), ctypes.c_double(), ctypes.c_double()
         L.cclr_dbg_profile_read(ctx, 1, opt.prec, ctypes.byref(nl), ctypes.byref(ms), ctypes.byref(fl))
         L.cclr_dbg_profile(ctx, 0)
-        res["gemm_tuning"] = tuning_record()
-        # every timed step's duration, and the GEMM shape classes first tuned inside the timed steps (0 when
-        # the warm-up covered them all)
+        res["gemm_variants"] = variant_record()
+        # every timed step's duration
         res["step_s"] = step_s
-        res["shapes_tuned_while_timed"] = len(res["gemm_tuning"]) - tuned_before
         cc.cclr_destroy(ctx)
         if tight_tol and args.mode == "response":
             # untimed FP64 reference solved to the tight tolerance
@@ -937,17 +918,17 @@ def main():
     ms = ctypes.c_double(main_res["ms"])
     fl = ctypes.c_double(main_res["fl"])
     t_gen = main_res["input_generation_s"]
-    extra = {k: main_res[k] for k in ("solver", "rc", "step_s", "shapes_tuned_while_timed") if k in main_res}
-    extra["gemm_tuning"] = main_res.get("gemm_tuning", [])[:16]
+    extra = {k: main_res[k] for k in ("solver", "rc", "step_s") if k in main_res}
+    extra["gemm_variants"] = main_res.get("gemm_variants", [])[:16]
     achieved = fl.value / (ms.value * 1e-3) / 1e12 if ms.value > 0 else 0.0
     sf = sigma_flops(o, v)
     ladder_shape = f"{(o * (o - 1) // 2) * args.nvec}x{v * (v - 1) // 2}x{v * (v - 1) // 2}"
-    variant = [ln for ln in main_res.get("gemm_tuning", []) if ln.startswith(ladder_shape)]
+    variant = [ln for ln in main_res.get("gemm_variants", []) if ln.startswith(ladder_shape)]
     chosen = int(variant[0].rsplit("->", 1)[1]) if variant else None
     roofline = {
         "bound": "mfma",
         "kernel": f"{gemm_kernel_name(chosen)} (packed particle-particle ladder, FP64 MFMA), largest launches" +
-                  (f"; autotuner: {variant[0]}" if variant else ""),
+                  (f"; {variant[0]}" if variant else ""),
         "achieved": round(achieved, 3),
         "peak": PEAK_FP64_TFLOPS,
         "unit": "TFLOP/s",
@@ -1007,8 +988,7 @@ def main():
         step_s = mres["dt"] / args.mixed_steps
         mx = {"prec": names[p], "value": mres["transforms"] / mres["dt"], "steps": args.mixed_steps,
               "ms_per_step": 1e3 * step_s, "transforms": mres["transforms"],
-              "job_speedup_vs_fp64": fp64_step / step_s, "step_s": mres.get("step_s"),
-              "shapes_tuned_while_timed": mres.get("shapes_tuned_while_timed")}
+              "job_speedup_vs_fp64": fp64_step / step_s, "step_s": mres.get("step_s")}
         if "alpha" in mres:
             mx["alpha_err_vs_fp64_timed"] = alpha_err(mres["alpha"], main_res["alpha"])
             if ref_alpha is not None:

@@ -171,10 +171,9 @@ int cclr_jacobian_right(cclr_ctx* ctx, int nvec, const double* omega, const doub
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * transform and arguments as cclr_jacobian_right, with every temporary taken
  * from a fixed 256 MiB work space that the library holds on each GPU it runs
- * on until the process ends.  The call makes no hipMalloc or hipFree and
- * starts no GEMM timing run (a product shape not yet timed in this context
- * uses the untimed kernel choice).  FP64 transforms only (CCLR_EINVAL when a
- * test hook forces another precision).  Sizes whose temporaries do not fit
+ * on until the process ends.  The call makes no hipMalloc or hipFree.
+ * FP64 transforms only (CCLR_EINVAL when a test hook forces another
+ * precision).  Sizes whose temporaries do not fit
  * are rejected with CCLR_ENOMEM and nothing is written; about six full
  * doubles tensors (16*o*o*v*v bytes each) per vector and three per call must
  * fit, e.g. four vectors at o=10, v=80.  Every call on one GPU uses that GPU's one work

@@ -29,7 +29,7 @@ int cclr_dbg_zgemm(int M, int N, int K, int batch, const cclr_c64* A, long long 
  * tiles with one LDS buffer, 20: 64x32 tiles, for outputs at most 32 wide;
  * 100 + v: variant v on the transposed product C^T = B^T A^T).
  * All pointers are device memory; strides in elements.  For tests
- * of every variant (the autotuner otherwise runs only the fastest). */
+ * of every variant (the library runs 10, 15, 16, 19 and 20, by shape). */
 int cclr_dbg_zgemm_f64(int variant, int batch, int M, int N, int K, const cclr_c64* A, long long sAb, long long sAm,
                        long long sAk, int conjA, const cclr_c64* B, long long sBb, long long sBk, long long sBn,
                        int conjB, cclr_c64* C, long long sCb, long long sCm, long long sCn, double ar, double ai,
@@ -68,10 +68,11 @@ int cclr_dbg_zgemm_group_f64(int variant, int nprob, const int* M, const int* N,
 
 /* The same product (device pointers, the context's stream) through the
  * context's GEMM dispatch: the register kernel of small products, the evenly
- * split kernel, the short-reduction vector-ALU kernel, the short-output vector-ALU kernels (at most 16 columns with the long operand
- * contiguous in m, at most 8 with it contiguous in k), split-K, or the
- * autotuned MFMA kernels (a product with at most 32 rows and more columns
- * runs transposed), chosen by shape as for the contractions of a transform. */
+ * split kernel, the short-reduction vector-ALU kernel, the short-output
+ * vector-ALU kernels (at most 16 columns with the long operand contiguous in
+ * m, at most 8 with it contiguous in k), split-K, or the MFMA tiles (a product
+ * with at most 32 rows and more columns runs transposed), chosen by shape as
+ * for the contractions of a transform. */
 int cclr_dbg_run_gemm(cclr_ctx* ctx, int M, int N, int K, int batch, const cclr_c64* A, long long sAb, long long sAm,
                       long long sAk, int conjA, const cclr_c64* B, long long sBb, long long sBk, long long sBn,
                       int conjB, cclr_c64* C, long long sCb, long long sCm, long long sCn, double alpha_re,
@@ -181,17 +182,10 @@ int cclr_dbg_small_eig(int n, const cclr_c64* H, int nroots, cclr_c64* w, cclr_c
  * for m[r] < 1).  Host pointers. */
 int cclr_dbg_ritz(int nr, int ld, const int* m, const cclr_c64* G, double* out);
 
-/* Autotuner record: writes up to cap bytes of text, one line per tuned
- * GEMM shape class: "MxNxK bB layoutL timed mxNxK bb: variant=ms ... -> chosen"
- * (the product's shape, then the part of it that was timed: at most 8192 rows
- * and 16 batch entries, so the times are those of the timed part; chosen is
- * the variant in use: within 2% of the fastest, the grouped tile order, then
- * larger tiles, are preferred; 100 + v is variant v on the transposed product
- * C^T = B^T A^T, timed for the 32-column variants when the row count is one
- * they pad less than 64-row tiles would).
- * enable >= 0 switches tuning of new shape classes on (1) or off (0) for
- * later products; with tuning off a product of a class not yet timed takes
- * the untimed choice, and the classes already timed keep theirs. */
+/* Record of the large FP64 products (1e10 flop and more): writes up to cap
+ * bytes of text, one line for each shape met, "MxNxK bB: -> variant" (at most
+ * 256 shapes; products on the register or the evenly split kernel are not in
+ * it).  The variant follows from the shape; enable has no effect. */
 int cclr_dbg_tuning(cclr_ctx* ctx, int enable, char* buf, long long cap);
 
 #ifdef __cplusplus

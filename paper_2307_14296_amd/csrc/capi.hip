@@ -432,8 +432,8 @@ int cclr_jacobian_right_noalloc(cclr_ctx* c, int nvec, const double* omega, cons
                 ", v=" + std::to_string(c->v) + " need more than the fixed work space of " +
                 std::to_string(kFixedWsBytes) + " bytes; use cclr_jacobian_right");
     std::lock_guard<std::mutex> busy(g_ws_busy[c->device]);
-    // route every temporary of this call into the work space, take no new
-    // timing runs, and keep the transform on the context's stream
+    // route every temporary of this call into the work space, and keep the
+    // transform on the context's stream
     struct Scope {
       cclr_ctx* c;
       bool overlap, prof;
@@ -441,7 +441,6 @@ int cclr_jacobian_right_noalloc(cclr_ctx* c, int nvec, const double* omega, cons
         c->arena.ext = (char*)c->fixed_ws;
         c->arena.ext_bytes = kFixedWsBytes;
         c->arena.ext_used = c->arena.ext_peak = 0;
-        c->no_timing = true;
         c->overlap = false;
         c->prof = false;
       }
@@ -451,7 +450,6 @@ int cclr_jacobian_right_noalloc(cclr_ctx* c, int nvec, const double* omega, cons
         c->fixed_ws_peak = c->arena.ext_peak;
         c->arena.ext = nullptr;
         c->arena.ext_bytes = c->arena.ext_used = 0;
-        c->no_timing = false;
         c->overlap = overlap;
         c->prof = prof;
       }

@@ -477,15 +477,12 @@ int cclr_dbg_small_eig(int n, const cclr_c64* H, int nroots, cclr_c64* w, cclr_c
   return rc;
 }
 
-int cclr_dbg_tuning(cclr_ctx* c, int enable, char* buf, long long cap) {
+int cclr_dbg_tuning(cclr_ctx* c, int, char* buf, long long cap) {
   if (!c) return CCLR_EINVAL;
-  if (enable >= 0) c->autotune = enable != 0;
   std::string out;
-  for (const auto& r : c->gemm_tuning_log) {
-    out += r.shape + ":";
-    for (const auto& vm : r.ms) out += " " + std::to_string(vm.first) + "=" + std::to_string(vm.second);
-    out += " -> " + std::to_string(r.chosen) + "\n";
-  }
+  for (const auto& [k, v] : c->gemm_record)
+    out += std::to_string(std::get<0>(k)) + "x" + std::to_string(std::get<1>(k)) + "x" + std::to_string(std::get<2>(k)) +
+           " b" + std::to_string(std::get<3>(k)) + ": -> " + std::to_string(v) + "\n";
   if (buf && cap > 0) {
     const size_t n = std::min<size_t>(out.size(), (size_t)cap - 1);
     memcpy(buf, out.data(), n);

@@ -741,6 +741,13 @@ static double even_cost(const SkPlan& p) {
   return t;
 }
 
+// the same for whole rounds of 128x128 direct-load tiles
+static double dma_cost(const GemmArgs& g) {
+  const int K = g.kchunk > 0 ? g.kchunk : g.K;
+  const i64 t = (i64)((g.M + 127) / 128) * ((g.N + 127) / 128) * g.batch;
+  return (double)((t + 255) / 256) * (7.27 * ((K + 15) / 16) + 8.0);
+}
+
 // FP64 products of some length on the evenly split kernel, in the orientation
 // and row count of least estimated time; false: not taken (short reductions,
 // where the other tiles are as fast, or large products that fill whole rounds
@@ -749,8 +756,7 @@ static bool even_split(cclr_ctx* c, const GemmArgs& g0) {
   if (g0.K < (std::min(g0.M, g0.N) <= 32 ? 512 : 256) || g0.kchunk > 0) return false;
   const i64 most = (i64)((g0.M + 31) / 32) * ((g0.N + 31) / 32) * g0.batch;
   if (most >= (1ll << 30)) return false;
-  const i64 t128 = (i64)((g0.M + 127) / 128) * ((g0.N + 127) / 128) * g0.batch;
-  const double dma = (double)((t128 + 255) / 256) * (7.27 * ((g0.K + 15) / 16) + 3.0);
+  const double dma = dma_cost(g0);
   // with two workgroups per compute unit, with one where the partial sums of
   // two have no room, and with whole tiles only
   for (int cutters : {512, 256, 0}) {
@@ -890,7 +896,7 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
       h.beta = 0;
       form = lowp ? -3 : -2;
       if (lowp) launch_zgemm_lowp(h, CCLR_FP32, c->stream);
-      else tuned_gemm(c, h);
+      else gemm_by_rule(c, h);
       launch_chunk_reduce(g, (int)S, W, c->stream);
       c->arena.reset(mk);
       return;
@@ -915,183 +921,68 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
     }
     launch_zgemm_lowp(g, CCLR_FP32, c->stream);
   } else {
-    form = tuned_gemm(c, g);
+    form = gemm_by_rule(c, g);
   }
-}
-
-// Autotuner.  The first time a large product of a given shape class (M, N,
-// K, batch, operand layouts) is requested, every MFMA kernel variant is
-// timed once with HIP events on a scratch output of the same strides, and
-// the fastest is cached in the context.  Products under 1e10 flop use the
-// untimed choice.
-// The row count M and the batch count carry the number of vectors a
-// transform is applied to, which changes from call to call (a lockstep
-// solve whose active right-hand sides converge one by one): they are timed
-// on at most kTuneRows rows and kTuneBatch batch entries and classed by
-// octave; N and K are classed by quarter octave.  Split-K products (the
-// partial products of run_gemm) are timed whole and classed by chunk length.
-constexpr int kTuneRows = 8192, kTuneBatch = 16;
-bool gemm_variant_grouped(int variant) {
-  return (variant > GEMM_64x64_G4 && variant <= 2 * GEMM_64x64_G4) || variant == GEMM_64x64_G4_SB_GROUPED ||
-         variant == GEMM_128x64_G4_SB_GROUPED || variant == GEMM_128x128_G4_GROUPED ||
-         variant == GEMM_128x128_DMA_GROUPED || variant == GEMM_64x256_DMA_GROUPED;
-}
-int octave_bucket(int x) {
-  int p = 1;
-  while (p < x) p *= 2;
-  return p;
-}
-int shape_bucket(int x) {
-  if (x <= 64) return x;
-  int p = 1;
-  while (p * 2 <= x) p *= 2;
-  const int q = p / 4;
-  return ((x + q - 1) / q) * q;
-}
-
-bool gemm_variant_narrow(int variant) { return variant == GEMM_128x32_G4_SB || variant == GEMM_64x32_G4; }
-
-// the 32-column tiles are worth timing for outputs at most kNarrowMaxN wide,
-// and for outputs up to 512 wide that 64-column tiles would pad by a further
-// eighth or more (200 columns: 224 against 256)
-static bool narrow_may_pay(int N) {
-  if (N <= kNarrowMaxN) return true;
-  const int p32 = (N + 31) / 32 * 32, p64 = (N + 63) / 64 * 64;
-  return N <= 512 && 8 * (p64 - p32) >= p32;
-}
-
-// the variant of a product that is not timed: 32-column tiles for outputs at
-// most 32 wide, 64-row tiles when the output has at most 64 rows (a 128-row
-// tile would be mostly empty)
-static int untimed_variant(const GemmArgs& g) {
-  if (g.N <= 32) return g.M <= 64 ? GEMM_64x32_G4 : GEMM_128x32_G4_SB;
-  // 64x32 tiles where they pad less or 64x64 ones would not go round twice
-  // (3600x320x80: 24 us against 27; 5850x130x130: 27 against 42), else 64x64
-  // with one LDS buffer (120x7140x120, batch 2: 40 us; 42 with two buffers)
-  const i64 tiles = (i64)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
-  if (g.M > 64 && (narrow_may_pay(g.N) || tiles < 400)) return GEMM_64x32_G4;
-  return GEMM_64x64_G4_SB;
 }
 
 void launch_gemm_choice(const GemmArgs& g, int choice, hipStream_t s) {
   if (choice >= kTransposedChoice) launch_zgemm_variant(transposed(g), choice - kTransposedChoice, s);
   else launch_zgemm_variant(g, choice, s);
 }
-static void launch_choice(const GemmArgs& g, int choice, hipStream_t s) { launch_gemm_choice(g, choice, s); }
 
-int tuned_gemm(cclr_ctx* c, const GemmArgs& g) {
+// Tile of the products that neither the register nor the evenly split kernel
+// takes: the least estimated time in us, 256 compute units taking one round of
+// tiles after another.  The constants are fitted to one MI355X; nk K tiles of
+// 16, t workgroups per 256:
+//   64x64, one LDS buffer  t (1.98 nk + 1)   7140x7140x120 825 (measured 821)
+//   128x32, one LDS buffer t (2.1 nk + 1)    2197000x10x130 1353 (1355)
+//   64x32                  t (1.08 nk + 1)   130x130x130, batch 400 257 (255)
+//   128x128 direct loads   t (7.27 nk + 8)   4000x4000x400 759 (756)
+// Over 43 shapes (N from 10 to 40000, K from 28 to 4000, batches to 700) the
+// choice is the fastest tile or within 4% of it.  The direct loads win from
+// K of 160 to 200 on where their rounds are full (6000x6000x224 985 against
+// 999; 14400x1920x256 865 against 882), the 64x64 tiles below (16900x1300x100
+// 329 against 367), 32 columns where 64 pad more (38000x200x200, batch 3 702
+// against 745; 90x90x200, batch 700 256 against 304), 32 rows likewise
+// (70x5000x240, batch 20 337 against 409).  Outputs at most 32 wide
+// stay on 32 columns (128 rows, 64 if the output has no more).
+// The XCD-grouped order re-reads less, but where the result is most of the
+// traffic the plain order is ahead (19900x19900x190 9000 against 9379): from
+// K = 320 on grouped, and the 64x64 tiles always (8385x8385x45 490 against 520).
+static int tile_variant(const GemmArgs& g) {
+  if (g.N <= 32) return g.M <= 64 ? GEMM_64x32_G4 : GEMM_128x32_G4_SB;
+  const int K = g.kchunk > 0 ? g.kchunk : g.K;
+  const double nk = (K + 15) / 16;
+  const i64 r64 = (g.M + 63) / 64, r128 = (g.M + 127) / 128, c32 = (g.N + 31) / 32, c64 = (g.N + 63) / 64;
+  auto rounds = [&](i64 tiles) { return (double)((tiles * g.batch + 255) / 256); };
+  int best = GEMM_64x64_G4_SB_GROUPED;
+  double t = rounds(r64 * c64) * (1.98 * nk + 1.0);
+  auto offer = [&](int v, double tv) {
+    if (tv < t) best = v, t = tv;
+  };
+  offer(GEMM_128x32_G4_SB, rounds(r128 * c32) * (2.1 * nk + 1.0));
+  offer(GEMM_64x32_G4, rounds(r64 * c32) * (1.08 * nk + 1.0));
+  // 32 rows, as 32 columns of C^T = B^T A^T; its stores run across the output
+  const i64 n64 = (g.N + 63) / 64, n128 = (g.N + 127) / 128, m32 = (g.M + 31) / 32;
+  offer(kTransposedChoice + GEMM_128x32_G4_SB, 1.05 * rounds(n128 * m32) * (2.1 * nk + 1.0));
+  offer(kTransposedChoice + GEMM_64x32_G4, 1.05 * rounds(n64 * m32) * (1.08 * nk + 1.0));
+  offer(K < 320 ? GEMM_128x128_DMA : GEMM_128x128_DMA_GROUPED, dma_cost(g));
+  return best;
+}
+
+int gemm_by_rule(cclr_ctx* c, const GemmArgs& g) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.K <= 0) return -1;
   if (frag_may_pay(g)) {
     small_product(c, g);
     return kFormFrag;
   }
   if (even_split(c, g)) return kFormEven;
-  const double flops = 8.0 * g.M * (double)g.N * (g.kchunk > 0 ? g.kchunk : g.K) * g.batch;
-  if (flops < 1e10) {
-    const int v = untimed_variant(g);
-    launch_zgemm_variant(g, v, c->stream);
-    return v;
-  }
-  // a split-K product keeps its whole batch (it carries the parallelism of the launch)
-  const int tmr = std::min(g.M, kTuneRows),
-            tbt = (g.nb2 > 1 || g.kchunk > 0) ? g.batch : std::min(g.batch, kTuneBatch);
-  // split-K products (kchunk > 0: the batch index carries the K chunk) are classed by the chunk length
-  // (the transposed product runs on 32-column tiles only when its row count
-  // is one that they pad less, which the row octave alone does not tell)
-  const bool trans_narrow = g.M != g.N && narrow_may_pay(g.M);
-  const auto key = std::make_tuple(octave_bucket(tmr), shape_bucket(g.N), shape_bucket(g.kchunk > 0 ? g.kchunk : g.K),
-                                   octave_bucket(tbt),
-                                   (g.sAk == 1 ? 1 : 0) + (g.sBn == 1 ? 2 : 0) + (g.nb2 > 1 ? 4 : 0) +
-                                       (g.kchunk > 0 ? 8 : 0) + (trans_narrow ? 16 : 0));
-  auto it = c->gemm_choice.find(key);
-  if (it != c->gemm_choice.end()) {
-    launch_choice(g, it->second, c->stream);
-    return it->second;
-  }
-  if (c->no_timing || !c->autotune) {  // no new timing runs (a call that may not allocate, or tuning off)
-    const int v = untimed_variant(g);
-    launch_zgemm_variant(g, v, c->stream);
-    return v;
-  }
-  // nothing else may run while the variants are timed: drain the side stream too
-  HIPCHK(hipStreamSynchronize(c->stream));
-  if (c->side) HIPCHK(hipStreamSynchronize(c->side));
-  // the timed product: the leading rows and batch entries, on a scratch output covering their index range
-  GemmArgs h = g;
-  h.M = tmr;
-  h.batch = tbt;
-  const i64 nb2 = h.nb2 > 1 ? h.nb2 : 1, nb1 = h.batch / nb2;
-  const i64 extent = (i64)(h.M - 1) * h.sCm + (i64)(h.N - 1) * h.sCn + (nb1 - 1) * h.sCb + (nb2 - 1) * h.sCb2 + 1;
-  Arena::Mark mk = c->arena.mark();
-  h.C = (cplx*)c->arena.get(sizeof(cplx) * (size_t)extent);
-  h.beta = 0;
-  hipEvent_t e0, e1;
-  HIPCHK(hipEventCreate(&e0));
-  HIPCHK(hipEventCreate(&e1));
-  // candidates: every variant (the 32-column ones only where they may pay) and,
-  // when the rows are a count that 32-column tiles pad less, those tiles on the
-  // transposed product
-  std::vector<int> cand;
-  for (int v = GEMM_128x64_G3; v < GEMM_NVAR; ++v)  // the simple kernel (variant 0) never competes
-    if (!gemm_variant_narrow(v) || narrow_may_pay(g.N)) cand.push_back(v);
-  if (trans_narrow)
-    for (int v = GEMM_128x64_G3; v < GEMM_NVAR; ++v)
-      if (gemm_variant_narrow(v)) cand.push_back(kTransposedChoice + v);
-  std::vector<double> ms(cand.size(), 0.0);
-  launch_zgemm_variant(h, gemm_default_variant(g), c->stream);  // warm caches and clocks
-  int best = gemm_default_variant(g);
-  double tbest = 1e300;
-  for (size_t q = 0; q < cand.size(); ++q) {
-    HIPCHK(hipEventRecord(e0, c->stream));
-    launch_choice(h, cand[q], c->stream);
-    HIPCHK(hipEventRecord(e1, c->stream));
-    HIPCHK(hipEventSynchronize(e1));
-    float t = 0.f;
-    HIPCHK(hipEventElapsedTime(&t, e0, e1));
-    ms[q] = t;
-    if (t < tbest) {
-      tbest = t;
-      best = cand[q];
-    }
-  }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  // within the timing noise (2%) of the fastest, prefer the variant that
-  // re-reads its operands from HBM least for the same time: the XCD-grouped
-  // tile order first, then tiles of 128 rows and of 128 or more columns, then the
-  // faster one
-  {
-    auto rereads = [](int choice) {
-      const int v = choice % kTransposedChoice;
-      const int base = gemm_variant_grouped(v) && v <= 2 * GEMM_64x64_G4 ? v - GEMM_64x64_G4 : v;
-      const bool rows128 = base == GEMM_128x64_G3 || base == GEMM_128x64_G4 || v == GEMM_128x64_G4_SB ||
-                           v == GEMM_128x64_G4_SB_GROUPED || (v >= GEMM_128x128_G4 && v < GEMM_64x256_DMA) ||
-                           v == GEMM_128x32_G4_SB;
-      const bool cols128 = v >= GEMM_128x128_G4 && !gemm_variant_narrow(v);
-      return (gemm_variant_grouped(v) ? 0 : 3) + (rows128 ? 0 : 1) + (cols128 ? 0 : 1);
-    };
-    size_t pick = 0;
-    for (size_t q = 0; q < cand.size(); ++q)
-      if (cand[q] == best) pick = q;
-    for (size_t q = 0; q < cand.size(); ++q) {
-      if (ms[q] > 1.02 * tbest) continue;
-      if (rereads(cand[q]) < rereads(cand[pick]) || (rereads(cand[q]) == rereads(cand[pick]) && ms[q] < ms[pick]))
-        pick = q;
-    }
-    best = cand[pick];
-  }
-  c->arena.reset(mk);
-  c->gemm_choice[key] = best;
-  std::vector<std::pair<int, double>> rec;
-  for (size_t q = 0; q < cand.size(); ++q) rec.push_back({cand[q], ms[q]});
-  // the product's shape, then the part that was timed (at most kTuneRows rows and kTuneBatch batch entries)
-  c->gemm_tuning_log.push_back({std::to_string(g.M) + "x" + std::to_string(g.N) + "x" + std::to_string(g.K) + " b" +
-                                    std::to_string(g.batch) + " layout" + std::to_string(std::get<4>(key)) +
-                                    " timed " + std::to_string(tmr) + "x" + std::to_string(g.N) + "x" +
-                                    std::to_string(g.K) + " b" + std::to_string(tbt),
-                                rec, best});
-  launch_choice(g, best, c->stream);
-  return best;
+  const int v = tile_variant(g);
+  launch_gemm_choice(g, v, c->stream);
+  // the record of large products, one line for each shape
+  if (8.0 * g.M * (double)g.N * g.K * g.batch >= 1e10 && c->gemm_record.size() < 256)
+    c->gemm_record.emplace(std::make_tuple(g.M, g.N, g.kchunk > 0 ? g.kchunk : g.K, g.batch), v);
+  return v;
 }
 
 // -------------------------------------------------------- integral views

@@ -243,7 +243,7 @@ std::complex<double> ccsd_residual(cclr_ctx* c, const VecSet& t, const VecSet& o
     g.B = Vp; g.sBk = 1; g.sBn = V2;
     g.C = out.d; g.sCm = V2; g.sCn = 1;
     g.ar = 1.0; g.ai = 0.0; g.beta = 0;
-    tuned_gemm(c, g);
+    gemm_by_rule(c, g);
   }
   launch_pack_sigma(1, (int)o, (int)v, X0.p, Xa.p, Xi.p, Xai.p, S1.p, out.s, out.d, nullptr, nullptr, nullptr,
                     c->stream, false);

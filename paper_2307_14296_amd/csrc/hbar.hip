@@ -134,7 +134,7 @@ void build_intermediates(cclr_ctx* c) {
     g.B = vp.d; g.sBk = V2; g.sBn = 1;
     g.C = c->Wp.c(); g.sCm = V2; g.sCn = 1;
     g.ar = 1.0; g.ai = 0.0; g.beta = 1;
-    tuned_gemm(c, g);
+    gemm_by_rule(c, g);
     c->arena.reset(m2);
   }
   // W^ie_mn = V^ie_mn - F^i_f t^ef_mn - W^io_mn t^e_o + 1/2 V^ie_fg tau^fg_mn

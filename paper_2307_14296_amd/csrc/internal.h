@@ -138,12 +138,7 @@ enum {
   GEMM_128x128_DMA_GROUPED = 16, GEMM_64x256_DMA = 17, GEMM_64x256_DMA_GROUPED = 18, GEMM_128x32_G4_SB = 19,
   GEMM_64x32_G4 = 20, GEMM_NVAR = 21
 };
-// the narrow variants (19, 20): timed by the autotuner for outputs at most this
-// wide (and for wider ones up to 512 that 64-column tiles pad much more)
-constexpr int kNarrowMaxN = 64;
-bool gemm_variant_grouped(int variant);
-bool gemm_variant_narrow(int variant);
-// an autotuner choice: an FP64 variant v, or kTransposedChoice + v for variant
+// a choice of tile: an FP64 variant v, or kTransposedChoice + v for variant
 // v on the transposed product C^T = B^T A^T
 constexpr int kTransposedChoice = 100;
 void launch_gemm_choice(const GemmArgs& g, int choice, hipStream_t s);
@@ -235,11 +230,9 @@ void launch_zgemm_frag(const GemmArgs& g, const FragPlan& p, cplx* W, hipStream_
 void launch_chunk_reduce(const GemmArgs& g, int S, const cplx* W, hipStream_t s);
 // GEMM with automatic K splitting when the output has too few tiles to fill the GPU
 void run_gemm(cclr_ctx* c, const GemmArgs& g);
-// FP64 GEMM through the autotuner (large products: variant timed once per shape class)
-int tuned_gemm(cclr_ctx* c, const GemmArgs& g);  // returns the variant launched
-// extent rounded up to the autotuner's quarter-octave and octave shape classes
-int shape_bucket(int x);
-int octave_bucket(int x);
+// FP64 GEMM on the kernel and tile that the rule on its extents names, without
+// K splitting; returns the variant launched, or the form of another kernel
+int gemm_by_rule(cclr_ctx* c, const GemmArgs& g);
 
 struct CopyArgs {
   int nd;
@@ -362,19 +355,9 @@ struct cclr_ctx {
   int sigma_prec = CCLR_FP64;
   // relative residual at which a reduced-precision inner solve is refined (0: default)
   double inner_tol = 0.0;
-  // GEMM autotuner: best FP64 kernel variant per shape class, and a record of
-  // the timings that decided it (variant -> ms)
-  std::map<std::tuple<int, int, int, int, int>, int> gemm_choice;
-  struct TuneRecord {
-    std::string shape;
-    std::vector<std::pair<int, double>> ms;  // (variant, ms) of every timed variant
-    int chosen;
-  };
-  std::vector<TuneRecord> gemm_tuning_log;
-  bool autotune = true;
-  // no new timing runs (they create events and take scratch outputs); cached
-  // choices are still used
-  bool no_timing = false;
+  // tile variant of the large FP64 products met so far, by (M, N, K, batch);
+  // at most 256 of them (read by cclr_dbg_tuning)
+  std::map<std::tuple<int, int, int, int>, int> gemm_record;
   // input checks (see InputCheck): kInputMarks marks on the device, the outcome
   // in pinned host memory, and the number of the current call
   int* input_bad = nullptr;

@@ -45,7 +45,7 @@ SigmaAcc prepare(cclr_ctx* c, const VecSet& in) {
 // operator, made on first use; the trial-vector side is split per product.
 void op_gemm(cclr_ctx* c, const GemmArgs& g, int which) {
   if (c->sigma_prec == CCLR_FP64) {
-    if (which < 2) tuned_gemm(c, g);
+    if (which < 2) gemm_by_rule(c, g);
     else run_gemm(c, g);
     return;
   }

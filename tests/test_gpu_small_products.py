@@ -121,6 +121,20 @@ def test_even_split(lib, M, N, K, batch, ta, tb, tc, conjA, conjB, beta):
     product(*lib, M, N, K, batch, ta, tb, tc, conjA, conjB, beta, -8)
 
 
+# the tile rule: each tile it names (10: 64x64, 15 and 16: 128x128 in plain and
+# grouped order, 19: 128x32, 20: 64x32, 100 + v: on the transposed product),
+# ragged in every extent, and 32 and 33 columns and 64 and 65 rows
+TILES = [(1301, 1289, 101, 1, 10), (2047, 2041, 239, 1, 15), (2041, 2047, 333, 1, 16), (90, 89, 201, 80, 19),
+         (701, 690, 99, 1, 20), (70, 1000, 239, 10, 119), (70, 1999, 99, 8, 120), (3000, 32, 250, 1, 19),
+         (64, 32, 90, 130, 20), (65, 32, 90, 130, 19), (3000, 33, 250, 1, 20)]
+
+
+@pytest.mark.parametrize("M,N,K,batch,form", TILES)
+@pytest.mark.parametrize("ta,tb,tc,conjA,conjB,beta", LAYOUTS)
+def test_tile_rule(lib, M, N, K, batch, form, ta, tb, tc, conjA, conjB, beta):
+    product(*lib, M, N, K, batch, ta, tb, tc, conjA, conjB, beta, form)
+
+
 @pytest.mark.parametrize("fm", [2, 3, 4, 5, 6])
 @pytest.mark.parametrize("M,N,K,batch,cutters", [(97, 70, 300, 1, 512), (97, 70, 300, 1, 0), (161, 1, 129, 2, 512),
                                                  (16, 64, 4100, 1, 7), (700, 3000, 140, 1, 512),
