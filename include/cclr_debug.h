@@ -85,6 +85,15 @@ int cclr_dbg_run_gemm_b2(cclr_ctx* ctx, int M, int N, int K, int nb1, int nb2, c
                          long long sBb2, long long sBk, long long sBn, cclr_c64* C, long long sCb, long long sCb2,
                          long long sCm, long long sCn, double alpha_re, double alpha_im, int beta);
 
+/* C (+)= alpha A B (row-major M x K, K x N, M x N; device pointers) on
+ * pre-split operands (prec CCLR_FP32, CCLR_BF16X3 or CCLR_BF16X2) with tiles
+ * of bm (64, 96, 128) x 128, those that do not fill whole rounds of workgroups
+ * cut into at most `cutters` <= 256 runs (0: none is cut); bm = 0: the plan
+ * the library chooses, cut tiles allowed if cutters > 0.  cut: how many tiles
+ * were cut (may be null). */
+int cclr_dbg_split_product(int prec, int bm, int cutters, int M, int N, int K, const cclr_c64* A, const cclr_c64* B,
+                           cclr_c64* C, double alpha_re, double alpha_im, int beta, int* cut);
+
 /* The same product (batch 1) in reduced arithmetic on pre-split operands, the
  * form of the transforms' ladder and ring products: prec = CCLR_FP32 (FP32
  * MFMA, three real products per complex block), CCLR_BF16X3 or CCLR_BF16X2

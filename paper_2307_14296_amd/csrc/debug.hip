@@ -206,11 +206,35 @@ int cclr_dbg_zgemm_group_f64(int variant, int nprob, const int* M, const int* N,
   return rc;
 }
 
+int cclr_dbg_split_product(int prec, int bm, int cutters, int M, int N, int K, const cclr_c64* A, const cclr_c64* B,
+                           cclr_c64* C, double ar, double ai, int beta, int* cut) {
+  char* dev = nullptr;
+  int rc = CCLR_OK;
+  try {
+    REQUIRE(M > 0 && N > 0 && K > 0 && cutters >= 0 && cutters <= 256, CCLR_EINVAL, "empty product or too many runs");
+    REQUIRE(prec == CCLR_FP32 || prec == CCLR_BF16X3 || prec == CCLR_BF16X2, CCLR_EINVAL, "unknown arithmetic");
+    const int form = split_form_of(prec);
+    const SplitPlan p = bm ? split_plan_for(M, N, K, form, bm, cutters) : split_plan(M, N, K, form, cutters > 0);
+    const size_t na = split_bytes(M, K, form, 0, p.bm), nb = split_bytes(N, K, form, 1);
+    HIPCHK(hipMalloc(&dev, na + nb + split_workspace(p)));
+    const SplitMat sa = launch_split(M, K, (const cplx*)A, K, 1, 0, dev, form, 0, nullptr, p.bm);
+    const SplitMat sb = launch_split(N, K, (const cplx*)B, 1, N, 0, dev + na, form, 1, nullptr);
+    launch_split_gemm(sa, sb, (cplx*)C, N, 1, ar, ai, beta, p, dev + na + nb, nullptr);
+    HIPCHK(hipDeviceSynchronize());
+    if (cut) *cut = (int)(p.tiles - p.whole);
+  } catch (const CclrError& e) {
+    rc = e.code;
+  }
+  if (dev) (void)hipFree(dev);
+  return rc;
+}
+
 int cclr_dbg_zgemm_lowp(int prec, int M, int N, int K, const cclr_c64* A, long long sAm, long long sAk, int conjA,
                         const cclr_c64* B, long long sBk, long long sBn, int conjB, cclr_c64* C, long long sCm,
                         long long sCn, double ar, double ai, int beta) {
   void* wa = nullptr;
   void* wb = nullptr;
+  void* ww = nullptr;
   int rc = CCLR_OK;
   try {
     REQUIRE(M > 0 && N > 0 && K > 0, CCLR_EINVAL, "empty product");
@@ -222,11 +246,13 @@ int cclr_dbg_zgemm_lowp(int prec, int M, int N, int K, const cclr_c64* A, long l
     g.ar = ar; g.ai = ai; g.beta = beta;
     if (prec == CCLR_FP32 || prec == CCLR_BF16X3 || prec == CCLR_BF16X2) {
       const int form = split_form_of(prec);
-      HIPCHK(hipMalloc(&wa, split_bytes(M, K, form, 0)));
+      const SplitPlan p = split_plan(M, N, K, form, true);
+      HIPCHK(hipMalloc(&wa, split_bytes(M, K, form, 0, p.bm)));
       HIPCHK(hipMalloc(&wb, split_bytes(N, K, form, 1)));
-      const SplitMat sa = launch_split(M, K, g.A, sAm, sAk, conjA, wa, form, 0, nullptr);
+      if (p.cutters > 0) HIPCHK(hipMalloc(&ww, split_workspace(p)));
+      const SplitMat sa = launch_split(M, K, g.A, sAm, sAk, conjA, wa, form, 0, nullptr, p.bm);
       const SplitMat sb = launch_split(N, K, g.B, sBn, sBk, conjB, wb, form, 1, nullptr);
-      launch_split_gemm(sa, sb, g.C, sCm, sCn, ar, ai, beta, nullptr);
+      launch_split_gemm(sa, sb, g.C, sCm, sCn, ar, ai, beta, p, ww, nullptr);
     } else {
       REQUIRE(prec == 16, CCLR_EINVAL, "unknown arithmetic");
       launch_zgemm_lowp(g, CCLR_FP32, nullptr);
@@ -237,6 +263,7 @@ int cclr_dbg_zgemm_lowp(int prec, int M, int N, int K, const cclr_c64* A, long l
   }
   if (wa) (void)hipFree(wa);
   if (wb) (void)hipFree(wb);
+  if (ww) (void)hipFree(ww);
   return rc;
 }
 

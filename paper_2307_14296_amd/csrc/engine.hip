@@ -614,6 +614,18 @@ void contract(cclr_ctx* c, cplx alpha, const Ten& A, const char* la, const Ten& 
 // short-output VALU kernel, -5 reduced precision on pre-split FP32 planes, -6
 // short-output VALU kernel on a long operand contiguous in k, -7 small
 // products straight from registers, -8 even split over the compute units)
+// g with its B side split already: splits the A side and multiplies
+void split_product(cclr_ctx* c, const GemmArgs& g, int form, const SplitMat& B) {
+  Arena::Mark mk = c->arena.mark();
+  SplitPlan p = split_plan(g.M, g.N, g.K, form, true);
+  void* W = p.cutters > 0 ? c->arena.try_get(split_workspace(p)) : nullptr;
+  if (p.cutters > 0 && !W) p = split_plan(g.M, g.N, g.K, form, false);
+  void* wa = c->arena.get(split_bytes(g.M, g.K, form, 0, p.bm));
+  const SplitMat A = launch_split(g.M, g.K, g.A, g.sAm, g.sAk, g.conjA, wa, form, 0, c->stream, p.bm);
+  launch_split_gemm(A, B, g.C, g.sCm, g.sCn, g.ar, g.ai, g.beta, p, W, c->stream);
+  c->arena.reset(mk);
+}
+
 static void run_gemm_form(cclr_ctx* c, const GemmArgs& g, int& form);
 static bool narrow_may_pay(int N);
 void run_gemm(cclr_ctx* c, const GemmArgs& g) {
@@ -911,11 +923,9 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
     if (g.batch == 1 && g.kchunk == 0 && g.nb2 <= 1 && g.M >= 512 && g.N >= 512 && g.K >= 256) {
       form = -5;
       Arena::Mark mk = c->arena.mark();
-      void* wa = c->arena.get(split_bytes(g.M, g.K, F32_G3, 0));
       void* wb = c->arena.get(split_bytes(g.N, g.K, F32_G3, 1));
-      const SplitMat A = launch_split(g.M, g.K, g.A, g.sAm, g.sAk, g.conjA, wa, F32_G3, 0, c->stream);
       const SplitMat B = launch_split(g.N, g.K, g.B, g.sBn, g.sBk, g.conjB, wb, F32_G3, 1, c->stream);
-      launch_split_gemm(A, B, g.C, g.sCm, g.sCn, g.ar, g.ai, g.beta, c->stream);
+      split_product(c, g, F32_G3, B);
       c->arena.reset(mk);
       return;
     }

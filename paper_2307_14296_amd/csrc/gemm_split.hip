@@ -31,6 +31,8 @@
 // instructions, no branches in the loop).  The Jacobian's ladder and ring
 // operators are split once per set of amplitudes and kept; the trial vectors
 // are split per product.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace {
@@ -38,7 +40,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
 
-constexpr int TM = 128;  // tile rows of both operands (and row padding of every split operand)
+constexpr int TN = 128;  // tile columns, and row padding of the B side
 
 // plane codes of a split operand
 enum { P_RH = 0, P_RL, P_IH, P_IL };
@@ -126,19 +128,70 @@ __device__ __forceinline__ bf8 as_bf8(u4v x) { return __builtin_bit_cast(bf8, x)
 
 #define MF(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0)
 
-// Copy CH contiguous 16-byte chunks (a multiple of NT) from global memory
+// Copy CH contiguous 16-byte chunks (a multiple of 64) from global memory
 // into LDS with direct loads; each wave instruction moves 64 consecutive chunks.
 template <int NT, int CH>
 __device__ __forceinline__ void dma_tile(const u4v* __restrict__ g, u4v* lds, int tid) {
-  static_assert(CH % NT == 0, "tile must be a whole number of rounds");
+  static_assert(CH % 64 == 0, "tile must be a whole number of wave loads");
 #pragma unroll
-  for (int e0 = 0; e0 < CH; e0 += NT)
+  for (int e0 = 0; e0 < CH; e0 += NT) {
+    if (e0 + NT > CH && e0 + (tid & ~63) >= CH) break;
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(g + e0 + tid),
                                      (__attribute__((address_space(3))) void*)(lds + e0 + (tid & ~63)), 16, 0, 0);
+  }
 }
 
-// C[m][n] (+)= alpha * sum_k A[m][k] B[n][k] on split operands.  128 x 128
-// tile per workgroup of eight waves (2 x 4, each 64 x 32 in 16x16 MFMA
+// The workgroups of one XCD (hardware index modulo 8) take consecutive
+// positions of the work order.
+__device__ __forceinline__ int xcd_position(int w, int n) {
+  const int x = w & 7, l = w >> 3, per = n >> 3, rem = n & 7;
+  return (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + l;
+}
+
+// Deals a product to this workgroup: its whole tiles first, then its run over
+// the k steps of the cut ones (at most nk steps, so at most two tiles).
+// seg(tile, first step, end, slot): slot < 0 a whole tile, else partial sums
+// to that slot of the workspace.
+template <class Seg>
+__device__ __forceinline__ void deal(const SplitPlan& p, const Seg& seg) {
+  const int pos = xcd_position((int)blockIdx.x, (int)gridDim.x);
+  const i64 total = (p.tiles - p.whole) * p.nk;
+  i64 t = pos, it = 0, end = 0;
+  if (pos < p.cutters) {
+    it = (i64)pos * total / p.cutters;
+    end = (i64)(pos + 1) * total / p.cutters;
+  }
+  i64 slot = 2 * (i64)pos;
+  while (t < p.whole || it < end) {
+    i64 tile = t, to = -1;
+    int k0 = 0, k1 = p.nk;
+    if (t < p.whole) {
+      t += gridDim.x;
+    } else {
+      const i64 c = it / p.nk;
+      tile = p.whole + c;
+      k0 = (int)(it - c * p.nk);
+      k1 = (int)min((i64)p.nk, k0 + (end - it));
+      if (k0 > 0 || k1 < p.nk) to = slot;
+      ++slot;
+      it += k1 - k0;
+    }
+    seg(tile, k0, k1, to);
+  }
+}
+
+__device__ __forceinline__ void put(cplx* dst, double xr, double xi, double ar, double ai, int beta) {
+  cplx y = make_double2(ar * xr - ai * xi, ar * xi + ai * xr);
+  if (beta) {
+    const cplx o = *dst;
+    y.x += o.x;
+    y.y += o.y;
+  }
+  *dst = y;
+}
+
+// C[m][n] (+)= alpha * sum_k A[m][k] B[n][k] on split operands.  BM x 128
+// tile per workgroup of eight waves (2 x 4, each BM/2 x 32 in 16x16 MFMA
 // blocks; two waves per SIMD, which hide each other's LDS and barrier
 // waits: about 1.2 times faster than four waves of 64 x 64 with one wave per
 // SIMD), double-buffered LDS filled by direct loads one k step ahead: each
@@ -148,38 +201,38 @@ __device__ __forceinline__ void dma_tile(const u4v* __restrict__ g, u4v* lds, in
 // block, whose time covers the reads of the next step's first fragments
 // (3-5% faster than a barrier after the last MFMA).  The
 // stages are separate LDS arrays, so the compiler does not make the reads of
-// one wait for the direct loads into the other.  Workgroups are numbered so
-// that each XCD (workgroups are dealt to the 8 XCDs round-robin) walks a
-// contiguous range of tiles, m fastest: the B tile of a step is shared by
-// the workgroups of one XCD and its L2.
-template <int F>
+// one wait for the direct loads into the other.
+//
+// The LDS holds one workgroup per compute unit.  A solve's transforms have
+// few tiles (a ladder of four vectors at o = 12, v = 90 is 264 x 4005: 96 of
+// 128 x 128, padded by 45%), so the grid is at most 256 workgroups that take
+// whole tiles while those fill all of them and equal runs of the k steps of
+// the others (deal); k_split_join adds the partial sums.  BM is 64, 96 or
+// 128, by estimated time (split_plan).  Bound by the bf16 MFMAs (1.28 us of a
+// 128-row k step; 1.5 to 2.0 measured, by how many compute units compete for
+// the operands).  Against whole 128 x 128 tiles, X3, us: 264x4005x4005 97 / 213,
+// 66x4005x4005 41 / 203, 1080x1080x1080 45 / 67, 4320x1080x1080 121 / 150,
+// 570x19900x19900 3790 / 4810.
+template <int F, int BM>
 __global__ __launch_bounds__(512) void k_cgemm_bf16s(const u4v* __restrict__ As, const u4v* __restrict__ Bs,
-                                                     int Mpad, int Npad, int nkc, int M, int N, cplx* __restrict__ C,
-                                                     i64 sCm, i64 sCn, double ar, double ai, int beta, int Mt, int T) {
+                                                     int Mpad, int Npad, int M, int N, cplx* __restrict__ C, i64 sCm,
+                                                     i64 sCn, double ar, double ai, int beta, SplitPlan p,
+                                                     float2* __restrict__ W) {
   constexpr FormDesc D = kForms[F];
   constexpr int PA = D.pa, PB = D.pb;
   constexpr int RSA = 4 * PA, RSB = 4 * PB;  // chunks per row
   constexpr int NT = 512;  // eight waves: two along m, four along n
-  constexpr int WM = TM / 2, WN = TM / 4;
+  constexpr int WM = BM / 2, WN = TN / 4;
   constexpr int FM = WM / 16, FN = WN / 16;
-  constexpr int CA = TM * RSA, CB = TM * RSB;  // chunks per tile and k step
+  constexpr int CA = BM * RSA, CB = TN * RSB;  // chunks per tile and k step
   // the two stages in separate arrays, so the compiler can tell a read of
   // one stage from the direct loads into the other and does not make the
   // reads wait for the loads
   __shared__ u4v sA0[CA], sA1[CA];
   __shared__ u4v sB0[CB], sB1[CB];
-  const int per = gridDim.x >> 3;
-  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-  if (t >= T) return;
-  const int m0 = (t % Mt) * TM, n0 = (t / Mt) * TM;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave & 1) * WM, wn = (wave >> 1) * WN;
-  static_assert(CA % NT == 0 && CB % NT == 0, "tiles must be whole rounds of direct loads");
   const int rr = lane & 15, g = lane >> 4;
-  auto fetch = [&](int kc, u4v* la, u4v* lb) {
-    dma_tile<NT, CA>(As + ((i64)kc * Mpad + m0) * RSA, la, tid);
-    dma_tile<NT, CB>(Bs + ((i64)kc * Npad + n0) * RSB, lb, tid);
-  };
   // LDS offsets of this lane's fragments (rows wm + 16 i + rr, wn + 16 j + rr;
   // the swizzle depends on the row only through rr)
   int offa[PA], offb[PB];
@@ -187,97 +240,97 @@ __global__ __launch_bounds__(512) void k_cgemm_bf16s(const u4v* __restrict__ As,
   for (int p = 0; p < PA; ++p) offa[p] = (wm + rr) * RSA + swz(PA, rr, 4 * p + g);
 #pragma unroll
   for (int p = 0; p < PB; ++p) offb[p] = (wn + rr) * RSB + swz(PB, rr, 4 * p + g);
-  f4 acc[3][FM][FN];
+  auto segment = [&](i64 t, int k0, int k1, i64 slot) {
+    const int m0 = (int)(t % p.tm) * BM, n0 = (int)(t / p.tm) * TN;
+    auto fetch = [&](int kc, u4v* la, u4v* lb) {
+      dma_tile<NT, CA>(As + ((i64)kc * Mpad + m0) * RSA, la, tid);
+      dma_tile<NT, CB>(Bs + ((i64)kc * Npad + n0) * RSB, lb, tid);
+    };
+    f4 acc[3][FM][FN];
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[a][i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    auto mfma_i = [&](int i, const bf8 (&a)[PA], const bf8 (&b)[FN][PB]) {
+#pragma unroll
+      for (int q = 0; q < D.nprod; ++q)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[D.prod[q][2]][i][j] = MF(a[D.prod[q][0]], b[j][D.prod[q][1]], acc[D.prod[q][2]][i][j]);
+    };
+    auto read_b = [&](const u4v* cb, bf8 (&b)[FN][PB]) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int p = 0; p < PB; ++p) b[j][p] = as_bf8(cb[offb[p] + 16 * j * RSB]);
+    };
+    auto read_a = [&](const u4v* ca, int i, bf8 (&a)[PA]) {
+#pragma unroll
+      for (int p = 0; p < PA; ++p) a[p] = as_bf8(ca[offa[p] + 16 * i * RSA]);
+    };
+    bf8 bq[FN][PB], aq[PA];  // the first fragments of the next step, read ahead
+    // one k step on the stage (ca, cb) while the next step's tiles load into (na, nb)
+    auto step = [&](int kc, const u4v* ca, const u4v* cb, u4v* na, u4v* nb) {
+      // the last step reloads its own tiles into the idle stage (no branch)
+      fetch(kc + 1 < k1 ? kc + 1 : kc, na, nb);
+      __builtin_amdgcn_sched_barrier(0);  // the loads are requested first, not scheduled between the MFMAs
+      // the wait and the barrier come once the last fragments of this stage
+      // are read; the next stage's first fragments are read while the MFMAs
+      // of the last row block run
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        bf8 a[PA];
+        if (i == 0) {
+#pragma unroll
+          for (int p = 0; p < PA; ++p) a[p] = aq[p];
+        } else {
+          read_a(ca, i, a);
+        }
+        if (i + 1 < FM) {
+          mfma_i(i, a, bq);
+        } else {
+          bf8 bn[FN][PB], an[PA];
+          __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_s_waitcnt(0);
+          __syncthreads();
+          read_b(nb, bn);
+          read_a(na, 0, an);
+          mfma_i(i, a, bq);
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int p = 0; p < PB; ++p) bq[j][p] = bn[j][p];
+#pragma unroll
+          for (int p = 0; p < PA; ++p) aq[p] = an[p];
+        }
+      }
+    };
+    __syncthreads();  // every wave is done with the stages of the previous segment
+    fetch(k0, sA0, sB0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    read_b(sB0, bq);
+    read_a(sA0, 0, aq);
+    for (int kc = k0; kc < k1; kc += 2) {
+      step(kc, sA0, sB0, sA1, sB1);
+      if (kc + 1 < k1) step(kc + 1, sA1, sB1, sA0, sB0);
+    }
+    // output block (i, j): row 16i + 4*(lane/16) + r, column 16j + lane%16
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j) acc[a][i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  auto mfma_i = [&](int i, const bf8 (&a)[PA], const bf8 (&b)[FN][PB]) {
-#pragma unroll
-    for (int q = 0; q < D.nprod; ++q)
-#pragma unroll
       for (int j = 0; j < FN; ++j)
-        acc[D.prod[q][2]][i][j] = MF(a[D.prod[q][0]], b[j][D.prod[q][1]], acc[D.prod[q][2]][i][j]);
-  };
-  auto read_b = [&](const u4v* cb, bf8 (&b)[FN][PB]) {
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int p = 0; p < PB; ++p) b[j][p] = as_bf8(cb[offb[p] + 16 * j * RSB]);
-  };
-  auto read_a = [&](const u4v* ca, int i, bf8 (&a)[PA]) {
-#pragma unroll
-    for (int p = 0; p < PA; ++p) a[p] = as_bf8(ca[offa[p] + 16 * i * RSA]);
-  };
-  bf8 bq[FN][PB], aq[PA];  // the first fragments of the next step, read ahead
-  // one k step on the stage (ca, cb) while the next step's tiles load into (na, nb)
-  auto step = [&](int kc, const u4v* ca, const u4v* cb, u4v* na, u4v* nb) {
-    // the last step reloads its own tiles into the idle stage (no branch)
-    fetch(kc + 1 < nkc ? kc + 1 : kc, na, nb);
-    __builtin_amdgcn_sched_barrier(0);  // the loads are requested first, not scheduled between the MFMAs
-    // the wait and the barrier come once the last fragments of this stage
-    // are read; the next stage's first fragments are read while the MFMAs
-    // of the last row block run
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      bf8 a[PA];
-      if (i == 0) {
-#pragma unroll
-        for (int p = 0; p < PA; ++p) a[p] = aq[p];
-      } else {
-        read_a(ca, i, a);
-      }
-      if (i + 1 < FM) {
-        mfma_i(i, a, bq);
-      } else {
-        bf8 bn[FN][PB], an[PA];
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        read_b(nb, bn);
-        read_a(na, 0, an);
-        mfma_i(i, a, bq);
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int p = 0; p < PB; ++p) bq[j][p] = bn[j][p];
-#pragma unroll
-        for (int p = 0; p < PA; ++p) aq[p] = an[p];
-      }
-    }
-  };
-  fetch(0, sA0, sB0);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  read_b(sB0, bq);
-  read_a(sA0, 0, aq);
-  for (int kc = 0; kc < nkc; kc += 2) {
-    step(kc, sA0, sB0, sA1, sB1);
-    if (kc + 1 < nkc) step(kc + 1, sA1, sB1, sA0, sB0);
-  }
-  // output block (i, j): row 16i + 4*(lane/16) + r, column 16j + lane%16
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * g + r;
-        const int n = n0 + wn + 16 * j + rr;
-        if (m < M && n < N) {
+        for (int r = 0; r < 4; ++r) {
+          const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
           const double xr = (double)acc[0][i][j][r] - (double)acc[1][i][j][r], xi = (double)acc[2][i][j][r];
-          cplx y = make_double2(ar * xr - ai * xi, ar * xi + ai * xr);
-          cplx* dst = C + (i64)m * sCm + (i64)n * sCn;
-          if (beta) {
-            const cplx o = *dst;
-            y.x += o.x;
-            y.y += o.y;
-          }
-          *dst = y;
+          if (slot >= 0) W[(slot * BM + m) * TN + n] = make_float2((float)xr, (float)xi);
+          else if (m0 + m < M && n0 + n < N) put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, xr, xi, ar, ai, beta);
         }
-      }
+  };
+  deal(p, segment);
 }
 #undef MF
 
@@ -338,120 +391,150 @@ __global__ __launch_bounds__(256) void k_split_f32(int rows, int K, const cplx* 
 }
 
 // C[m][n] (+)= alpha * sum_k A[m][k] B[n][k] on FP32 split operands: the
-// pipeline of k_cgemm_bf16s (128 x 128 tiles of eight 64 x 32 waves, direct
-// loads one 16-deep k step ahead into the other of two LDS stages).
+// pipeline and the even split of k_cgemm_bf16s (BM x 128 tiles of eight
+// BM/2 x 32 waves, direct loads one 16-deep k step ahead into the other of
+// two LDS stages).  Against whole 128 x 128 tiles, us: 264x4005x4005 283 / 808,
+// 4320x1080x1080 315 / 464, 570x19900x19900 11680 / 15890.
+template <int BM>
 __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, const u4v* __restrict__ Bs, int Mpad,
-                                                    int Npad, int nkb, int M, int N, cplx* __restrict__ C, i64 sCm,
-                                                    i64 sCn, double ar, double ai, int beta, int Mt, int T) {
-  constexpr int RS = 12, NT = 512, WM = TM / 2, WN = TM / 4, FM = WM / 16, FN = WN / 16;
-  constexpr int CH = TM * RS;  // chunks per tile and k step
-  static_assert(CH % NT == 0, "tiles must be whole rounds of direct loads");
-  __shared__ u4v sA0[CH], sA1[CH];
-  __shared__ u4v sB0[CH], sB1[CH];
-  const int per = gridDim.x >> 3;
-  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-  if (t >= T) return;
-  const int m0 = (t % Mt) * TM, n0 = (t / Mt) * TM;
+                                                    int Npad, int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn,
+                                                    double ar, double ai, int beta, SplitPlan p,
+                                                    float2* __restrict__ W) {
+  constexpr int RS = 12, NT = 512, WM = BM / 2, WN = TN / 4, FM = WM / 16, FN = WN / 16;
+  constexpr int CA = BM * RS, CB = TN * RS;  // chunks per tile and k step
+  __shared__ u4v sA0[CA], sA1[CA];
+  __shared__ u4v sB0[CB], sB1[CB];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave & 1) * WM, wn = (wave >> 1) * WN;
   const int rr = lane & 15, g = lane >> 4;
-  auto fetch = [&](int kb, u4v* la, u4v* lb) {
-    dma_tile<NT, CH>(As + ((i64)kb * Mpad + m0) * RS, la, tid);
-    dma_tile<NT, CH>(Bs + ((i64)kb * Npad + n0) * RS, lb, tid);
-  };
   // the rotation depends on the row only through rr (wm, wn and 16 i are multiples of 16)
   int off[3];
 #pragma unroll
   for (int p = 0; p < 3; ++p) off[p] = rr * RS + f32pos(rr, 4 * p + g);
-  f4 acc[3][FM][FN];
+  auto segment = [&](i64 t, int k0, int k1, i64 slot) {
+    const int m0 = (int)(t % p.tm) * BM, n0 = (int)(t / p.tm) * TN;
+    auto fetch = [&](int kb, u4v* la, u4v* lb) {
+      dma_tile<NT, CA>(As + ((i64)kb * Mpad + m0) * RS, la, tid);
+      dma_tile<NT, CB>(Bs + ((i64)kb * Npad + n0) * RS, lb, tid);
+    };
+    f4 acc[3][FM][FN];
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[a][i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    auto mfma_i = [&](int i, const f4 (&a)[3], const f4 (&b)[FN][3]) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+            acc[p][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[p][s], b[j][p][s], acc[p][i][j], 0, 0, 0);
+    };
+    auto read_b = [&](const u4v* cb, f4 (&b)[FN][3]) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) b[j][p] = __builtin_bit_cast(f4, cb[(wn + 16 * j) * RS + off[p]]);
+    };
+    auto read_a = [&](const u4v* ca, int i, f4 (&a)[3]) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) a[p] = __builtin_bit_cast(f4, ca[(wm + 16 * i) * RS + off[p]]);
+    };
+    f4 bq[FN][3], aq[3];  // the first fragments of the next step, read ahead
+    auto step = [&](int kb, const u4v* ca, const u4v* cb, u4v* na, u4v* nb) {
+      fetch(kb + 1 < k1 ? kb + 1 : kb, na, nb);
+      __builtin_amdgcn_sched_barrier(0);  // the loads are requested first, not scheduled between the MFMAs
+      // as in the split-BF16 kernel: wait and barrier before the last row block's MFMAs
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        f4 a[3];
+        if (i == 0) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p) a[p] = aq[p];
+        } else {
+          read_a(ca, i, a);
+        }
+        if (i + 1 < FM) {
+          mfma_i(i, a, bq);
+        } else {
+          f4 bn[FN][3], an[3];
+          __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_s_waitcnt(0);
+          __syncthreads();
+          read_b(nb, bn);
+          read_a(na, 0, an);
+          mfma_i(i, a, bq);
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) bq[j][p] = bn[j][p];
+#pragma unroll
+          for (int p = 0; p < 3; ++p) aq[p] = an[p];
+        }
+      }
+    };
+    __syncthreads();  // every wave is done with the stages of the previous segment
+    fetch(k0, sA0, sB0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    read_b(sB0, bq);
+    read_a(sA0, 0, aq);
+    for (int kb = k0; kb < k1; kb += 2) {
+      step(kb, sA0, sB0, sA1, sB1);
+      if (kb + 1 < k1) step(kb + 1, sA1, sB1, sA0, sB0);
+    }
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j) acc[a][i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  auto mfma_i = [&](int i, const f4 (&a)[3], const f4 (&b)[FN][3]) {
+      for (int j = 0; j < FN; ++j)
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[p][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[p][s], b[j][p][s], acc[p][i][j], 0, 0, 0);
-  };
-  auto read_b = [&](const u4v* cb, f4 (&b)[FN][3]) {
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) b[j][p] = __builtin_bit_cast(f4, cb[(wn + 16 * j) * RS + off[p]]);
-  };
-  auto read_a = [&](const u4v* ca, int i, f4 (&a)[3]) {
-#pragma unroll
-    for (int p = 0; p < 3; ++p) a[p] = __builtin_bit_cast(f4, ca[(wm + 16 * i) * RS + off[p]]);
-  };
-  f4 bq[FN][3], aq[3];  // the first fragments of the next step, read ahead
-  auto step = [&](int kb, const u4v* ca, const u4v* cb, u4v* na, u4v* nb) {
-    fetch(kb + 1 < nkb ? kb + 1 : kb, na, nb);
-    __builtin_amdgcn_sched_barrier(0);  // the loads are requested first, not scheduled between the MFMAs
-    // as in the split-BF16 kernel: wait and barrier before the last row block's MFMAs
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      f4 a[3];
-      if (i == 0) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) a[p] = aq[p];
-      } else {
-        read_a(ca, i, a);
-      }
-      if (i + 1 < FM) {
-        mfma_i(i, a, bq);
-      } else {
-        f4 bn[FN][3], an[3];
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        read_b(nb, bn);
-        read_a(na, 0, an);
-        mfma_i(i, a, bq);
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int p = 0; p < 3; ++p) bq[j][p] = bn[j][p];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) aq[p] = an[p];
-      }
-    }
-  };
-  fetch(0, sA0, sB0);
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  read_b(sB0, bq);
-  read_a(sA0, 0, aq);
-  for (int kb = 0; kb < nkb; kb += 2) {
-    step(kb, sA0, sB0, sA1, sB1);
-    if (kb + 1 < nkb) step(kb + 1, sA1, sB1, sA0, sB0);
-  }
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * g + r;
-        const int n = n0 + wn + 16 * j + rr;
-        if (m < M && n < N) {
-          const double k1 = acc[0][i][j][r], k2 = acc[1][i][j][r], k3 = acc[2][i][j][r];
-          const double xr = k1 - k3, xi = k1 + k2;
-          cplx y = make_double2(ar * xr - ai * xi, ar * xi + ai * xr);
-          cplx* dst = C + (i64)m * sCm + (i64)n * sCn;
-          if (beta) {
-            const cplx o = *dst;
-            y.x += o.x;
-            y.y += o.y;
-          }
-          *dst = y;
+        for (int r = 0; r < 4; ++r) {
+          const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
+          const double g1 = acc[0][i][j][r], g2 = acc[1][i][j][r], g3 = acc[2][i][j][r];
+          const double xr = g1 - g3, xi = g1 + g2;
+          if (slot >= 0) W[(slot * BM + m) * TN + n] = make_float2((float)xr, (float)xi);
+          else if (m0 + m < M && n0 + n < N) put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, xr, xi, ar, ai, beta);
         }
-      }
+  };
+  deal(p, segment);
+}
+
+// Adds the partial sums of cut tile whole + blockIdx.x in the order of k, in
+// FP64, and stores the result, one element per thread (blockIdx.y: which 256
+// of the tile).
+__global__ __launch_bounds__(256) void k_split_join(int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn, double ar,
+                                                    double ai, int beta, SplitPlan p, const float2* __restrict__ W) {
+  const i64 total = (p.tiles - p.whole) * p.nk, t = blockIdx.x;
+  const i64 lo = t * p.nk, hi = lo + p.nk;
+  // run c covers the k steps [c total / cutters, (c + 1) total / cutters): the runs with a part of [lo, hi)
+  i64 c0 = lo * p.cutters / total;
+  while ((c0 + 1) * total / p.cutters <= lo) ++c0;
+  const i64 b0 = c0 * total / p.cutters;
+  if (b0 <= lo && (c0 + 1) * total / p.cutters >= hi) return;  // in one run: stored whole
+  i64 c1 = c0 + 1;
+  while (c1 < p.cutters && c1 * total / p.cutters < hi) ++c1;
+  const i64 tile = p.whole + t;
+  const int size = p.bm * TN, e = blockIdx.y * 256 + threadIdx.x;
+  const int m = (int)(tile % p.tm) * p.bm + e / TN, n = (int)(tile / p.tm) * TN + e % TN;
+  if (m >= M || n >= N) return;
+  // the first run may have begun in the tile before: then this is its second piece
+  const float2 first = W[(2 * c0 + (b0 < lo ? 1 : 0)) * size + e];
+  double xr = first.x, xi = first.y;
+  constexpr int U = 4;
+  for (i64 c = c0 + 1; c < c1; c += U) {
+    float2 w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) w[u] = c + u < c1 ? W[2 * (c + u) * size + e] : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      xr += (double)w[u].x;
+      xi += (double)w[u].y;
+    }
+  }
+  put(C + (i64)m * sCm + (i64)n * sCn, xr, xi, ar, ai, beta);
 }
 
 template <int P>
@@ -469,12 +552,12 @@ bool split_form_valid(int form) { return form == BF16_X3 || form == BF16_X2 || f
 
 int split_form_of(int prec) { return prec == CCLR_FP32 ? F32_G3 : prec == CCLR_BF16X2 ? BF16_X2 : BF16_X3; }
 
-SplitMat split_shape(int rows, int K, int form, int side) {
+SplitMat split_shape(int rows, int K, int form, int side, int tile) {
   REQUIRE(split_form_valid(form), CCLR_EINVAL, "split: unknown form");
   SplitMat s;
   s.rows = rows;
   s.K = K;
-  s.rows_pad = (rows + TM - 1) / TM * TM;
+  s.rows_pad = (rows + tile - 1) / tile * tile;
   s.form = form;
   s.side = side;
   if (form == F32_G3) {
@@ -491,15 +574,15 @@ SplitMat split_shape(int rows, int K, int form, int side) {
   return s;
 }
 
-size_t split_bytes(int rows, int K, int form, int side) {
-  const SplitMat s = split_shape(rows, K, form, side);
+size_t split_bytes(int rows, int K, int form, int side, int tile) {
+  const SplitMat s = split_shape(rows, K, form, side, tile);
   return (size_t)s.rows_pad * (size_t)s.nkc * (size_t)s.chunks * 16;
 }
 
 SplitMat launch_split(int rows, int K, const cplx* src, i64 sR, i64 sK, int conj, void* dst, int form, int side,
-                      hipStream_t st) {
+                      hipStream_t st, int tile) {
   REQUIRE(rows > 0 && K > 0, CCLR_EINVAL, "split: empty operand");
-  SplitMat s = split_shape(rows, K, form, side);
+  SplitMat s = split_shape(rows, K, form, side, tile);
   s.p = dst;
   if (form == F32_G3) {
     const i64 units = (i64)s.rows_pad * s.nkc * 4;
@@ -516,25 +599,101 @@ SplitMat launch_split(int rows, int K, const cplx* src, i64 sR, i64 sK, int conj
   return s;
 }
 
+SplitPlan split_plan_for(int M, int N, int K, int form, int bm, int cutters) {
+  SplitPlan p;
+  p.bm = bm;
+  p.tm = (M + bm - 1) / bm;
+  p.nk = split_shape(1, K, form, 0).nkc;
+  p.tiles = (i64)p.tm * ((N + TN - 1) / TN);
+  constexpr int G = 256;
+  const i64 rounds = p.tiles / G, rest = p.tiles % G;
+  p.whole = p.tiles;
+  p.grid = (int)std::min<i64>(p.tiles, G);
+  const i64 c = std::min<i64>(cutters, rest * p.nk / 4);  // runs of at least four steps
+  if (c > rest) {
+    p.whole = rounds * G;
+    p.cutters = (int)c;
+    p.grid = rounds ? G : (int)c;
+  }
+  return p;
+}
+
+// Estimated time in us of a plan: the k steps of the busiest workgroup (low:
+// few compute units at work, full: all of them and their traffic), each whole
+// tile's stores, and for cut tiles the partial sums, written and read at
+// 4 TB/s.  Measured against it on one MI355X, X3, us (tile rows, cut or whole):
+// 264x4005x4005 96 cut 97 (est. 97), 128 cut 121 (121), 96 whole 165 (166), 128
+// whole 213 (215); 4320x1080x1080 128 cut 121 (124), 96 whole 123 (126), 128
+// whole 150 (146); 2400x800x800 96 whole 45 (47), 64 cut 53 (56).
+static double split_cost(const SplitPlan& p, int form) {
+  // us per k step with 128, 96 and 64 rows
+  static const double low[3][3] = {{1.5, 1.15, 0.9}, {1.05, 0.84, 0.74}, {3.2, 2.55, 1.68}};
+  static const double full[3][3] = {{2.0, 1.6, 1.37}, {1.4, 1.18, 1.0}, {3.2, 2.55, 1.68}};
+  const int r = p.bm == 128 ? 0 : p.bm == 96 ? 1 : 2;
+  const double lo = low[form][r], hi = full[form][r], tile = p.bm * TN / 4e6;  // us of one byte per element
+  const i64 rounds = p.whole / 256, last = p.whole % 256;
+  double t = (double)rounds * (p.nk * hi + 2.0 + 256 * 16 * tile);
+  if (last) t += p.nk * (lo + (hi - lo) * (double)last / 256) + 2.0 + (double)last * 16 * tile;
+  if (p.cutters) {
+    const double rest = (double)(p.tiles - p.whole);
+    t += rest * p.nk / p.cutters * hi + 4.0 + (p.cutters + rest) * 16 * tile;
+  }
+  return t;
+}
+
+SplitPlan split_plan(int M, int N, int K, int form, bool room) {
+  REQUIRE(split_form_valid(form), CCLR_EINVAL, "split: unknown form");
+  SplitPlan best;
+  double t = 1e300;
+  for (int bm : {128, 96, 64})
+    for (int cutters : {0, 256}) {
+      if (cutters && !room) continue;
+      const SplitPlan p = split_plan_for(M, N, K, form, bm, cutters);
+      const double tp = split_cost(p, form);
+      if (tp < t) best = p, t = tp;
+    }
+  return best;
+}
+
+size_t split_workspace(const SplitPlan& p) { return sizeof(float2) * 2 * (size_t)p.cutters * p.bm * TN; }
+
+namespace {
+template <int BM>
+void launch_bm(const SplitMat& A, const SplitMat& B, cplx* C, i64 sCm, i64 sCn, double ar, double ai, int beta,
+               const SplitPlan& p, float2* W, hipStream_t st) {
+  const dim3 grid((unsigned)p.grid), block(512);
+  const u4v *a = (const u4v*)A.p, *b = (const u4v*)B.p;
+  if (A.form == F32_G3)
+    hipLaunchKernelGGL(k_cgemm_f32s<BM>, grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows, B.rows, C, sCm, sCn,
+                       ar, ai, beta, p, W);
+  else if (A.form == BF16_X2)
+    hipLaunchKernelGGL((k_cgemm_bf16s<BF16_X2, BM>), grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows, B.rows,
+                       C, sCm, sCn, ar, ai, beta, p, W);
+  else
+    hipLaunchKernelGGL((k_cgemm_bf16s<BF16_X3, BM>), grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows, B.rows,
+                       C, sCm, sCn, ar, ai, beta, p, W);
+}
+}  // namespace
+
 void launch_split_gemm(const SplitMat& A, const SplitMat& B, cplx* C, i64 sCm, i64 sCn, double ar, double ai,
-                       int beta, hipStream_t st) {
+                       int beta, const SplitPlan& p, void* W, hipStream_t st) {
   REQUIRE(A.p && B.p, CCLR_EINVAL, "split GEMM: operand not split");
   REQUIRE(A.form == B.form && A.side == 0 && B.side == 1, CCLR_EINVAL, "split GEMM: operands of different forms");
   REQUIRE(A.K == B.K && A.nkc == B.nkc && A.nkc > 0, CCLR_EINVAL, "split GEMM: operands differ in K");
-  const int Mt = A.rows_pad / TM, Nt = B.rows_pad / TM;
-  const i64 T = (i64)Mt * Nt;
-  REQUIRE(T < (i64)1 << 30, CCLR_EINVAL, "split GEMM: too many tiles");
-  const i64 grid = (T + 7) / 8 * 8;
-  if (A.form == F32_G3)
-    hipLaunchKernelGGL(k_cgemm_f32s, dim3((unsigned)grid), dim3(512), 0, st, (const u4v*)A.p, (const u4v*)B.p,
-                       A.rows_pad, B.rows_pad, A.nkc, A.rows, B.rows, C, sCm, sCn, ar, ai, beta, Mt, (int)T);
-  else if (A.form == BF16_X2)
-    hipLaunchKernelGGL((k_cgemm_bf16s<BF16_X2>), dim3((unsigned)grid), dim3(512), 0, st, (const u4v*)A.p,
-                       (const u4v*)B.p, A.rows_pad, B.rows_pad, A.nkc, A.rows, B.rows, C, sCm, sCn, ar, ai, beta, Mt,
-                       (int)T);
-  else
-    hipLaunchKernelGGL((k_cgemm_bf16s<BF16_X3>), dim3((unsigned)grid), dim3(512), 0, st, (const u4v*)A.p,
-                       (const u4v*)B.p, A.rows_pad, B.rows_pad, A.nkc, A.rows, B.rows, C, sCm, sCn, ar, ai, beta, Mt,
-                       (int)T);
+  REQUIRE(A.rows_pad == p.tm * p.bm && p.tiles == (i64)p.tm * (B.rows_pad / TN) && B.rows_pad % TN == 0 &&
+              p.nk == A.nkc && (p.cutters == 0 || W),
+          CCLR_EINVAL, "split GEMM: operands and plan differ");
+  REQUIRE(p.tiles < (i64)1 << 30, CCLR_EINVAL, "split GEMM: too many tiles");
+  switch (p.bm) {
+    case 64: launch_bm<64>(A, B, C, sCm, sCn, ar, ai, beta, p, (float2*)W, st); break;
+    case 96: launch_bm<96>(A, B, C, sCm, sCn, ar, ai, beta, p, (float2*)W, st); break;
+    case 128: launch_bm<128>(A, B, C, sCm, sCn, ar, ai, beta, p, (float2*)W, st); break;
+    default: throw CclrError(CCLR_EINVAL, "split GEMM: no such tile");
+  }
   HIPCHK(hipGetLastError());
+  if (p.cutters > 0) {
+    hipLaunchKernelGGL(k_split_join, dim3((unsigned)(p.tiles - p.whole), p.bm * TN / 256), dim3(256), 0, st, A.rows,
+                       B.rows, C, sCm, sCn, ar, ai, beta, p, (const float2*)W);
+    HIPCHK(hipGetLastError());
+  }
 }

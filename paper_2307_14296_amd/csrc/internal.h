@@ -172,14 +172,27 @@ struct SplitMat {
   int form = 0, side = 0, nplanes = 0, chunks = 0;
   int planes[4] = {0, 0, 0, 0};
 };
-SplitMat split_shape(int rows, int K, int form, int side);
-size_t split_bytes(int rows, int K, int form, int side);
+SplitMat split_shape(int rows, int K, int form, int side, int tile = 128);
+size_t split_bytes(int rows, int K, int form, int side, int tile = 128);
 // dst <- split of op(src)[r][k] = src[r*sR + k*sK] (conjugated if conj)
 SplitMat launch_split(int rows, int K, const cplx* src, i64 sR, i64 sK, int conj, void* dst, int form, int side,
-                      hipStream_t s);
-// C[m][n] (+)= alpha * sum_k A[m][k] B[n][k] on operands split for one form, FP32 accumulation
+                      hipStream_t s, int tile = 128);
+// How a product of split operands runs: tiles of bm x 128 (the A side's rows
+// padded to bm), `whole` of them dealt whole and the k steps of the rest cut
+// into `cutters` equal runs (0: none); cut tiles need split_workspace bytes.
+struct SplitPlan {
+  int bm = 128, tm = 0, nk = 0, grid = 0, cutters = 0;
+  i64 tiles = 0, whole = 0;
+};
+SplitPlan split_plan_for(int M, int N, int K, int form, int bm, int cutters);
+// the plan of least estimated time; room: cut tiles are allowed
+SplitPlan split_plan(int M, int N, int K, int form, bool room);
+size_t split_workspace(const SplitPlan& p);
+void split_product(cclr_ctx* c, const GemmArgs& g, int form, const SplitMat& B);
+// C[m][n] (+)= alpha * sum_k A[m][k] B[n][k] on operands split for one form,
+// FP32 accumulation (partial sums of cut tiles in FP32, added in FP64)
 void launch_split_gemm(const SplitMat& A, const SplitMat& B, cplx* C, i64 sCm, i64 sCn, double ar, double ai,
-                       int beta, hipStream_t s);
+                       int beta, const SplitPlan& p, void* W, hipStream_t s);
 // Eigenpairs of a small dense complex matrix on the GPU (one workgroup):
 // H(i, j) = Hu[j ld + i] for i <= j and Hl[i ld + j] for i > j, n <= kSmallEigMax;
 // work holds small_eig_work_elems(n) elements.  Writes theta[r] and the unit-norm

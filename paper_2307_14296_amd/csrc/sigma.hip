@@ -59,11 +59,7 @@ void op_gemm(cclr_ctx* c, const GemmArgs& g, int which) {
     W = launch_split(g.N, g.K, g.B, g.sBn, g.sBk, g.conjB, c->wsplit[which].p, form, 1, c->stream);
   }
   REQUIRE(W.rows == g.N && W.K == g.K, CCLR_EINVAL, "split operator has another shape");
-  Arena::Mark mk = c->arena.mark();
-  void* ws = c->arena.get(split_bytes(g.M, g.K, form, 0));
-  const SplitMat A = launch_split(g.M, g.K, g.A, g.sAm, g.sAk, g.conjA, ws, form, 0, c->stream);
-  launch_split_gemm(A, W, g.C, g.sCm, g.sCn, g.ar, g.ai, g.beta, c->stream);
-  c->arena.reset(mk);
+  split_product(c, g, form, W);
 }
 
 // Ring term  Z[(k,i,a),(j,b)] = sum_(m,e) R[(k,i,a),(m,e)] W[(m,e),(j,b)]  written into the
