@@ -5,8 +5,8 @@
 // as 16 x 4 x 480 then is one workgroup that waits for memory 30 times in a
 // row.  Here the waves of a workgroup share one tile of 16 FM x 16 FN and
 // split its K loop: each loads its operand fragments straight into the
-// registers of v_mfma_f64_16x16x4_f64 (a lane's four steps of a 16-deep K tile
-// are four consecutive k, 64 contiguous bytes where k has unit stride), the
+// registers of v_mfma_f64_16x16x4_f64 (a load takes 16 rows and four
+// consecutive k, 64 contiguous bytes of each row where k has unit stride), the
 // next tile's loads in flight while the MFMAs of the current one run, and the
 // waves' sums are added in LDS at the end.  A long reduction is cut over
 // workgroups as well; the partial sums go to a workspace that
@@ -14,51 +14,70 @@
 //
 // Bound by the latency of a few loads per wave (3-4 us a launch up to K = 96,
 // 8 us at 16x4x480; 44 us on a 64x32 tile) and, for long reductions, by the
-// operands' bytes: 12x100x120000 54 us = 3.6 TB/s (585 us on the vector
-// kernel with its serial chunk sums).
+// operands' bytes, which the tiles of a chunk read through one XCD's L2:
+// 12x100x120000 43 us = 5.4 TB/s (585 us on the vector kernel with its serial
+// chunk sums), 90x48x48060 43, 80x30x31600 26, 130x10x83850 42, 20x200x38000 in
+// a batch of 3 126 (83, 36, 58 and 188 with chunks over all XCDs, 516 to 525
+// workgroups for 512 places, and loads of 16 bytes out of 64 per row).
 #include <algorithm>
 
 #include "gemm_dma.h"
 
 namespace {
 template <int FM, int FN, int NW>
-__global__ __launch_bounds__(64 * NW) void k_zgemm_frag(GemmArgs g, int tm, int kc, int S, cplx* __restrict__ W) {
+__global__ __launch_bounds__(64 * NW, (FM * FN == 4 ? 2 : 4)) void k_zgemm_frag(GemmArgs g, int tm, int nt, int kc, int S,
+                                                          int xcd, cplx* __restrict__ W) {
   constexpr int BM = 16 * FM, BN = 16 * FN;
+  constexpr int U = FM * FN >= 2 ? 2 : 4, KT = 4 * U;  // MFMA steps and depth of a K tile
   __shared__ cplx red[NW > 1 ? NW : 1][NW > 1 ? BM * BN : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rr = lane & 15, gq = lane >> 4;
-  const int m0 = (blockIdx.x % tm) * BM, n0 = (blockIdx.x / tm) * BN, q = blockIdx.y;
-  const i64 bz = blockIdx.z;
+  // xcd: all tiles of a chunk run on one XCD (workgroups are dealt to the 8
+  // XCDs round-robin), which then reads the chunk's operands into its L2 once
+  int t = blockIdx.x, q = 0;
+  if (xcd) {
+    const int l = t >> 3, c = l / nt;
+    q = 8 * c + (t & 7);
+    t = l - c * nt;
+    if (q >= S) return;
+  } else if (S > 1) {
+    q = t / nt;
+    t -= q * nt;
+  }
+  const int m0 = (t % tm) * BM, n0 = (t / tm) * BN;
+  const i64 bz = blockIdx.y;
   const int k0 = q * kc, k1 = min(g.K, k0 + kc);
   const unsigned sgnA = g.conjA ? 0x80000000u : 0u, sgnB = g.conjB ? 0x80000000u : 0u;
   // rows past the operand read its last row; their outputs are not stored
   const cplx *pa[FM], *pb[FN];
 #pragma unroll
-  for (int i = 0; i < FM; ++i) pa[i] = g.A + boff(g, bz, g.sAb, g.sAb2) + (i64)min(m0 + 16 * i + rr, g.M - 1) * g.sAm;
+  for (int i = 0; i < FM; ++i)
+    pa[i] = g.A + boff(g, bz, g.sAb, g.sAb2) + (i64)min(m0 + 16 * i + rr, g.M - 1) * g.sAm + gq * g.sAk;
 #pragma unroll
-  for (int j = 0; j < FN; ++j) pb[j] = g.B + boff(g, bz, g.sBb, g.sBb2) + (i64)min(n0 + 16 * j + rr, g.N - 1) * g.sBn;
+  for (int j = 0; j < FN; ++j)
+    pb[j] = g.B + boff(g, bz, g.sBb, g.sBb2) + (i64)min(n0 + 16 * j + rr, g.N - 1) * g.sBn + gq * g.sBk;
   d4 cr[FM][FN], ci[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int j = 0; j < FN; ++j) cr[i][j] = ci[i][j] = d4{0, 0, 0, 0};
-  cplx fa[2][4][FM], fb[2][4][FN];
-  // this lane's elements of the 16-deep K tile at kb; zero beyond the chunk, in both operands
+  cplx fa[2][U][FM], fb[2][U][FN];
+  // this lane's elements of the K tile at kb; zero beyond the chunk, in both operands
   auto load = [&](int kb, int s) {
-    if (kb + 16 <= k1) {
+    if (kb + KT <= k1) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = kb + 4 * gq + u;
+      for (int u = 0; u < U; ++u) {
+        const i64 oa = (i64)(kb + 4 * u) * g.sAk, ob = (i64)(kb + 4 * u) * g.sBk;
 #pragma unroll
-        for (int i = 0; i < FM; ++i) fa[s][u][i] = pa[i][(i64)k * g.sAk];
+        for (int i = 0; i < FM; ++i) fa[s][u][i] = pa[i][oa];
 #pragma unroll
-        for (int j = 0; j < FN; ++j) fb[s][u][j] = pb[j][(i64)k * g.sBk];
+        for (int j = 0; j < FN; ++j) fb[s][u][j] = pb[j][ob];
       }
     } else {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = kb + 4 * gq + u;
+      for (int u = 0; u < U; ++u) {
+        const int k = kb + 4 * u + gq;
         const bool in = k < k1;
-        const i64 kk = in ? k : k1 - 1;
+        const i64 kk = (in ? k : k1 - 1) - gq;
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
           const cplx x = pa[i][kk * g.sAk];
@@ -74,7 +93,7 @@ __global__ __launch_bounds__(64 * NW) void k_zgemm_frag(GemmArgs g, int tm, int 
   };
   auto mfma = [&](int s) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       cplx a[FM], b[FN];
 #pragma unroll
       for (int i = 0; i < FM; ++i) a[i] = flip_im(fa[s][u][i], sgnA);
@@ -96,17 +115,17 @@ __global__ __launch_bounds__(64 * NW) void k_zgemm_frag(GemmArgs g, int tm, int 
         }
     }
   };
-  int kb = k0 + 16 * wave;
+  int kb = k0 + KT * wave;
   if (kb < k1) {
     load(kb, 0);
     for (;;) {
-      if (kb + 16 * NW < k1) load(kb + 16 * NW, 1);
+      if (kb + KT * NW < k1) load(kb + KT * NW, 1);
       mfma(0);
-      kb += 16 * NW;
+      kb += KT * NW;
       if (kb >= k1) break;
-      if (kb + 16 * NW < k1) load(kb + 16 * NW, 0);
+      if (kb + KT * NW < k1) load(kb + KT * NW, 0);
       mfma(1);
-      kb += 16 * NW;
+      kb += KT * NW;
       if (kb >= k1) break;
     }
   }
@@ -228,13 +247,37 @@ FragPlan frag_plan(const GemmArgs& g) {
   const auto blocks = [&](int fm, int fn) {
     return (i64)((g.M + 16 * fm - 1) / (16 * fm)) * ((g.N + 16 * fn - 1) / (16 * fn)) * g.batch;
   };
+  const int kt = (g.K + 15) / 16;
+  // Long reductions are cut into chunks that fill each XCD once: 128 workgroups
+  // of four waves on each, 64 with 32 x 32 tiles (registers).  Ten more of 1000
+  // took a second round: 20x200x38000, batch 3 121 us with 24 chunks, 173 with
+  // 25.  Tile height and width by the rate their operand reads, out of L2, were
+  // measured at (16-row panels over 9, 7.5 and 6.5 TB/s): 90x48x48060 43 us on
+  // 32 x 16, 53 on 32 x 32; 32x120x114240 93 and 84.
+  if (kt >= 32 && blocks(1, 1) <= 512) {
+    static const struct { int fm, fn, slots; double cost; } shapes[] = {
+        {1, 1, 1024, 0.222}, {2, 1, 1024, 0.4}, {1, 2, 1024, 0.4}, {2, 2, 512, 0.61}};
+    double best = 1e300;
+    for (const auto& x : shapes) {
+      const i64 nb = blocks(x.fm, x.fn), per = x.slots / 8 / nb;
+      const i64 S = std::min<i64>(per ? 8 * per : x.slots / nb, kt / 8);
+      if (S < 2 || (double)nb * x.cost >= best) continue;
+      best = (double)nb * x.cost;
+      p.fm = x.fm, p.fn = x.fn, p.nw = 4;
+      p.xcd = S >= 8 && (S % 8 == 0 || S >= 64);
+      p.kc = (int)(((g.K + S - 1) / S + 15) / 16 * 16);
+    }
+    if (p.kc > 0) {
+      p.S = (g.K + p.kc - 1) / p.kc;
+      return p;
+    }
+  }
   // larger tiles read each operand fewer times, once they alone keep the compute units busy
   const i64 work = blocks(1, 1) * ((g.K + 255) / 256);
   p.fm = p.fn = 1;
   if (g.M > 16 && work >= 1024) p.fm = 2;
   if (g.N > 16 && work >= 2048) p.fn = 2;
   const i64 nb = blocks(p.fm, p.fn);
-  const int kt = (g.K + 15) / 16;
   p.nw = kt <= 1 ? 1 : (p.fm * p.fn == 1 && kt > 4 ? 8 : 4);
   // cut the reduction until there are about 512 workgroups, each wave with at least 4 K tiles
   i64 S = std::min<i64>((512 + nb - 1) / nb, kt / (4 * p.nw));
@@ -250,8 +293,10 @@ void launch_zgemm_frag(const GemmArgs& g, const FragPlan& p, cplx* W, hipStream_
   REQUIRE(g.M >= 1 && g.N >= 1 && g.K >= 1 && g.batch >= 1 && g.batch < 65536 && g.kchunk == 0 && p.S >= 1 &&
               p.S < 65536 && (p.S == 1 || W) && (i64)p.kc * p.S >= g.K && (i64)tm * tn < (1ll << 31),
           CCLR_EINVAL, "small product: arguments outside the kernel's contract");
-  const dim3 grid((unsigned)(tm * tn), (unsigned)p.S, (unsigned)g.batch);
-#define FRAG(FM, FN, NW) hipLaunchKernelGGL((k_zgemm_frag<FM, FN, NW>), grid, dim3(64 * NW), 0, s, g, tm, p.kc, p.S, W)
+  const i64 wgs = (i64)tm * tn * (p.xcd ? (p.S + 7) / 8 * 8 : p.S);
+  REQUIRE(wgs < (1ll << 31), CCLR_EINVAL, "small product: too many workgroups");
+  const dim3 grid((unsigned)wgs, (unsigned)g.batch);
+#define FRAG(FM, FN, NW) hipLaunchKernelGGL((k_zgemm_frag<FM, FN, NW>), grid, dim3(64 * NW), 0, s, g, tm, tm * tn, p.kc, p.S, p.xcd, W)
   if (p.fm == 1 && p.fn == 1) {
     if (p.nw == 1) FRAG(1, 1, 1);
     else if (p.nw == 4) FRAG(1, 1, 4);

@@ -233,9 +233,9 @@ size_t sk_workspace(const SkPlan& p);
 void launch_zgemm_sk(const GemmArgs& g, const SkPlan& p, cplx* W, hipStream_t s);
 // small FP64 products (gemm_frag.hip): tiles of 16 fm x 16 fn blocks, the K
 // loop shared by the nw waves of a workgroup and cut in S chunks of kc; S > 1
-// needs a workspace of batch*S*M*N elements
+// needs a workspace of batch*S*M*N elements; xcd: the tiles of a chunk on one XCD
 struct FragPlan {
-  int fm, fn, nw, kc, S;
+  int fm, fn, nw, kc, S, xcd;
 };
 FragPlan frag_plan(const GemmArgs& g);
 void launch_zgemm_frag(const GemmArgs& g, const FragPlan& p, cplx* W, hipStream_t s);
