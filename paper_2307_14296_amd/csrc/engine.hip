@@ -814,16 +814,19 @@ static void run_gemm_form(cclr_ctx* c, const GemmArgs& g0, int& form) {
       Arena::Mark mk = c->arena.mark();
       GemmArgs h = g0;
       const i64 s2b = n2 > 1 ? 1 : 0;  // the second batch level's stride factor in the copies
-      if (ca) {
-        cplx* t = (cplx*)c->arena.get(sizeof(cplx) * (size_t)(g0.batch * M * K));
-        copy4(c, {n1, n2, M, K}, t, {n2 * M * K, M * K, K, 1}, g0.A, {g0.sAb, s2b * g0.sAb2, g0.sAm, g0.sAk}, false);
-        h.A = t; h.sAb = n2 * M * K; h.sAb2 = M * K; h.sAm = K; h.sAk = 1;
-      }
-      if (cb) {
-        cplx* t = (cplx*)c->arena.get(sizeof(cplx) * (size_t)(g0.batch * K * N));
-        copy4(c, {n1, n2, K, N}, t, {n2 * K * N, K * N, N, 1}, g0.B, {g0.sBb, s2b * g0.sBb2, g0.sBk, g0.sBn}, false);
-        h.B = t; h.sBb = n2 * K * N; h.sBb2 = K * N; h.sBk = N; h.sBn = 1;
-      }
+      // a batch level that an input does not vary over (stride 0) is copied once
+      auto outermost = [&](const cplx*& X, i64& s1, i64& s2, i64& sr, i64& sq, i64 r, i64 q) {
+        const i64 d1 = s1 == 0 ? 1 : n1, d2 = s2b * s2 == 0 ? 1 : n2;
+        cplx* t = (cplx*)c->arena.get(sizeof(cplx) * (size_t)(d1 * d2 * r * q));
+        copy4(c, {d1, d2, r, q}, t, {d2 * r * q, r * q, q, 1}, X, {s1, s2b * s2, sr, sq}, false);
+        X = t;
+        s1 = s1 == 0 ? 0 : d2 * r * q;
+        s2 = s2b * s2 == 0 ? 0 : r * q;
+        sr = q;
+        sq = 1;
+      };
+      if (ca) outermost(h.A, h.sAb, h.sAb2, h.sAm, h.sAk, M, K);
+      if (cb) outermost(h.B, h.sBb, h.sBb2, h.sBk, h.sBn, K, N);
       if (cc) {
         cplx* t = (cplx*)c->arena.get(sizeof(cplx) * (size_t)(g0.batch * M * N));
         h.C = t; h.sCb = n2 * M * N; h.sCb2 = M * N; h.sCm = N; h.sCn = 1; h.beta = 0;

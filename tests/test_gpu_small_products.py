@@ -168,3 +168,25 @@ def test_even_split_without_room():
         product(L, ctx, 300, 5000, 300, 1, False, False, False, 0, 0, 1, -8)
     finally:
         cc.cclr_destroy(ctx)
+
+
+@pytest.mark.parametrize("shared", [1, 2])
+def test_batch_innermost_input_shared_over_a_level(lib, shared):
+    """An input whose unit stride is one batch index and which does not vary
+    over the other (stride 0), in either order of the levels."""
+    L, ctx = lib
+    M, N, K, nv, ns = 90, 40, 70, 24, 9  # nv entries of A along its unit stride, shared by ns products each
+    rng = np.random.default_rng(shared)
+    A, C0 = crand(rng, M, K, nv), crand(rng, nv, ns, M, N)
+    B = crand(rng, nv, ns, K, N)
+    if shared == 1:  # the shared level is the first
+        B, C0 = B.transpose(1, 0, 2, 3).copy(), C0.transpose(1, 0, 2, 3).copy()
+    nb1, nb2 = (ns, nv) if shared == 1 else (nv, ns)
+    Ad, Bd, Cd = dev(A), dev(B), dev(C0)
+    sA1, sA2 = (0, 1) if shared == 1 else (1, 0)
+    rc = L.cclr_dbg_run_gemm_b2(ctx, M, N, K, nb1, nb2, Ad.data_ptr(), sA1, sA2, K * nv, nv, Bd.data_ptr(),
+                                nb2 * K * N, K * N, N, 1, Cd.data_ptr(), nb2 * M * N, M * N, N, 1, 0.5, 0.25, 1)
+    assert rc == 0
+    Ab = A.transpose(2, 0, 1)
+    Ab = Ab[None] if shared == 1 else Ab[:, None]
+    check(Cd.cpu().numpy(), Ab, B, C0, 0.5 + 0.25j, K)
