@@ -39,10 +39,7 @@ void build_intermediates(cclr_ctx* c) {
   contract(c, one, t1, "ia", t1, "jb", tau, "ijab");
   contract(c, mone, t1, "ib", t1, "ja", tau, "ijab");
 
-  auto alloc = [&](DevBuf& b, i64 n) {
-    b.alloc(c, sizeof(cplx) * (size_t)n);
-    launch_fill(b.c(), n, cx(0.0), c->stream);
-  };
+  auto alloc = [&](DevBuf& b, i64 n) { b.alloc(c, sizeof(cplx) * (size_t)n); };
   alloc(c->Foo, o * o);
   alloc(c->Fvv, v * v);
   alloc(c->Fov, o * v);
@@ -61,20 +58,20 @@ void build_intermediates(cclr_ctx* c) {
   Ten Voovv = Vblk(c, "oovv");
 
   // F^i_m = f^i_m + f^i_e t^e_m + V^in_me t^e_n + 1/2 V^in_ef tau^ef_mn
-  tcopy(c, Foo, "im", fblk(c, "oo"), "im", one);
+  tcopy(c, Foo, "im", fblk(c, "oo"), "im", one, false);
   contract(c, one, fblk(c, "ov"), "ie", t1, "me", Foo, "im");
   contract(c, one, Vblk(c, "ooov"), "inme", t1, "ne", Foo, "im");
   contract(c, half, Voovv, "inef", tau, "mnef", Foo, "im");
   // F^a_e = f^a_e - f^m_e t^a_m + V^am_ef t^f_m - 1/2 V^mn_ef tau^af_mn
-  tcopy(c, Fvv, "ae", fblk(c, "vv"), "ae", one);
+  tcopy(c, Fvv, "ae", fblk(c, "vv"), "ae", one, false);
   contract(c, mone, fblk(c, "ov"), "me", t1, "ma", Fvv, "ae");
   contract(c, one, Vblk(c, "vovv"), "amef", t1, "mf", Fvv, "ae");
   contract(c, mhalf, Voovv, "mnef", tau, "mnaf", Fvv, "ae");
   // F^m_e = f^m_e + V^mn_ef t^f_n
-  tcopy(c, Fov, "me", fblk(c, "ov"), "me", one);
+  tcopy(c, Fov, "me", fblk(c, "ov"), "me", one, false);
   contract(c, one, Voovv, "mnef", t1, "nf", Fov, "me");
   // W^ij_mn = V^ij_mn + P(mn) V^ij_en t^e_m + 1/2 V^ij_ef tau^ef_mn
-  tcopy(c, Woooo, "ijmn", Vblk(c, "oooo"), "ijmn", one);
+  tcopy(c, Woooo, "ijmn", Vblk(c, "oooo"), "ijmn", one, false);
   {
     Ten w = tmp(c, {o, o, o, o});
     contract(c, one, Vblk(c, "oovo"), "ijen", t1, "me", w, "ijmn", false);
@@ -83,7 +80,7 @@ void build_intermediates(cclr_ctx* c) {
   }
   contract(c, half, Voovv, "ijef", tau, "mnef", Woooo, "ijmn");
   // W^mb_ej = V^mb_ej + V^mb_ef t^f_j - V^mn_ej t^b_n - V^mn_ef (t^fb_jn + t^f_j t^b_n)
-  tcopy(c, Wovvo, "mbej", Vblk(c, "ovvo"), "mbej", one);
+  tcopy(c, Wovvo, "mbej", Vblk(c, "ovvo"), "mbej", one, false);
   contract(c, one, Vblk(c, "ovvv"), "mbef", t1, "jf", Wovvo, "mbej");
   contract(c, mone, Vblk(c, "oovo"), "mnej", t1, "nb", Wovvo, "mbej");
   {
@@ -93,13 +90,13 @@ void build_intermediates(cclr_ctx* c) {
     contract(c, mone, Voovv, "mnef", w, "jnfb", Wovvo, "mbej");
   }
   // barW^mb_ej = V^mb_ej - V^mn_ef t^bf_nj
-  tcopy(c, Wbar, "mbej", Vblk(c, "ovvo"), "mbej", one);
+  tcopy(c, Wbar, "mbej", Vblk(c, "ovvo"), "mbej", one, false);
   contract(c, mone, Voovv, "mnef", t2, "njbf", Wbar, "mbej");
   // W^mn_ie = V^mn_ie + t^f_i V^mn_fe
-  tcopy(c, Wooov, "mnie", Vblk(c, "ooov"), "mnie", one);
+  tcopy(c, Wooov, "mnie", Vblk(c, "ooov"), "mnie", one, false);
   contract(c, one, t1, "if", Voovv, "mnfe", Wooov, "mnie");
   // W^am_ef = V^am_ef - V^nm_ef t^a_n
-  tcopy(c, Wvovv, "amef", Vblk(c, "vovv"), "amef", one);
+  tcopy(c, Wvovv, "amef", Vblk(c, "vovv"), "amef", one, false);
   contract(c, mone, Voovv, "nmef", t1, "na", Wvovv, "amef");
   // W^ef_ab = V^ef_ab - P(ef) V^mf_ab t^e_m + 1/2 V^mn_ab tau^ef_mn, packed: Wp[EF][AB]
   {
@@ -139,7 +136,7 @@ void build_intermediates(cclr_ctx* c) {
   }
   // W^ie_mn = V^ie_mn - F^i_f t^ef_mn - W^io_mn t^e_o + 1/2 V^ie_fg tau^fg_mn
   //          + P(mn) barW^ie_fn t^f_m + P(mn) V^io_mf t^ef_no
-  tcopy(c, Wovoo, "iemn", Vblk(c, "ovoo"), "iemn", one);
+  tcopy(c, Wovoo, "iemn", Vblk(c, "ovoo"), "iemn", one, false);
   contract(c, mone, Fov, "if", t2, "mnef", Wovoo, "iemn");
   contract(c, mone, Woooo, "iomn", t1, "oe", Wovoo, "iemn");
   contract(c, half, Vblk(c, "ovvv"), "iefg", tau, "mnfg", Wovoo, "iemn");
@@ -152,7 +149,7 @@ void build_intermediates(cclr_ctx* c) {
   }
   // W^ef_am = V^ef_am - P(ef) V^en_ag t^gf_mn + W^ef_ag t^g_m + F^n_a t^ef_mn
   //          + 1/2 V^no_am tau^ef_no - P(ef) barW^nf_am t^e_n
-  tcopy(c, Wvvvo, "efam", Vblk(c, "vvvo"), "efam", one);
+  tcopy(c, Wvvvo, "efam", Vblk(c, "vvvo"), "efam", one, false);
   // W^ef_ag t^g_m is formed from the pieces of W^ef_ag (no unpacked W^ef_ab):
   //   V^ef_ag t^g_m - P(ef) t^e_n (V^nf_ag t^g_m) + 1/2 tau^ef_no (V^no_ag t^g_m)
   {
