@@ -627,7 +627,6 @@ void split_product(cclr_ctx* c, const GemmArgs& g, int form, const SplitMat& B) 
 }
 
 static void run_gemm_form(cclr_ctx* c, const GemmArgs& g, int& form);
-static bool narrow_may_pay(int N);
 void run_gemm(cclr_ctx* c, const GemmArgs& g) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.K <= 0) return;
   int form = 0;
@@ -697,12 +696,13 @@ constexpr int kFormFrag = -7, kFormEven = -8;
 //    loads per workgroup: 16x4x480 9 against 44 (64x32 tiles), 93x31x465 9
 //    against 76 (128x32), 465x93x31 4 against 37 (vector ALU), 558x186x186 8
 //    against 34 (64x64); at 7128 (45x3160x45, batch 4) 22 against 12;
-//  * long reductions with one side at most 48 and at most 128 blocks, or at
-//    most 40 blocks: 10x40x31600 16 against 59, 130x10x83850 57 against 195,
-//    80x40x31600 44 against 80 (63 evenly split); above that the operands are
-//    read too often: 144x144x10000 75 against 54 evenly split.  Up to 4
-//    columns the vector kernels stay: 80x4x800, batch 80, 27 against 31, but
-//    800x4x800 13 against 9;
+//  * long reductions with at most 96 blocks, or at most 128 where one side is
+//    at most 48, or up to 14000 block tiles: 10x40x31600 13 against 59,
+//    130x10x83850 43 against 195, 80x80x3600, batch 3 29 against 43 (evenly
+//    split), 144x144x8100 44 against 47, 96x96x1000, batch 6 23 against 27;
+//    beyond, 90x90x5940, batch 4 (144 blocks) 59 against 52.  Up to 4 columns
+//    the vector kernels stay: 80x4x800, batch 80, 27 against 31, but 800x4x800
+//    13 against 9;
 //  * short reductions with one side at most 16: 83850x10x10 11 against 31,
 //    14400x16x16, batch 32, 39 against 52.
 // Outputs 17 to 32 wide with more than 128 blocks stay on the 32-column tiles.
@@ -712,7 +712,7 @@ static bool frag_may_pay(const GemmArgs& g) {
   const int lo = std::min(g.M, g.N);
   if (g.K > 32 && lo > 16 && lo <= 32 && f > 128) return false;
   if (f * kt <= 5120) return true;
-  if (g.K >= 512) return lo > 4 && ((lo <= 48 && f <= 128) || f <= 40);
+  if (g.K >= 512) return lo > 4 && ((lo <= 48 && f <= 128) || f <= 40 || (lo > 16 && (f <= 96 || f * kt <= 14000)));
   return g.K <= 32 && lo <= 16 && f < (i64(1) << 22);
 }
 

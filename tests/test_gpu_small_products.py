@@ -77,7 +77,8 @@ LAYOUTS = [(False, False, False, 0, 1, 0), (True, False, True, 1, 0, 1), (False,
 # rule; tiles of 32 x 16, 16 x 32 and 32 x 32; long reductions at their limits
 FRAG = [(1, 1, 1, 1), (16, 16, 16, 1), (17, 15, 17, 3), (4, 4, 480, 1), (33, 16, 33, 2), (16, 256, 4096, 1),
         (256, 320, 256, 1), (500, 40, 40, 1), (2, 3000, 31, 2), (48, 640, 601, 1), (80, 128, 5000, 1),
-        (10, 10, 70001, 1), (83850, 10, 10, 1), (9, 120, 20000, 2), (64, 64, 64, 16)]
+        (10, 10, 70001, 1), (83850, 10, 10, 1), (9, 120, 20000, 2), (64, 64, 64, 16), (128, 192, 3001, 1),
+        (200, 160, 1600, 1), (80, 80, 3600, 3), (40, 33, 513, 14)]
 
 
 @pytest.mark.parametrize("M,N,K,batch", FRAG)
@@ -111,8 +112,8 @@ def test_chunk_sums(lib, M, N, K, batch, form):
 # even split: every row count of the tile in both orientations (45, 66, 91,
 # 130, 180 rows against long sides), K tails and K of whole tiles, whole
 # rounds with a cut rest, fewer runs than workgroups, batches
-EVEN = [(45, 1000, 1030, 1), (1000, 66, 528, 1), (91, 700, 800, 1), (180, 513, 2047, 1), (130, 140, 9000, 1),
-        (1500, 1500, 300, 1), (65, 65, 2001, 2), (200, 200, 700, 3), (33, 2000, 900, 1), (500, 300, 260, 2)]
+EVEN = [(45, 1000, 1530, 1), (1000, 66, 728, 1), (91, 700, 900, 1), (180, 513, 2047, 1), (130, 190, 9000, 1),
+        (1500, 1500, 300, 1), (65, 65, 2401, 4), (200, 200, 700, 3), (33, 2000, 900, 1), (500, 300, 260, 2)]
 
 
 @pytest.mark.parametrize("M,N,K,batch", EVEN)
