@@ -278,21 +278,36 @@ __global__ __launch_bounds__(kT) void k_small_eig(int n, const cplx* __restrict_
 // shifted QR as above without vectors, so each rotation touches the active
 // window only.  out[2 r], out[2 r + 1]; zeros where m[r] < 1 or the iteration
 // did not converge.  In LDS up to kRitzLds, else in work [r][ld][ld + 1].
-// Bound by the latency of the rotations: 0.2 ms at m = 20 for any number of
-// matrices, where the host took 0.6 ms for each (4 ms at m = 37).
+// Bound by the latency of the rotations, which depend on one another.  A lane
+// owns a column while they act on rows, and a row while they act on columns:
+// the row (column) that two rotations share stays in its registers, the pair
+// that defines a rotation is read across lanes, and the subdiagonal is tested
+// by all lanes at once: three matrices of m = 20 in 0.53 ms, 37 in 1.46, 60 in
+// 3.4, copies included (0.63, 1.82 and 4.5 through LDS; the host took 0.6 ms
+// for each matrix of 20, 4 ms at 37).
+// x of one lane, the same for all
+__device__ __forceinline__ cplx lane_value(cplx x, int lane) {
+  auto pick = [lane](double v) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+  };
+  return make_double2(pick(x.x), pick(x.y));
+}
+
 constexpr int kRitzLds = 96;
 __global__ __launch_bounds__(kT) void k_ritz(const int* __restrict__ m, const cplx* __restrict__ G, int ld,
                                              cplx* __restrict__ work, double* __restrict__ out) {
-  __shared__ cplx T[kRitzLds * kRitzLds];
+  __shared__ cplx T[kRitzLds * (kRitzLds + 1)];
   __shared__ cplx cs[kSmallEigMax], sn[kSmallEigMax], vv[kSmallEigMax];
   const int r = blockIdx.x, t = threadIdx.x, n = m[r];
   if (t == 0) out[2 * r] = out[2 * r + 1] = 0.0;
   if (n < 1) return;
   cplx* A = n <= kRitzLds ? T : work + (i64)r * ld * (ld + 1);
+  const int lw = n <= kRitzLds ? n | 1 : n;  // odd: a column is spread over the banks
   const cplx* __restrict__ g = G + (i64)r * ld * ld;
-  for (int e = t; e < n * n; e += kT) A[e] = g[(i64)(e / n) * ld + e % n];
+  for (int e = t; e < n * n; e += kT) A[e / n * lw + e % n] = g[(i64)(e / n) * ld + e % n];
   __syncthreads();
-  auto h = [&](int i, int j) -> cplx& { return A[i * n + j]; };
+  auto h = [&](int i, int j) -> cplx& { return A[i * lw + j]; };
   // ---- Householder reduction
   for (int k = 0; k + 2 < n; ++k) {
     double s2 = 0.0;
@@ -316,29 +331,57 @@ __global__ __launch_bounds__(kT) void k_ritz(const int* __restrict__ m, const cp
     const double inv = 1.0 / sqrt(v2);
     for (int i = k + 1 + t; i < n; i += kT) vv[i] = cscale(vv[i], inv);
     __syncthreads();
+    // four entries are read before any is written: the loads do not wait for the stores
     for (int j = k + t; j < n; j += kT) {  // columns (those before k are reduced already)
       cplx s = cz(0.0);
 #pragma unroll 4
       for (int i = k + 1; i < n; ++i) s = cadd(s, cjmul(vv[i], h(i, j)));
-      for (int i = k + 1; i < n; ++i) h(i, j) = csub(h(i, j), cscale(cmul(vv[i], s), 2.0));
+      s = cscale(s, 2.0);
+      int i = k + 1;
+      for (; i + 3 < n; i += 4) {
+        cplx x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = csub(h(i + q, j), cmul(vv[i + q], s));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) h(i + q, j) = x[q];
+      }
+      for (; i < n; ++i) h(i, j) = csub(h(i, j), cmul(vv[i], s));
     }
     __syncthreads();
     for (int i = t; i < n; i += kT) {  // rows
       cplx s = cz(0.0);
 #pragma unroll 4
       for (int j = k + 1; j < n; ++j) s = cadd(s, cmul(h(i, j), vv[j]));
-      for (int j = k + 1; j < n; ++j) h(i, j) = csub(h(i, j), cscale(cmul(s, cconj(vv[j])), 2.0));
+      s = cscale(s, 2.0);
+      int j = k + 1;
+      for (; j + 3 < n; j += 4) {
+        cplx x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = csub(h(i, j + q), cmul(s, cconj(vv[j + q])));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) h(i, j + q) = x[q];
+      }
+      for (; j < n; ++j) h(i, j) = csub(h(i, j), cmul(s, cconj(vv[j])));
     }
     __syncthreads();
   }
   // ---- shifted QR on the active window [l, hi]
   const double eps = 2.220446049250313e-16;
+  constexpr int NS = (kSmallEigMax + kT - 1) / kT;  // columns (rows) t, t + 64 of a lane
+  const int ns = n > kT ? NS : 1;
   int hi = n - 1, iter = 0, total = 0;
   while (hi > 0) {
-    int l = hi;
-    for (; l > 0; --l) {
-      const double s = cabsv(h(l - 1, l - 1)) + cabsv(h(l, l));
-      if (cabsv(h(l, l - 1)) <= eps * (s > 0.0 ? s : 1.0)) break;
+    int l = 0;  // the last negligible subdiagonal entry of rows 1 .. hi
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+      const int k = t + q * kT;
+      bool small = false;
+      if (k >= 1 && k <= hi) {
+        const double s = cabsv(h(k - 1, k - 1)) + cabsv(h(k, k));
+        small = cabsv(h(k, k - 1)) <= eps * (s > 0.0 ? s : 1.0);
+      }
+      const unsigned long long any = __ballot(small);
+      if (any) l = q * kT + 63 - __clzll((long long)any);
     }
     if (l == hi) {  // one eigenvalue converged
       --hi;
@@ -358,27 +401,64 @@ __global__ __launch_bounds__(kT) void k_ritz(const int* __restrict__ m, const cp
     if (l > 0 && t == 0) h(l, l - 1) = cz(0.0);
     for (int k = l + t; k <= hi; k += kT) h(k, k) = csub(h(k, k), mu);
     __syncthreads();
-    for (int k = l; k < hi; ++k) {  // rotations from the left
-      const cplx x = h(k, k), y = h(k + 1, k);
-      const double q = sqrt(cnorm(x) + cnorm(y));
+    // rotations from the left: lane t holds row k of its columns in u, row k + 1 in w
+    cplx u[NS], w[NS];
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+      if (q < ns && t + q * kT <= hi) u[q] = h(l, t + q * kT), w[q] = h(l + 1, t + q * kT);
+      else u[q] = w[q] = cz(0.0);
+    for (int k = l; k < hi; ++k) {
+      cplx nx[NS];  // row k + 2, read while the rotation is formed
+#pragma unroll
+      for (int q = 0; q < NS; ++q) {
+        const int j = t + q * kT;
+        nx[q] = q < ns && j <= hi && k + 2 <= hi ? h(k + 2, j) : cz(0.0);
+      }
+      const int src = k & (kT - 1);
+      const bool second = NS > 1 && k >= kT;
+      const cplx x = lane_value(second ? u[NS - 1] : u[0], src), y = lane_value(second ? w[NS - 1] : w[0], src);
+      const double s2 = cnorm(x) + cnorm(y);
       cplx cc = cz(1.0), ss = cz(0.0);
-      if (q > 0.0) cc = cscale(x, 1.0 / q), ss = cscale(y, 1.0 / q);
-      __syncthreads();
+      if (s2 > 0.0) {
+        const double inv = rsqrt(s2);
+        cc = cscale(x, inv);
+        ss = cscale(y, inv);
+      }
       if (t == 0) cs[k - l] = cc, sn[k - l] = ss;
-      for (int j = k + t; j <= hi; j += kT) {
-        const cplx u = h(k, j), w = h(k + 1, j);
-        h(k, j) = cadd(cjmul(cc, u), cjmul(ss, w));
-        h(k + 1, j) = csub(cmul(cc, w), cmul(ss, u));
+#pragma unroll
+      for (int q = 0; q < NS; ++q) {
+        const int j = t + q * kT;
+        if (q < ns && j >= k && j <= hi) h(k, j) = cadd(cjmul(cc, u[q]), cjmul(ss, w[q]));
+        if (q < ns && j == k) h(k + 1, k) = cz(0.0);
+        u[q] = csub(cmul(cc, w[q]), cmul(ss, u[q]));
+        w[q] = nx[q];
       }
-      __syncthreads();
     }
-    for (int i = l + t; i <= hi; i += kT)  // and from the right, by rows
-      for (int k = (i > l + 1 ? i - 1 : l); k < hi; ++k) {
-        const cplx cc = cs[k - l], ss = sn[k - l];
-        const cplx u = h(i, k), w = h(i, k + 1);
-        h(i, k) = cadd(cmul(u, cc), cmul(w, ss));
-        h(i, k + 1) = csub(cmul(w, cconj(cc)), cmul(u, cconj(ss)));
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+      if (q < ns && t + q * kT == hi) h(hi, hi) = u[q];
+    __syncthreads();
+    // and from the right: lane t holds column k of its rows in u; rotation k acts on rows l .. k + 1
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+      const int i = t + q * kT;
+      if (q >= ns || i < l || i > hi) continue;
+      cplx v = h(i, l), z = h(i, l + 1), cc = cs[0], ss = sn[0];
+      for (int k = l; k < hi; ++k) {
+        const int kn = min(k + 1, hi - 1);  // the next rotation, read ahead of the store
+        const cplx zn = h(i, kn + 1), cn = cs[kn - l], sn2 = sn[kn - l];
+        if (i <= k + 1) {
+          h(i, k) = cadd(cmul(v, cc), cmul(z, ss));
+          v = csub(cmul(z, cconj(cc)), cmul(v, cconj(ss)));
+        } else {
+          v = z;
+        }
+        z = zn;
+        cc = cn;
+        ss = sn2;
       }
+      h(i, hi) = v;
+    }
     __syncthreads();
     for (int k = l + t; k <= hi; k += kT) h(k, k) = cadd(h(k, k), mu);
     __syncthreads();
