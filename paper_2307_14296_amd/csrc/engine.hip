@@ -703,8 +703,10 @@ constexpr int kFormFrag = -7, kFormEven = -8;
 //    beyond, 90x90x5940, batch 4 (144 blocks) 59 against 52.  Up to 4 columns
 //    the vector kernels stay: 80x4x800, batch 80, 27 against 31, but 800x4x800
 //    13 against 9;
-//  * short reductions with one side at most 16: 83850x10x10 11 against 31,
-//    14400x16x16, batch 32, 39 against 52.
+//  * shorter reductions with one side at most 16 (above K = 32 and 4 columns),
+//    which reads the long operand once at the copy rate: 83850x10x10 11 against
+//    31, 14400x16x16, batch 32, 39 against 52, 97200x12x90 32 against 48 (32
+//    columns), 83850x10x130 41 against 65, 1728000x16x120 908 against 944.
 // Outputs 17 to 32 wide with more than 128 blocks stay on the 32-column tiles.
 static bool frag_may_pay(const GemmArgs& g) {
   if (g.kchunk > 0 || g.batch >= 65536) return false;
@@ -713,7 +715,7 @@ static bool frag_may_pay(const GemmArgs& g) {
   if (g.K > 32 && lo > 16 && lo <= 32 && f > 128) return false;
   if (f * kt <= 5120) return true;
   if (g.K >= 512) return lo > 4 && ((lo <= 48 && f <= 128) || f <= 40 || (lo > 16 && (f <= 96 || f * kt <= 14000)));
-  return g.K <= 32 && lo <= 16 && f < (i64(1) << 22);
+  return lo <= 16 && (g.K <= 32 || lo > 4) && f < (i64(1) << 22);
 }
 
 static void small_product(cclr_ctx* c, const GemmArgs& g) {

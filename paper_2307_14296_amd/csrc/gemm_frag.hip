@@ -278,7 +278,8 @@ FragPlan frag_plan(const GemmArgs& g) {
   if (g.M > 16 && work >= 1024) p.fm = 2;
   if (g.N > 16 && work >= 2048) p.fn = 2;
   const i64 nb = blocks(p.fm, p.fn);
-  p.nw = kt <= 1 ? 1 : (p.fm * p.fn == 1 && kt > 4 ? 8 : 4);
+  // one wave a tile where the tiles alone are two a SIMD (97200x12x90 32 us, 36 with four)
+  p.nw = kt <= 1 || (nb >= 2048 && kt <= 8) ? 1 : (p.fm * p.fn == 1 && kt > 4 ? 8 : 4);
   // cut the reduction until there are about 512 workgroups, each wave with at least 4 K tiles
   i64 S = std::min<i64>((512 + nb - 1) / nb, kt / (4 * p.nw));
   S = std::max<i64>(1, std::min<i64>(S, 4096));

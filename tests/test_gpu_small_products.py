@@ -78,7 +78,8 @@ LAYOUTS = [(False, False, False, 0, 1, 0), (True, False, True, 1, 0, 1), (False,
 FRAG = [(1, 1, 1, 1), (16, 16, 16, 1), (17, 15, 17, 3), (4, 4, 480, 1), (33, 16, 33, 2), (16, 256, 4096, 1),
         (256, 320, 256, 1), (500, 40, 40, 1), (2, 3000, 31, 2), (48, 640, 601, 1), (80, 128, 5000, 1),
         (10, 10, 70001, 1), (83850, 10, 10, 1), (9, 120, 20000, 2), (64, 64, 64, 16), (128, 192, 3001, 1),
-        (200, 160, 1600, 1), (80, 80, 3600, 3), (40, 33, 513, 14)]
+        (200, 160, 1600, 1), (80, 80, 3600, 3), (40, 33, 513, 14),
+        (70001, 12, 90, 1), (16, 40003, 129, 1), (9, 6000, 511, 4), (70000, 16, 33, 2)]
 
 
 @pytest.mark.parametrize("M,N,K,batch", FRAG)
