@@ -52,6 +52,14 @@ void* fixed_ws_address(int dev) {
 }  // namespace
 
 namespace {
+// after an error the stream may still be reading the caller's arrays: a call
+// returns only when it has finished with them
+void drain(cclr_ctx* c) {
+  if (!c) return;
+  (void)hipStreamSynchronize(c->stream);
+  if (c->side) (void)hipStreamSynchronize(c->side);
+}
+
 template <class F>
 int guarded(cclr_ctx* c, F&& f) {
   try {
@@ -61,13 +69,16 @@ int guarded(cclr_ctx* c, F&& f) {
     }
     return f();
   } catch (const CclrError& e) {
+    drain(c);
     if (c) c->err = e.what();
     else g_create_error = e.what();
     return e.code;
   } catch (const std::bad_alloc&) {
+    drain(c);
     if (c) c->err = "host allocation failed";
     return CCLR_ENOMEM;
   } catch (const std::exception& e) {
+    drain(c);
     if (c) c->err = e.what();
     return CCLR_EHIP;
   }
