@@ -261,7 +261,8 @@ int cclr_create(int o, int v, const cclr_options* opt, cclr_ctx** out) {
       HIPCHK(hipMalloc((void**)&c->input_bad, sizeof(int) * kInputMarks));
       HIPCHK(hipHostMalloc((void**)&c->input_host, sizeof(int), hipHostMallocDefault));
       *c->input_host = 0;
-      HIPCHK(hipMemset(c->input_bad, 0, sizeof(int) * kInputMarks));
+      // on the context's stream: nothing orders the null stream before a non-blocking one
+      HIPCHK(hipMemsetAsync(c->input_bad, 0, sizeof(int) * kInputMarks, c->stream));
     } catch (...) {
       if (c->input_bad) (void)hipFree(c->input_bad);
       if (c->input_host) (void)hipHostFree(c->input_host);

@@ -1,5 +1,6 @@
 """Calls that fail after work has been queued: they return only when the stream
-has finished with the caller's arrays."""
+has finished with the caller's arrays.  And a rejected input of one context
+means nothing to the next, also while the null stream is busy."""
 import numpy as np
 import pytest
 import torch
@@ -59,3 +60,21 @@ def test_missing_integral_block(setup):
     assert cc.lib().cclr_set_hamiltonian(ctx, *ptrs[:-1], None) == cc.CCLR_EINVAL
     assert drained()
     cc.cclr_set_hamiltonian(ctx, *blocks)
+
+
+def test_marks_of_a_destroyed_context(setup):
+    cc, _, _, blocks = setup
+    stream = torch.cuda.Stream()
+    bad = [blocks[0].clone()] + blocks[1:]
+    bad[0][0, 0] = float("nan")
+    for _ in range(3):
+        old = cc.cclr_create(4, 16, stream=stream)
+        with pytest.raises(cc.CclrError):
+            cc.cclr_set_hamiltonian(old, *bad)
+        cc.cclr_destroy(old)
+        busy()
+        ctx = cc.cclr_create(4, 16, stream=stream)  # its marks may lie where the old ones did
+        try:
+            cc.cclr_set_hamiltonian(ctx, *blocks)
+        finally:
+            cc.cclr_destroy(ctx)
