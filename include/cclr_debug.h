@@ -167,6 +167,11 @@ int cclr_dbg_set_overlap(cclr_ctx* ctx, int enable);
  * Negative values are CCLR_EINVAL. */
 int cclr_dbg_set_blocking(cclr_ctx* ctx, long long wp_block, int rhs_group);
 
+/* The next n device allocations of ctx find no room, as on a full device (an
+ * allocation is tried again after the context's own idle work memory has been
+ * released and once more after that of the device's other contexts). */
+int cclr_dbg_fail_allocs(cclr_ctx* ctx, int n);
+
 /* Hessian products (t^X F) of nvec response vectors with the context's
  * amplitudes and lambda (cclr_solve_lambda first; CCLR_ESTATE otherwise):
  * x1 [nvec][o][v], x2 [nvec][o][o][v][v] in (only unique doubles read), s1,

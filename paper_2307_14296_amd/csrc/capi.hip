@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <limits>
 #include <map>
+#include <memory>
 #include <mutex>
 
 #include "internal.h"
@@ -52,16 +53,20 @@ void* fixed_ws_address(int dev) {
 }  // namespace
 
 namespace {
-// after an error the stream may still be reading the caller's arrays: a call
-// returns only when it has finished with them
-void drain(cclr_ctx* c) {
+// After an error the stream may still be reading the caller's arrays: a call
+// returns only when it has finished with them, and with the work memory taken
+// since mk, which is handed back.
+void drain(cclr_ctx* c, const Arena::Mark& mk) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
   if (c->side) (void)hipStreamSynchronize(c->side);
+  c->arena.reset(mk);
 }
 
 template <class F>
 int guarded(cclr_ctx* c, F&& f) {
+  const InCall busy(c);
+  const Arena::Mark mk = c ? c->arena.mark() : Arena::Mark{0, 0};
   try {
     if (c) {
       c->err.clear();
@@ -69,16 +74,16 @@ int guarded(cclr_ctx* c, F&& f) {
     }
     return f();
   } catch (const CclrError& e) {
-    drain(c);
+    drain(c, mk);
     if (c) c->err = e.what();
     else g_create_error = e.what();
     return e.code;
   } catch (const std::bad_alloc&) {
-    drain(c);
+    drain(c, mk);
     if (c) c->err = "host allocation failed";
     return CCLR_ENOMEM;
   } catch (const std::exception& e) {
-    drain(c);
+    drain(c, mk);
     if (c) c->err = e.what();
     return CCLR_EHIP;
   }
@@ -269,6 +274,7 @@ int cclr_create(int o, int v, const cclr_options* opt, cclr_ctx** out) {
       delete c;
       throw;
     }
+    register_context(c);
     *out = c;
     return CCLR_OK;
   });
@@ -276,6 +282,7 @@ int cclr_create(int o, int v, const cclr_options* opt, cclr_ctx** out) {
 
 int cclr_destroy(cclr_ctx* c) {
   if (!c) return CCLR_OK;
+  unregister_context(c);
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
   if (c->side) {
@@ -477,6 +484,8 @@ int cclr_jacobian_right_multi(int nctx, cclr_ctx* const* ctx, const int* nvec, c
   cclr_ctx* c0 = ctx[0];
   std::vector<Arena::Mark> marks(nctx);
   std::vector<bool> marked(nctx, false);
+  std::vector<std::unique_ptr<InCall>> busy;
+  for (int i = 0; i < nctx; ++i) busy.emplace_back(new InCall(ctx[i]));
   const int rc = guarded(c0, [&]() -> int {
     REQUIRE(nvec && omega && gamma && r1 && r2 && s1 && s2, CCLR_EINVAL, "null argument array");
     for (int i = 0; i < nctx; ++i) {

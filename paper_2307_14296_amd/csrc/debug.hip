@@ -31,6 +31,7 @@ int cclr_dbg_run_gemm_b2(cclr_ctx* c, int M, int N, int K, int nb1, int nb2, con
                          long long sBk, long long sBn, cclr_c64* C, long long sCb, long long sCb2, long long sCm,
                          long long sCn, double ar, double ai, int beta) {
   if (!c) return CCLR_EINVAL;
+  const InCall busy(c);
   try {
     REQUIRE(M > 0 && N > 0 && K > 0 && nb1 > 0 && nb2 > 1 && (long long)nb1 * nb2 < 65536, CCLR_EINVAL,
             "two-level batch: empty product or batch out of range");
@@ -53,6 +54,7 @@ int cclr_dbg_run_gemm(cclr_ctx* c, int M, int N, int K, int batch, const cclr_c6
                       int conjB, cclr_c64* C, long long sCb, long long sCm, long long sCn, double ar, double ai,
                       int beta) {
   if (!c) return CCLR_EINVAL;
+  const InCall busy(c);
   try {
     REQUIRE(M > 0 && N > 0 && K > 0 && batch > 0, CCLR_EINVAL, "empty product");
     GemmArgs g{};
@@ -284,6 +286,7 @@ int cclr_dbg_contract(cclr_ctx* c, double ar, double ai, const cclr_c64* A, cons
                       const cclr_c64* B, const char* lb, const long long* bdims, cclr_c64* C, const char* lc,
                       const long long* cdims) {
   if (!c) return CCLR_EINVAL;
+  const InCall busy(c);
   try {
     contract(c, cx(ar, ai), dten(A, la, adims), la, dten(B, lb, bdims), lb, dten(C, lc, cdims), lc, true);
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -313,6 +316,7 @@ int cclr_dbg_get(cclr_ctx* c, const char* name, cclr_c64* dst, long long* count)
     const i64 v = c->v;
     if (count) *count = (long long)(v * v * v * v);
     if (dst && c->Wp.p) {
+      const InCall busy(c);
       try {
         with_plain_wp(c, [&]() { launch_unpack_vvvv(c->v, c->Wp.c(), (cplx*)dst, c->stream); });
         HIPCHK(hipStreamSynchronize(c->stream));
@@ -416,9 +420,16 @@ int cclr_dbg_set_blocking(cclr_ctx* c, long long wp_block, int rhs_group) {
   return CCLR_OK;
 }
 
+int cclr_dbg_fail_allocs(cclr_ctx* c, int n) {
+  if (!c || n < 0) return CCLR_EINVAL;
+  c->dbg_fail_allocs = n;
+  return CCLR_OK;
+}
+
 int cclr_dbg_hessian(cclr_ctx* c, int nvec, const cclr_c64* x1, const cclr_c64* x2, cclr_c64* s1, cclr_c64* s2) {
   if (!c || nvec < 1 || !x1 || !x2 || !s1 || !s2) return CCLR_EINVAL;
   if (!c->have_t || !c->have_lam) return CCLR_ESTATE;
+  const InCall busy(c);
   try {
     HIPCHK(hipSetDevice(c->device));
     Arena::Mark mk = c->arena.mark();

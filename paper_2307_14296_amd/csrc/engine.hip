@@ -14,19 +14,63 @@
 #include "internal.h"
 
 // ------------------------------------------------------------ allocation
+namespace {
+std::mutex g_contexts_mutex;  // taken before any context's in_call, which is only tried under it
+std::vector<cclr_ctx*> g_contexts;
+
+// releases the idle work memory of the other contexts on c's device that no call is using
+void release_others(cclr_ctx* c) {
+  std::lock_guard<std::mutex> lk(g_contexts_mutex);
+  for (cclr_ctx* x : g_contexts) {
+    if (x == c || x->device != c->device || !x->in_call.try_lock()) continue;
+    x->arena.release_idle();
+    x->in_call.unlock();
+  }
+}
+}  // namespace
+
+void register_context(cclr_ctx* c) {
+  std::lock_guard<std::mutex> lk(g_contexts_mutex);
+  g_contexts.push_back(c);
+}
+
+void unregister_context(cclr_ctx* c) {
+  std::lock_guard<std::mutex> lk(g_contexts_mutex);
+  g_contexts.erase(std::remove(g_contexts.begin(), g_contexts.end(), c), g_contexts.end());
+}
+
+// Where the cap or the device leaves no room, the context's own idle work
+// memory is released and then that of the device's other contexts, before the
+// request is refused: what contexts keep between calls costs no caller memory.
 void DevBuf::alloc(cclr_ctx* c, size_t nbytes) {
   if (p && nbytes == bytes && ctx == c) return;  // same size: keep the allocation
   release();
   if (nbytes == 0) return;
-  if (c->opt.device_mem_cap && c->allocated + nbytes > c->opt.device_mem_cap)
+  auto over_cap = [&]() { return c->opt.device_mem_cap && c->allocated + nbytes > c->opt.device_mem_cap; };
+  if (over_cap()) c->arena.release_idle();
+  if (over_cap())
     throw CclrError(CCLR_ENOMEM, "device memory cap exceeded (" + std::to_string(c->allocated + nbytes) +
                                      " > " + std::to_string(c->opt.device_mem_cap) + " bytes)");
-  hipError_t e = hipMalloc(&p, nbytes);
-  if (e != hipSuccess) {
+  auto take = [&]() {
+    if (c->dbg_fail_allocs > 0) {
+      --c->dbg_fail_allocs;
+      return false;
+    }
+    if (hipMalloc(&p, nbytes) == hipSuccess) return true;
     p = nullptr;
     (void)hipGetLastError();
-    throw CclrError(CCLR_ENOMEM, "hipMalloc of " + std::to_string(nbytes) + " bytes failed");
+    return false;
+  };
+  bool got = take();
+  if (!got) {
+    c->arena.release_idle();
+    got = take();
   }
+  if (!got) {
+    release_others(c);
+    got = take();
+  }
+  if (!got) throw CclrError(CCLR_ENOMEM, "hipMalloc of " + std::to_string(nbytes) + " bytes failed");
   ctx = c;
   bytes = nbytes;
   c->allocated += nbytes;
@@ -64,6 +108,11 @@ void* Arena::get(size_t bytes) {
     }
     if (cur + 1 < chunks.size()) ++cur;
     else break;
+  }
+  if (!chunks.empty() && used[cur] == 0 && chunks[cur]->bytes == 0) {  // an entry whose memory was released
+    chunks[cur]->alloc(ctx, std::max(bytes, chunk_bytes));
+    used[cur] = bytes;
+    return chunks[cur]->p;
   }
   DevBuf* b = new DevBuf();
   try {
@@ -122,8 +171,18 @@ void Arena::trim(size_t keep) {
   }
 }
 
-// idle arena memory a context keeps at quiet points: a sixty-fourth of the
-// device, none under a memory cap
+void Arena::release_idle() {
+  bool any = false;
+  for (size_t k = 0; k < chunks.size(); ++k) any = any || (used[k] == 0 && chunks[k]->bytes > 0);
+  if (!any) return;
+  (void)hipDeviceSynchronize();  // queued work may still use what has been handed back
+  for (size_t k = 0; k < chunks.size(); ++k)
+    if (used[k] == 0) chunks[k]->release();
+}
+
+// idle arena memory a context keeps at quiet points (4 GiB: what the build of
+// the intermediates and a solve take at o = 12, v = 90), none under a memory
+// cap; any allocation that finds no room gets it back
 size_t arena_keep(const cclr_ctx* c) { return c->opt.device_mem_cap ? 0 : size_t(4) << 30; }
 
 // How many of n vectors, each needing bytes_per_vec of working memory, fit

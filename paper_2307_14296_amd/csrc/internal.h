@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <complex>
 #include <map>
+#include <mutex>
 #include <tuple>
 #include <vector>
 #include <stdexcept>
@@ -79,6 +80,9 @@ struct Arena {
   Mark mark() const;
   void reset(Mark m);
   void trim(size_t keep = 0);
+  // frees the memory of every chunk that holds nothing, whatever its place (its
+  // entry stays, empty, so that marks keep their meaning)
+  void release_idle();
 };
 
 // ----------------------------------------------------------- tensor views
@@ -331,6 +335,9 @@ struct cclr_ctx {
   size_t allocated = 0;
   int device = 0;
 
+  // held by the call that uses the context (see InCall)
+  std::recursive_mutex in_call;
+
   // inputs
   DevBuf f, Voooo, Vooov, Voovv, Vovov, Vovvv, Vvvvv, t1, t2;
   bool have_H = false, have_t = false, have_lam = false;
@@ -393,6 +400,8 @@ struct cclr_ctx {
   // right-hand sides a memory-bounded group may hold
   i64 dbg_wp_block = 0;
   int dbg_rhs_group = 0;
+  // device allocations of the context that are to find no room (for tests)
+  int dbg_fail_allocs = 0;
   // optional timing of the particle-particle ladder GEMM launches
   bool prof = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
@@ -404,6 +413,24 @@ struct cclr_ctx {
   i64 ns() const { return (i64)o * v; }
   i64 nd() const { return O2() * V2(); }
 };
+
+// A call on a context, while it runs.  A context is used by one thread at a
+// time; the lock tells a call of another thread that runs out of device memory
+// whose idle work memory it may release.
+struct InCall {
+  cclr_ctx* c;
+  explicit InCall(cclr_ctx* ctx) : c(ctx) {
+    if (c) c->in_call.lock();
+  }
+  ~InCall() {
+    if (c) c->in_call.unlock();
+  }
+  InCall(const InCall&) = delete;
+  InCall& operator=(const InCall&) = delete;
+};
+// contexts between cclr_create and cclr_destroy, whose idle memory can be released
+void register_context(cclr_ctx* c);
+void unregister_context(cclr_ctx* c);
 
 // integral block views (any kinds string, e.g. "vovv"), derived by symmetry
 Ten Vblk(cclr_ctx* c, const char* kinds);
