@@ -38,10 +38,11 @@
  *   copies of f, the integral blocks, t, lambda and the intermediates and
  *   retains no caller pointer after a call returns.  A context is used by one
  *   host thread at a time; distinct contexts are independent.
- * - Between calls a context keeps the work memory of its last calls, of which
- *   cclr_set_amplitudes leaves it at most 4 GiB (none under a
- *   device_mem_cap).  An allocation of any context on the same device that
- *   finds no room gets the idle part of it back; cclr_destroy frees it.
+ * - Between calls a context keeps work memory: of its last calls' at most half
+ *   of the device's memory (what fits under a device_mem_cap), and after
+ *   cclr_set_amplitudes at most 4 GiB (none under a cap).  An allocation of
+ *   any context on the same device that finds no room gets the idle part of
+ *   it back; cclr_destroy frees it.
  * - Return codes: CCLR_OK (0); CCLR_ENOTCONV (> 0: result written, solver
  *   did not reach the tolerance, see cclr_solve_info); negative codes are
  *   errors, with cclr_last_error() describing them.  Inputs containing

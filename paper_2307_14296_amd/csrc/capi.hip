@@ -63,7 +63,14 @@ void drain(cclr_ctx* c, const Arena::Mark& mk) {
   c->arena.reset(mk);
 }
 
-template <class F>
+// What a call leaves in the arena serves the next one; beyond half of the
+// device it is released (but not by a call on the fixed work space, which
+// makes no hipFree: guarded<false>).
+void quiet(cclr_ctx* c) {
+  if (c && !c->opt.device_mem_cap && !c->arena.ext) c->arena.trim(c->device_bytes / 2);
+}
+
+template <bool kMayFree = true, class F>
 int guarded(cclr_ctx* c, F&& f) {
   const InCall busy(c);
   const Arena::Mark mk = c ? c->arena.mark() : Arena::Mark{0, 0};
@@ -72,7 +79,9 @@ int guarded(cclr_ctx* c, F&& f) {
       c->err.clear();
       HIPCHK(hipSetDevice(c->device));
     }
-    return f();
+    const int rc = f();
+    if (kMayFree) quiet(c);
+    return rc;
   } catch (const CclrError& e) {
     drain(c, mk);
     if (c) c->err = e.what();
@@ -262,6 +271,8 @@ int cclr_create(int o, int v, const cclr_options* opt, cclr_ctx** out) {
     }
     c->arena.ctx = c;
     try {
+      size_t fr = 0;
+      HIPCHK(hipMemGetInfo(&fr, &c->device_bytes));
       c->fixed_ws = fixed_ws_address(c->device);
       HIPCHK(hipMalloc((void**)&c->input_bad, sizeof(int) * kInputMarks));
       HIPCHK(hipHostMalloc((void**)&c->input_host, sizeof(int), hipHostMallocDefault));
@@ -435,7 +446,7 @@ int cclr_jacobian_right(cclr_ctx* c, int nvec, const double* omega, const double
 int cclr_jacobian_right_noalloc(cclr_ctx* c, int nvec, const double* omega, const double* gamma,
                                 const cclr_c64* r1, const cclr_c64* r2, cclr_c64* s1, cclr_c64* s2) {
   if (!c) return CCLR_EINVAL;
-  return guarded(c, [&]() -> int {
+  return guarded<false>(c, [&]() -> int {
     require_t(c);
     check_freqs(nvec, omega, gamma);
     if (nvec == 0) return CCLR_OK;
@@ -534,7 +545,10 @@ int cclr_jacobian_right_multi(int nctx, cclr_ctx* const* ctx, const int* nvec, c
     return CCLR_OK;
   });
   for (int i = 0; i < nctx; ++i)
-    if (marked[i]) ctx[i]->arena.reset(marks[i]);
+    if (marked[i]) {
+      ctx[i]->arena.reset(marks[i]);
+      quiet(ctx[i]);
+    }
   return rc;
 }
 

@@ -157,14 +157,18 @@ void Arena::reset(Mark m) {
   cur = m.chunk;
 }
 
+size_t Arena::idle() const {
+  size_t b = 0;
+  for (size_t k = chunks.size(); k > cur + 1 && used[k - 1] == 0; --k) b += chunks[k - 1]->bytes;
+  return b;
+}
+
 void Arena::trim(size_t keep) {
-  // free every chunk after the active one that holds nothing, down to `keep` bytes of them
-  size_t idle = 0;
-  for (size_t k = chunks.size(); k > cur + 1 && used[k - 1] == 0; --k) idle += chunks[k - 1]->bytes;
-  if (idle <= keep) return;
+  size_t left = idle();
+  if (left <= keep) return;
   (void)hipDeviceSynchronize();
-  while (idle > keep && chunks.size() > cur + 1 && used.back() == 0) {
-    idle -= chunks.back()->bytes;
+  while (left > keep && chunks.size() > cur + 1 && used.back() == 0) {
+    left -= chunks.back()->bytes;
     delete chunks.back();
     chunks.pop_back();
     used.pop_back();
@@ -180,36 +184,31 @@ void Arena::release_idle() {
     if (used[k] == 0) chunks[k]->release();
 }
 
-// idle arena memory a context keeps at quiet points (4 GiB: what the build of
+// idle arena memory a context keeps after a build (4 GiB: what the build of
 // the intermediates and a solve take at o = 12, v = 90), none under a memory
 // cap; any allocation that finds no room gets it back
 size_t arena_keep(const cclr_ctx* c) { return c->opt.device_mem_cap ? 0 : size_t(4) << 30; }
 
 // How many of n vectors, each needing bytes_per_vec of working memory, fit
-// in the device memory that is still free (and under the context's cap).
-// Unused arena chunks beyond what a context keeps are released first, and all
-// of them where not every vector fits otherwise, so that they count as free
-// (releasing all on every call had each solve return and take again its
-// subspace memory, up to 40 ms of a solve of 30 with other contexts alive).
+// in the device memory that is free or idle in the arena.  Idle memory stays
+// for them: released here and taken again, it cost each response function at
+// o = 20, v = 200 in BF16X3 (12 vectors, 48 slots) 1 to 4 s beside 1.15 s of
+// work, since the driver hands out what it has just got back only once that is
+// cleared.  Chunks of other sizes are released by the allocation that finds no
+// room (DevBuf::alloc), and here under a cap, which they would eat into.
 int fit_vectors(cclr_ctx* c, double bytes_per_vec, int n) {
   if (n <= 1) return n;
-  auto room = [&]() {
-    size_t fr = 0, tot = 0;
-    HIPCHK(hipMemGetInfo(&fr, &tot));
-    double budget = 0.8 * (double)fr;
-    if (c->opt.device_mem_cap) {
-      const double left = c->opt.device_mem_cap > c->allocated ? (double)(c->opt.device_mem_cap - c->allocated) : 0.0;
-      budget = std::min(budget, left);
-    }
-    return (int)std::max(1.0, std::min((double)n, std::floor(budget / std::max(bytes_per_vec, 1.0))));
-  };
-  c->arena.trim(arena_keep(c));
-  int fit = room();
-  if (fit < n) {
-    c->arena.trim();
-    fit = room();
+  if (c->opt.device_mem_cap) c->arena.trim();
+  size_t fr = 0, tot = 0;
+  HIPCHK(hipMemGetInfo(&fr, &tot));
+  double budget = 0.8 * ((double)fr + (double)c->arena.idle());
+  if (c->opt.device_mem_cap) {
+    const double left = c->opt.device_mem_cap > c->allocated ? (double)(c->opt.device_mem_cap - c->allocated) : 0.0;
+    budget = std::min(budget, left);
   }
-  return c->dbg_rhs_group > 0 ? std::min(fit, c->dbg_rhs_group) : fit;
+  int fit = (int)std::max(1.0, std::min((double)n, std::floor(budget / std::max(bytes_per_vec, 1.0))));
+  if (c->dbg_rhs_group > 0) fit = std::min(fit, c->dbg_rhs_group);
+  return fit;
 }
 
 // ------------------------------------------------------------------ views

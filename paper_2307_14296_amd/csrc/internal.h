@@ -79,6 +79,7 @@ struct Arena {
   struct Mark { size_t chunk, top; };
   Mark mark() const;
   void reset(Mark m);
+  size_t idle() const;  // bytes of the chunks after the active one, if they hold nothing
   void trim(size_t keep = 0);
   // frees the memory of every chunk that holds nothing, whatever its place (its
   // entry stays, empty, so that marks keep their meaning)
@@ -334,6 +335,7 @@ struct cclr_ctx {
   std::string err;
   size_t allocated = 0;
   int device = 0;
+  size_t device_bytes = 0;  // memory of the device
 
   // held by the call that uses the context (see InCall)
   std::recursive_mutex in_call;
@@ -497,7 +499,7 @@ int solve_system(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rh
 void merge_conditioning(cclr_solve_info& dst, const cclr_solve_info& src);
 // nvec packed vectors from the arena
 VecSet packed_buf(cclr_ctx* c, int n);
-// idle arena memory (bytes) a context keeps at quiet points
+// idle arena memory (bytes) a context keeps after a build
 size_t arena_keep(const cclr_ctx* c);
 // how many of n vectors with the given working memory each fit in free device memory (>= 1)
 int fit_vectors(cclr_ctx* c, double bytes_per_vec, int n);

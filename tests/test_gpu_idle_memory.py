@@ -1,6 +1,7 @@
 """Work memory that contexts keep between calls is given back where an
 allocation finds no room: the context's own, and that of another context on
-the device.  That an allocation finds none is set from the host."""
+the device.  Where it fits it stays for the next call.  That an allocation
+finds no room is set from the host."""
 import ctypes
 import threading
 
@@ -99,6 +100,18 @@ def test_no_room_at_all(lib):
         transform(lib, small, 1600)
         cc.cclr_destroy(small)
     transform(lib, ctx, 100)
+    cc.cclr_destroy(ctx)
+
+
+def test_second_solve_allocates_nothing(lib):
+    # 300 right-hand sides with 48 slots each, 5 GB of subspace: A = 0, so x = b / z
+    cc, H, (r1, r2), (s1, s2) = lib
+    ctx, n = context(cc, H), 300
+    for fails in (0, 3):
+        assert cc.lib().cclr_dbg_fail_allocs(ctx, fails) == 0
+        rc, info = cc.cclr_solve_damped(ctx, cc.CCLR_RIGHT, [0.5] * n, [0.25] * n, r1[:n], r2[:n], s1[:n], s2[:n])
+        assert rc == 0, info.as_dict()
+        assert torch.allclose(s1[:n], r1[:n] / (0.5 + 0.25j), rtol=0, atol=1e-9) and not bool(s2[:n].any())
     cc.cclr_destroy(ctx)
 
 
