@@ -190,6 +190,15 @@ __device__ __forceinline__ void put(cplx* dst, double xr, double xi, double ar, 
   *dst = y;
 }
 
+// the three accumulators of entry (m, n) of a cut tile's run, as they are: one
+// plane each, so that a wave's stores are runs of 16 floats
+__device__ __forceinline__ void keep(float* __restrict__ W, i64 slot, int bm, int m, int n, float a, float b, float c) {
+  float* w = W + (3 * slot * bm + m) * TN + n;
+  w[0] = a;
+  w[bm * TN] = b;
+  w[2 * bm * TN] = c;
+}
+
 // C[m][n] (+)= alpha * sum_k A[m][k] B[n][k] on split operands.  BM x 128
 // tile per workgroup of eight waves (2 x 4, each BM/2 x 32 in 16x16 MFMA
 // blocks; two waves per SIMD, which hide each other's LDS and barrier
@@ -217,7 +226,7 @@ template <int F, int BM>
 __global__ __launch_bounds__(512) void k_cgemm_bf16s(const u4v* __restrict__ As, const u4v* __restrict__ Bs,
                                                      int Mpad, int Npad, int M, int N, cplx* __restrict__ C, i64 sCm,
                                                      i64 sCn, double ar, double ai, int beta, SplitPlan p,
-                                                     float2* __restrict__ W) {
+                                                     float* __restrict__ W) {
   constexpr FormDesc D = kForms[F];
   constexpr int PA = D.pa, PB = D.pb;
   constexpr int RSA = 4 * PA, RSB = 4 * PB;  // chunks per row
@@ -325,9 +334,12 @@ __global__ __launch_bounds__(512) void k_cgemm_bf16s(const u4v* __restrict__ As,
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
-          const double xr = (double)acc[0][i][j][r] - (double)acc[1][i][j][r], xi = (double)acc[2][i][j][r];
-          if (slot >= 0) W[(slot * BM + m) * TN + n] = make_float2((float)xr, (float)xi);
-          else if (m0 + m < M && n0 + n < N) put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, xr, xi, ar, ai, beta);
+          if (slot >= 0) {
+            keep(W, slot, BM, m, n, acc[0][i][j][r], acc[1][i][j][r], acc[2][i][j][r]);
+          } else if (m0 + m < M && n0 + n < N) {
+            const double xr = (double)acc[0][i][j][r] - (double)acc[1][i][j][r], xi = (double)acc[2][i][j][r];
+            put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, xr, xi, ar, ai, beta);
+          }
         }
   };
   deal(p, segment);
@@ -399,7 +411,7 @@ template <int BM>
 __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, const u4v* __restrict__ Bs, int Mpad,
                                                     int Npad, int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn,
                                                     double ar, double ai, int beta, SplitPlan p,
-                                                    float2* __restrict__ W) {
+                                                    float* __restrict__ W) {
   constexpr int RS = 12, NT = 512, WM = BM / 2, WN = TN / 4, FM = WM / 16, FN = WN / 16;
   constexpr int CA = BM * RS, CB = TN * RS;  // chunks per tile and k step
   __shared__ u4v sA0[CA], sA1[CA];
@@ -493,20 +505,23 @@ __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
-          const double g1 = acc[0][i][j][r], g2 = acc[1][i][j][r], g3 = acc[2][i][j][r];
-          const double xr = g1 - g3, xi = g1 + g2;
-          if (slot >= 0) W[(slot * BM + m) * TN + n] = make_float2((float)xr, (float)xi);
-          else if (m0 + m < M && n0 + n < N) put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, xr, xi, ar, ai, beta);
+          if (slot >= 0) {
+            keep(W, slot, BM, m, n, acc[0][i][j][r], acc[1][i][j][r], acc[2][i][j][r]);
+          } else if (m0 + m < M && n0 + n < N) {
+            const double g1 = acc[0][i][j][r], g2 = acc[1][i][j][r], g3 = acc[2][i][j][r];
+            put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, g1 - g3, g1 + g2, ar, ai, beta);
+          }
         }
   };
   deal(p, segment);
 }
 
-// Adds the partial sums of cut tile whole + blockIdx.x in the order of k, in
-// FP64, and stores the result, one element per thread (blockIdx.y: which 256
-// of the tile).
+// Adds the accumulators of the runs of cut tile whole + blockIdx.x in the order
+// of k, in FP64, forms the result of them and stores it, one element per
+// thread (blockIdx.y: which 256 of the tile).
 __global__ __launch_bounds__(256) void k_split_join(int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn, double ar,
-                                                    double ai, int beta, SplitPlan p, const float2* __restrict__ W) {
+                                                    double ai, int beta, SplitPlan p, int gauss,
+                                                    const float* __restrict__ W) {
   const i64 total = (p.tiles - p.whole) * p.nk, t = blockIdx.x;
   const i64 lo = t * p.nk, hi = lo + p.nk;
   // run c covers the k steps [c total / cutters, (c + 1) total / cutters): the runs with a part of [lo, hi)
@@ -520,20 +535,27 @@ __global__ __launch_bounds__(256) void k_split_join(int M, int N, cplx* __restri
   const int size = p.bm * TN, e = blockIdx.y * 256 + threadIdx.x;
   const int m = (int)(tile % p.tm) * p.bm + e / TN, n = (int)(tile / p.tm) * TN + e % TN;
   if (m >= M || n >= N) return;
-  // the first run may have begun in the tile before: then this is its second piece
-  const float2 first = W[(2 * c0 + (b0 < lo ? 1 : 0)) * size + e];
-  double xr = first.x, xi = first.y;
+  double x[3];
+  {
+    // the first run may have begun in the tile before: then this is its second piece
+    const float* w = W + 3 * (2 * c0 + (b0 < lo ? 1 : 0)) * size + e;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) x[q] = w[q * size];
+  }
   constexpr int U = 4;
   for (i64 c = c0 + 1; c < c1; c += U) {
-    float2 w[U];
+    float w[U][3];
 #pragma unroll
-    for (int u = 0; u < U; ++u) w[u] = c + u < c1 ? W[2 * (c + u) * size + e] : make_float2(0.f, 0.f);
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      xr += (double)w[u].x;
-      xi += (double)w[u].y;
-    }
+      for (int q = 0; q < 3; ++q) w[u][q] = c + u < c1 ? W[(6 * (c + u) + q) * size + e] : 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) x[q] += (double)w[u][q];
   }
+  // split-BF16: Ar Br, Ai Bi, Ar Bi + Ai Br; FP32: k1, k2, k3 of Gauss's form
+  const double xr = x[0] - x[gauss ? 2 : 1], xi = gauss ? x[0] + x[1] : x[2];
   put(C + (i64)m * sCm + (i64)n * sCn, xr, xi, ar, ai, beta);
 }
 
@@ -636,7 +658,7 @@ static double split_cost(const SplitPlan& p, int form) {
   if (last) t += p.nk * (lo + (hi - lo) * (double)last / 256) + 2.0 + (double)last * 16 * tile;
   if (p.cutters) {
     const double rest = (double)(p.tiles - p.whole);
-    t += rest * p.nk / p.cutters * hi + 4.0 + (p.cutters + rest) * 16 * tile;
+    t += rest * p.nk / p.cutters * hi + 4.0 + p.cutters * 24 * tile + rest * 16 * tile;
   }
   return t;
 }
@@ -655,12 +677,12 @@ SplitPlan split_plan(int M, int N, int K, int form, bool room) {
   return best;
 }
 
-size_t split_workspace(const SplitPlan& p) { return sizeof(float2) * 2 * (size_t)p.cutters * p.bm * TN; }
+size_t split_workspace(const SplitPlan& p) { return sizeof(float) * 6 * (size_t)p.cutters * p.bm * TN; }
 
 namespace {
 template <int BM>
 void launch_bm(const SplitMat& A, const SplitMat& B, cplx* C, i64 sCm, i64 sCn, double ar, double ai, int beta,
-               const SplitPlan& p, float2* W, hipStream_t st) {
+               const SplitPlan& p, float* W, hipStream_t st) {
   const dim3 grid((unsigned)p.grid), block(512);
   const u4v *a = (const u4v*)A.p, *b = (const u4v*)B.p;
   if (A.form == F32_G3)
@@ -685,15 +707,15 @@ void launch_split_gemm(const SplitMat& A, const SplitMat& B, cplx* C, i64 sCm, i
           CCLR_EINVAL, "split GEMM: operands and plan differ");
   REQUIRE(p.tiles < (i64)1 << 30, CCLR_EINVAL, "split GEMM: too many tiles");
   switch (p.bm) {
-    case 64: launch_bm<64>(A, B, C, sCm, sCn, ar, ai, beta, p, (float2*)W, st); break;
-    case 96: launch_bm<96>(A, B, C, sCm, sCn, ar, ai, beta, p, (float2*)W, st); break;
-    case 128: launch_bm<128>(A, B, C, sCm, sCn, ar, ai, beta, p, (float2*)W, st); break;
+    case 64: launch_bm<64>(A, B, C, sCm, sCn, ar, ai, beta, p, (float*)W, st); break;
+    case 96: launch_bm<96>(A, B, C, sCm, sCn, ar, ai, beta, p, (float*)W, st); break;
+    case 128: launch_bm<128>(A, B, C, sCm, sCn, ar, ai, beta, p, (float*)W, st); break;
     default: throw CclrError(CCLR_EINVAL, "split GEMM: no such tile");
   }
   HIPCHK(hipGetLastError());
   if (p.cutters > 0) {
     hipLaunchKernelGGL(k_split_join, dim3((unsigned)(p.tiles - p.whole), p.bm * TN / 256), dim3(256), 0, st, A.rows,
-                       B.rows, C, sCm, sCn, ar, ai, beta, p, (const float2*)W);
+                       B.rows, C, sCm, sCn, ar, ai, beta, p, A.form == F32_G3 ? 1 : 0, (const float*)W);
     HIPCHK(hipGetLastError());
   }
 }
