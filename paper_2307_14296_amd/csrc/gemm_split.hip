@@ -214,14 +214,18 @@ __device__ __forceinline__ void keep(float* __restrict__ W, i64 slot, int bm, in
 //
 // The LDS holds one workgroup per compute unit.  A solve's transforms have
 // few tiles (a ladder of four vectors at o = 12, v = 90 is 264 x 4005: 96 of
-// 128 x 128, padded by 45%), so the grid is at most 256 workgroups that take
-// whole tiles while those fill all of them and equal runs of the k steps of
-// the others (deal); k_split_join adds the partial sums.  BM is 64, 96 or
-// 128, by estimated time (split_plan).  Bound by the bf16 MFMAs (1.28 us of a
+// 128 x 128, padded by 45%): then 256 workgroups take whole tiles while those
+// fill all of them and equal runs of the k steps of the others (deal), and
+// k_split_join adds the partial sums.  Products that gain nothing from that
+// run one workgroup per tile, the XCDs on contiguous ranges of tiles, m
+// fastest, so that the B tile of a step is shared in an XCD's L2: a ring of 12
+// vectors, 48000x4000x4000, 13.1 ms in X3 and 9.7 in X2 (14.3 and 11.5 on 256
+// workgroups in rounds).  BM is 64, 96 or 128, by estimated time (split_plan).
+// Bound by the bf16 MFMAs (1.28 us of a
 // 128-row k step; 1.5 to 2.0 measured, by how many compute units compete for
-// the operands).  Against whole 128 x 128 tiles, X3, us: 264x4005x4005 97 / 213,
-// 66x4005x4005 41 / 203, 1080x1080x1080 45 / 67, 4320x1080x1080 121 / 150,
-// 570x19900x19900 3790 / 4810.
+// the operands).  Against whole 128 x 128 tiles, X3, us: 264x4005x4005 103 / 218,
+// 66x4005x4005 50 / 205, 1080x1080x1080 42 / 62, 4320x1080x1080 110 / 138,
+// 570x19900x19900 3920 / 4900.
 template <int F, int BM>
 __global__ __launch_bounds__(512) void k_cgemm_bf16s(const u4v* __restrict__ As, const u4v* __restrict__ Bs,
                                                      int Mpad, int Npad, int M, int N, cplx* __restrict__ C, i64 sCm,
@@ -405,9 +409,12 @@ __global__ __launch_bounds__(256) void k_split_f32(int rows, int K, const cplx* 
 // C[m][n] (+)= alpha * sum_k A[m][k] B[n][k] on FP32 split operands: the
 // pipeline and the even split of k_cgemm_bf16s (BM x 128 tiles of eight
 // BM/2 x 32 waves, direct loads one 16-deep k step ahead into the other of
-// two LDS stages).  Against whole 128 x 128 tiles, us: 264x4005x4005 283 / 808,
-// 4320x1080x1080 315 / 464, 570x19900x19900 11680 / 15890.
-template <int BM>
+// two LDS stages).  Without cut tiles the 128-row kernel takes one tile and no
+// loop over tiles (CUT = false), which spares it registers: 2280x19900x19900
+// 39.5 ms, 41.5 with the loop (the bf16 forms are the same with and without).
+// Against whole 128 x 128 tiles, us: 264x4005x4005 289 / 740, 4320x1080x1080
+// 300 / 411, 570x19900x19900 11630 / 14700.
+template <int BM, bool CUT>
 __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, const u4v* __restrict__ Bs, int Mpad,
                                                     int Npad, int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn,
                                                     double ar, double ai, int beta, SplitPlan p,
@@ -488,7 +495,7 @@ __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, 
         }
       }
     };
-    __syncthreads();  // every wave is done with the stages of the previous segment
+    if (CUT) __syncthreads();  // every wave is done with the stages of the previous segment
     fetch(k0, sA0, sB0);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -505,7 +512,7 @@ __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
-          if (slot >= 0) {
+          if (CUT && slot >= 0) {
             keep(W, slot, BM, m, n, acc[0][i][j][r], acc[1][i][j][r], acc[2][i][j][r]);
           } else if (m0 + m < M && n0 + n < N) {
             const double g1 = acc[0][i][j][r], g2 = acc[1][i][j][r], g3 = acc[2][i][j][r];
@@ -513,7 +520,8 @@ __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, 
           }
         }
   };
-  deal(p, segment);
+  if (CUT) deal(p, segment);
+  else segment(xcd_position((int)blockIdx.x, (int)gridDim.x), 0, p.nk, -1);
 }
 
 // Adds the accumulators of the runs of cut tile whole + blockIdx.x in the order
@@ -630,7 +638,7 @@ SplitPlan split_plan_for(int M, int N, int K, int form, int bm, int cutters) {
   constexpr int G = 256;
   const i64 rounds = p.tiles / G, rest = p.tiles % G;
   p.whole = p.tiles;
-  p.grid = (int)std::min<i64>(p.tiles, G);
+  p.grid = (int)p.tiles;
   const i64 c = std::min<i64>(cutters, rest * p.nk / 4);  // runs of at least four steps
   if (c > rest) {
     p.whole = rounds * G;
@@ -643,10 +651,8 @@ SplitPlan split_plan_for(int M, int N, int K, int form, int bm, int cutters) {
 // Estimated time in us of a plan: the k steps of the busiest workgroup (low:
 // few compute units at work, full: all of them and their traffic), each whole
 // tile's stores, and for cut tiles the partial sums, written and read at
-// 4 TB/s.  Measured against it on one MI355X, X3, us (tile rows, cut or whole):
-// 264x4005x4005 96 cut 97 (est. 97), 128 cut 121 (121), 96 whole 165 (166), 128
-// whole 213 (215); 4320x1080x1080 128 cut 121 (124), 96 whole 123 (126), 128
-// whole 150 (146); 2400x800x800 96 whole 45 (47), 64 cut 53 (56).
+// 4 TB/s, and a tenth on their steps, since each workgroup starts at another k
+// and neighbours no longer share operand panels.
 static double split_cost(const SplitPlan& p, int form) {
   // us per k step with 128, 96 and 64 rows
   static const double low[3][3] = {{1.5, 1.15, 0.9}, {1.05, 0.84, 0.74}, {3.2, 2.55, 1.68}};
@@ -654,26 +660,35 @@ static double split_cost(const SplitPlan& p, int form) {
   const int r = p.bm == 128 ? 0 : p.bm == 96 ? 1 : 2;
   const double lo = low[form][r], hi = full[form][r], tile = p.bm * TN / 4e6;  // us of one byte per element
   const i64 rounds = p.whole / 256, last = p.whole % 256;
+  if (p.cutters == 0 && form == F32_G3 && r == 0) return (p.nk * 3.05 + 2.0 + 256 * 16 * tile) * (rounds + (last > 0));
   double t = (double)rounds * (p.nk * hi + 2.0 + 256 * 16 * tile);
   if (last) t += p.nk * (lo + (hi - lo) * (double)last / 256) + 2.0 + (double)last * 16 * tile;
   if (p.cutters) {
     const double rest = (double)(p.tiles - p.whole);
-    t += rest * p.nk / p.cutters * hi + 4.0 + p.cutters * 24 * tile + rest * 16 * tile;
+    t += 1.1 * rest * p.nk / p.cutters * hi + 16.0 + p.cutters * 24 * tile + rest * 16 * tile;
   }
   return t;
 }
 
+// The tile height of least estimated time, and cut tiles where they are
+// estimated 2% faster than that without.  Over 46 products (45 to 48000 rows,
+// K 600 to 19900) in the three forms that is at most 8% off the fastest plan
+// measured and never behind whole 128 x 128 tiles.  Cut on any gain in the
+// estimate, 29% behind: 540x3160x3160 in X2 113 us cut, 85 whole (96 rows of
+// 128: 119); 2280x19900x19900 in X2 10240, 9970.
 SplitPlan split_plan(int M, int N, int K, int form, bool room) {
   REQUIRE(split_form_valid(form), CCLR_EINVAL, "split: unknown form");
   SplitPlan best;
   double t = 1e300;
-  for (int bm : {128, 96, 64})
-    for (int cutters : {0, 256}) {
-      if (cutters && !room) continue;
+  for (int cutters : {0, 256}) {
+    if (cutters && !room) continue;
+    if (cutters) t *= 0.98;
+    for (int bm : {128, 96, 64}) {
       const SplitPlan p = split_plan_for(M, N, K, form, bm, cutters);
       const double tp = split_cost(p, form);
       if (tp < t) best = p, t = tp;
     }
+  }
   return best;
 }
 
@@ -685,15 +700,18 @@ void launch_bm(const SplitMat& A, const SplitMat& B, cplx* C, i64 sCm, i64 sCn, 
                const SplitPlan& p, float* W, hipStream_t st) {
   const dim3 grid((unsigned)p.grid), block(512);
   const u4v *a = (const u4v*)A.p, *b = (const u4v*)B.p;
-  if (A.form == F32_G3)
-    hipLaunchKernelGGL(k_cgemm_f32s<BM>, grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows, B.rows, C, sCm, sCn,
-                       ar, ai, beta, p, W);
+  if (A.form == F32_G3 && BM == 128 && p.cutters == 0)
+    hipLaunchKernelGGL((k_cgemm_f32s<128, false>), grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows, B.rows, C,
+                       sCm, sCn, ar, ai, beta, p, W);
+  else if (A.form == F32_G3)
+    hipLaunchKernelGGL((k_cgemm_f32s<BM, true>), grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows, B.rows, C,
+                       sCm, sCn, ar, ai, beta, p, W);
   else if (A.form == BF16_X2)
-    hipLaunchKernelGGL((k_cgemm_bf16s<BF16_X2, BM>), grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows, B.rows,
-                       C, sCm, sCn, ar, ai, beta, p, W);
+    hipLaunchKernelGGL((k_cgemm_bf16s<BF16_X2, BM>), grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows,
+                       B.rows, C, sCm, sCn, ar, ai, beta, p, W);
   else
-    hipLaunchKernelGGL((k_cgemm_bf16s<BF16_X3, BM>), grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows, B.rows,
-                       C, sCm, sCn, ar, ai, beta, p, W);
+    hipLaunchKernelGGL((k_cgemm_bf16s<BF16_X3, BM>), grid, block, 0, st, a, b, A.rows_pad, B.rows_pad, A.rows,
+                       B.rows, C, sCm, sCn, ar, ai, beta, p, W);
 }
 }  // namespace
 
@@ -705,7 +723,8 @@ void launch_split_gemm(const SplitMat& A, const SplitMat& B, cplx* C, i64 sCm, i
   REQUIRE(A.rows_pad == p.tm * p.bm && p.tiles == (i64)p.tm * (B.rows_pad / TN) && B.rows_pad % TN == 0 &&
               p.nk == A.nkc && (p.cutters == 0 || W),
           CCLR_EINVAL, "split GEMM: operands and plan differ");
-  REQUIRE(p.tiles < (i64)1 << 30, CCLR_EINVAL, "split GEMM: too many tiles");
+  // uncut, a workgroup of 512 threads for each tile
+  REQUIRE(p.tiles < (i64)1 << 23 && (p.cutters > 0 || p.grid == p.tiles), CCLR_EINVAL, "split GEMM: too many tiles");
   switch (p.bm) {
     case 64: launch_bm<64>(A, B, C, sCm, sCn, ar, ai, beta, p, (float*)W, st); break;
     case 96: launch_bm<96>(A, B, C, sCm, sCn, ar, ai, beta, p, (float*)W, st); break;
