@@ -664,6 +664,24 @@ void contract(cclr_ctx* c, cplx alpha, const Ten& A, const char* la, const Ten& 
   c->arena.reset(mk);
 }
 
+// g with its B side split already: splits the A side and multiplies.  What is
+// left of the arena goes to the split first: the product can do without cut
+// tiles and their partial sums.
+void split_product(cclr_ctx* c, const GemmArgs& g, int form, const SplitMat& B) {
+  Arena::Mark mk = c->arena.mark();
+  const SplitPlan whole = split_plan(g.M, g.N, g.K, form, false);
+  const size_t need = split_bytes(g.M, g.K, form, 0, whole.bm);
+  SplitPlan p = split_plan(g.M, g.N, g.K, form, true);
+  const size_t want = split_bytes(g.M, g.K, form, 0, p.bm);
+  void* wa = want > need ? c->arena.try_get(want) : nullptr;
+  if (!wa) wa = c->arena.get(need), p = want > need ? whole : p;
+  void* W = p.cutters > 0 ? c->arena.try_get(split_workspace(p)) : nullptr;
+  if (!W) p = whole;
+  const SplitMat A = launch_split(g.M, g.K, g.A, g.sAm, g.sAk, g.conjA, wa, form, 0, c->stream, p.bm);
+  launch_split_gemm(A, B, g.C, g.sCm, g.sCn, g.ar, g.ai, g.beta, p, W, c->stream);
+  c->arena.reset(mk);
+}
+
 // GEMM dispatch: products whose output covers too few 64x64 tiles to occupy
 // the 256 compute units split the reduction into chunks that write partial
 // products to a workspace, summed in a fixed order afterwards.
@@ -672,18 +690,6 @@ void contract(cclr_ctx* c, cplx alpha, const Ten& A, const char* la, const Ten& 
 // short-output VALU kernel, -5 reduced precision on pre-split FP32 planes, -6
 // short-output VALU kernel on a long operand contiguous in k, -7 small
 // products straight from registers, -8 even split over the compute units)
-// g with its B side split already: splits the A side and multiplies
-void split_product(cclr_ctx* c, const GemmArgs& g, int form, const SplitMat& B) {
-  Arena::Mark mk = c->arena.mark();
-  SplitPlan p = split_plan(g.M, g.N, g.K, form, true);
-  void* W = p.cutters > 0 ? c->arena.try_get(split_workspace(p)) : nullptr;
-  if (p.cutters > 0 && !W) p = split_plan(g.M, g.N, g.K, form, false);
-  void* wa = c->arena.get(split_bytes(g.M, g.K, form, 0, p.bm));
-  const SplitMat A = launch_split(g.M, g.K, g.A, g.sAm, g.sAk, g.conjA, wa, form, 0, c->stream, p.bm);
-  launch_split_gemm(A, B, g.C, g.sCm, g.sCn, g.ar, g.ai, g.beta, p, W, c->stream);
-  c->arena.reset(mk);
-}
-
 static void run_gemm_form(cclr_ctx* c, const GemmArgs& g, int& form);
 void run_gemm(cclr_ctx* c, const GemmArgs& g) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0 || g.K <= 0) return;
