@@ -198,8 +198,9 @@ int cclr_dbg_ritz(int nr, int ld, const int* m, const cclr_c64* G, double* out);
 
 /* Record of the large FP64 products (1e10 flop and more): writes up to cap
  * bytes of text, one line for each shape met, "MxNxK bB: -> variant" (at most
- * 256 shapes; products on the register or the evenly split kernel are not in
- * it).  The variant follows from the shape; enable has no effect. */
+ * 256 shapes; products on the register or the evenly split kernel or split
+ * along K are not in it).  The variant follows from the shape; enable has no
+ * effect. */
 int cclr_dbg_tuning(cclr_ctx* ctx, int enable, char* buf, long long cap);
 
 #ifdef __cplusplus

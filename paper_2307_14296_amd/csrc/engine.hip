@@ -1074,9 +1074,10 @@ int gemm_by_rule(cclr_ctx* c, const GemmArgs& g) {
   if (even_split(c, g)) return kFormEven;
   const int v = tile_variant(g);
   launch_gemm_choice(g, v, c->stream);
-  // the record of large products, one line for each shape
-  if (8.0 * g.M * (double)g.N * g.K * g.batch >= 1e10 && c->gemm_record.size() < 256)
-    c->gemm_record.emplace(std::make_tuple(g.M, g.N, g.kchunk > 0 ? g.kchunk : g.K, g.batch), v);
+  // the record of large products, one line for each shape (the parts of one
+  // that is split along K are none)
+  if (g.kchunk == 0 && 8.0 * g.M * (double)g.N * g.K * g.batch >= 1e10 && c->gemm_record.size() < 256)
+    c->gemm_record.emplace(std::make_tuple(g.M, g.N, g.K, g.batch), v);
   return v;
 }
 
