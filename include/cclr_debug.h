@@ -172,6 +172,9 @@ int cclr_dbg_set_blocking(cclr_ctx* ctx, long long wp_block, int rhs_group);
  * released and once more after that of the device's other contexts). */
 int cclr_dbg_fail_allocs(cclr_ctx* ctx, int n);
 
+/* Device memory that ctx holds, in bytes. */
+int cclr_dbg_allocated(cclr_ctx* ctx, long long* bytes);
+
 /* Hessian products (t^X F) of nvec response vectors with the context's
  * amplitudes and lambda (cclr_solve_lambda first; CCLR_ESTATE otherwise):
  * x1 [nvec][o][v], x2 [nvec][o][o][v][v] in (only unique doubles read), s1,

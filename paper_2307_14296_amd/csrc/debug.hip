@@ -426,6 +426,13 @@ int cclr_dbg_fail_allocs(cclr_ctx* c, int n) {
   return CCLR_OK;
 }
 
+int cclr_dbg_allocated(cclr_ctx* c, long long* bytes) {
+  if (!c || !bytes) return CCLR_EINVAL;
+  const InCall busy(c);
+  *bytes = (long long)c->allocated;
+  return CCLR_OK;
+}
+
 int cclr_dbg_hessian(cclr_ctx* c, int nvec, const cclr_c64* x1, const cclr_c64* x2, cclr_c64* s1, cclr_c64* s2) {
   if (!c || nvec < 1 || !x1 || !x2 || !s1 || !s2) return CCLR_EINVAL;
   if (!c->have_t || !c->have_lam) return CCLR_ESTATE;

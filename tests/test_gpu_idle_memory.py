@@ -23,6 +23,7 @@ def lib():
         pytest.skip("no GPU")
     import paper_2307_14296_amd as cc
     cc.lib().cclr_dbg_fail_allocs.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    cc.lib().cclr_dbg_allocated.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_longlong)]
     n = O + V
     H = [zeros(n, n)] + [zeros(*[O if c == "o" else V for c in k]) for k in ("oooo", "ooov", "oovv", "ovov", "ovvv", "vvvv")]
     big = zeros(1600, O, V), zeros(1600, O, O, V, V)
@@ -45,9 +46,10 @@ def transform(lib, ctx, n):
     assert bool((s1[:n] == -(0.5 + 0.25j)).all()) and not bool(s2[:n].any())
 
 
-def free():
-    torch.cuda.synchronize()
-    return torch.cuda.mem_get_info()[0]
+def held(cc, ctx):
+    n = ctypes.c_longlong()
+    assert cc.lib().cclr_dbg_allocated(ctx, ctypes.byref(n)) == 0
+    return n.value
 
 
 def test_own_idle_memory(lib):
@@ -57,32 +59,34 @@ def test_own_idle_memory(lib):
     for fails in (0, 1):
         ctx = context(cc, H)
         transform(lib, ctx, 100)
-        f = free()
+        before = held(cc, ctx)
         assert cc.lib().cclr_dbg_fail_allocs(ctx, fails) == 0
         transform(lib, ctx, 1600)
-        taken.append(f - free())
+        taken.append(held(cc, ctx) - before)
         transform(lib, ctx, 100)
         transform(lib, ctx, 1600)
         cc.cclr_destroy(ctx)
-    print(f"taken {taken[0] / 2 ** 20:.0f} MiB, {taken[1] / 2 ** 20:.0f} MiB with the idle chunk released", flush=True)
-    assert taken[1] <= taken[0] - CHUNK + (1 << 20)
+    print(f"taken {taken[0]} bytes, {taken[1]} with the idle chunk released", flush=True)
+    assert taken[1] == taken[0] - CHUNK
 
 
 def test_idle_memory_of_another_context(lib):
     cc, H = lib[:2]
     keeper = context(cc, H)
+    idle = held(cc, keeper)
     transform(lib, keeper, 100)
     other = context(cc, H)
-    f = free()
+    before = held(cc, keeper)
     assert cc.lib().cclr_dbg_fail_allocs(other, 2) == 0
     cc.cclr_set_amplitudes(other, zeros(O, V), zeros(O, O, V, V))  # same sizes: keeps what it has
     transform(lib, other, 1600)
+    after = held(cc, keeper)
     cc.cclr_destroy(other)
-    got = free() - f
     transform(lib, keeper, 100)
+    again = held(cc, keeper)
     cc.cclr_destroy(keeper)
-    print(f"{got / 2 ** 20:.0f} MiB more than before", flush=True)
-    assert got >= 2 * CHUNK
+    print(f"{before} bytes before, {after} after", flush=True)
+    assert before == idle + CHUNK and after == before - 2 * CHUNK and again == before
 
 
 def test_no_room_at_all(lib):
