@@ -651,44 +651,46 @@ SplitPlan split_plan_for(int M, int N, int K, int form, int bm, int cutters) {
 // Estimated time in us of a plan: the k steps of the busiest workgroup (low:
 // few compute units at work, full: all of them and their traffic), each whole
 // tile's stores, and for cut tiles the partial sums, written and read at
-// 4 TB/s, and a tenth on their steps, since each workgroup starts at another k
-// and neighbours no longer share operand panels.
+// 4 TB/s, the second launch, and a tenth on their steps, since each workgroup
+// starts at another k and neighbours no longer share operand panels.
 static double split_cost(const SplitPlan& p, int form) {
   // us per k step with 128, 96 and 64 rows
   static const double low[3][3] = {{1.5, 1.15, 0.9}, {1.05, 0.84, 0.74}, {3.2, 2.55, 1.68}};
   static const double full[3][3] = {{2.0, 1.6, 1.37}, {1.4, 1.18, 1.0}, {3.2, 2.55, 1.68}};
   const int r = p.bm == 128 ? 0 : p.bm == 96 ? 1 : 2;
   const double lo = low[form][r], hi = full[form][r], tile = p.bm * TN / 4e6;  // us of one byte per element
+  auto step = [&](i64 busy) { return lo + (hi - lo) * (double)busy / 256; };
   const i64 rounds = p.whole / 256, last = p.whole % 256;
   if (p.cutters == 0 && form == F32_G3 && r == 0) return (p.nk * 3.05 + 2.0 + 256 * 16 * tile) * (rounds + (last > 0));
   double t = (double)rounds * (p.nk * hi + 2.0 + 256 * 16 * tile);
-  if (last) t += p.nk * (lo + (hi - lo) * (double)last / 256) + 2.0 + (double)last * 16 * tile;
+  if (last) t += p.nk * step(last) + 2.0 + (double)last * 16 * tile;
   if (p.cutters) {
     const double rest = (double)(p.tiles - p.whole);
-    t += 1.1 * rest * p.nk / p.cutters * hi + 16.0 + p.cutters * 24 * tile + rest * 16 * tile;
+    t += 1.1 * rest * p.nk / p.cutters * step(p.cutters) + 8.0 + p.cutters * (6.0 / 256 + 24 * tile) + rest * 16 * tile;
   }
   return t;
 }
 
-// The tile height of least estimated time, and cut tiles where they are
-// estimated 2% faster than that without.  Over 46 products (45 to 48000 rows,
-// K 600 to 19900) in the three forms that is at most 8% off the fastest plan
-// measured and never behind whole 128 x 128 tiles.  Cut on any gain in the
-// estimate, 29% behind: 540x3160x3160 in X2 113 us cut, 85 whole (96 rows of
-// 128: 119); 2280x19900x19900 in X2 10240, 9970.
+// The tile height and the number of runs of least estimated time; cut tiles
+// where they are estimated 2% faster than that without.  Over 65 products (10
+// to 48000 rows, K 144 to 19900) in the three forms that is at most 13% off
+// the fastest plan measured, 1% in the mean (2% with 256 runs always:
+// 55x2016x2016 in X2 29 us on 252 runs, 22 on 64 to 128).  Cut on any gain in
+// the estimate, it was up to 29% behind whole 128 x 128 tiles: 540x3160x3160 in
+// X2 113 us cut, 85 whole; 2280x19900x19900 in X2 10240, 9970.
 SplitPlan split_plan(int M, int N, int K, int form, bool room) {
   REQUIRE(split_form_valid(form), CCLR_EINVAL, "split: unknown form");
   SplitPlan best;
   double t = 1e300;
-  for (int cutters : {0, 256}) {
-    if (cutters && !room) continue;
-    if (cutters) t *= 0.98;
+  auto offer = [&](int cutters, double margin) {
     for (int bm : {128, 96, 64}) {
       const SplitPlan p = split_plan_for(M, N, K, form, bm, cutters);
-      const double tp = split_cost(p, form);
+      const double tp = split_cost(p, form) * margin;
       if (tp < t) best = p, t = tp;
     }
-  }
+  };
+  offer(0, 0.98);
+  for (int cutters = 64; room && cutters <= 256; cutters += 32) offer(cutters, 1.0);
   return best;
 }
 

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("prec,M,N,K,cut", [
     ("bf16x3", 540, 3160, 3160, False), ("bf16x2", 540, 3160, 3160, False), ("fp32", 540, 3160, 3160, False),
-    ("bf16x3", 300, 900, 900, False), ("bf16x2", 300, 900, 900, False), ("fp32", 300, 900, 900, True),
+    ("bf16x3", 704, 704, 704, False), ("bf16x2", 704, 704, 704, False), ("fp32", 704, 704, 704, True),
     ("bf16x3", 45, 3160, 3160, True), ("bf16x2", 45, 3160, 3160, True)])
 def test_cut_where_it_pays(lib, prec, M, N, K, cut):  # noqa: F811
     run(lib, prec, 0, 256, M, N, K, 0, cut)
