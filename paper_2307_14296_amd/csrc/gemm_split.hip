@@ -190,13 +190,19 @@ __device__ __forceinline__ void put(cplx* dst, double xr, double xi, double ar, 
   *dst = y;
 }
 
-// the three accumulators of entry (m, n) of a cut tile's run, as they are: one
-// plane each, so that a wave's stores are runs of 16 floats
-__device__ __forceinline__ void keep(float* __restrict__ W, i64 slot, int bm, int m, int n, float a, float b, float c) {
-  float* w = W + (3 * slot * bm + m) * TN + n;
-  w[0] = a;
-  w[bm * TN] = b;
-  w[2 * bm * TN] = c;
+// the accumulators of a cut tile's run, as they are: 16 bytes a lane, fragment
+// after fragment ([accumulator][i][j][thread of 512][row of 4]), so that the
+// stores of a wave and the loads of k_split_join are whole lines (4-byte
+// stores into rows: 4 to 13 us more, 264x4005x4005 in X3 103 us against 95)
+template <int FM, int FN>
+__device__ __forceinline__ void keep(float* __restrict__ W, i64 slot, const f4 (&acc)[3][FM][FN]) {
+  f4* w = (f4*)W + slot * (3 * FM * FN * 512) + threadIdx.x;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) w[((a * FM + i) * FN + j) * 512] = acc[a][i][j];
 }
 
 // C[m][n] (+)= alpha * sum_k A[m][k] B[n][k] on split operands.  BM x 128
@@ -330,6 +336,10 @@ __global__ __launch_bounds__(512) void k_cgemm_bf16s(const u4v* __restrict__ As,
       step(kc, sA0, sB0, sA1, sB1);
       if (kc + 1 < k1) step(kc + 1, sA1, sB1, sA0, sB0);
     }
+    if (slot >= 0) {
+      keep(W, slot, acc);
+      return;
+    }
     // output block (i, j): row 16i + 4*(lane/16) + r, column 16j + lane%16
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -337,13 +347,9 @@ __global__ __launch_bounds__(512) void k_cgemm_bf16s(const u4v* __restrict__ As,
       for (int j = 0; j < FN; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
-          if (slot >= 0) {
-            keep(W, slot, BM, m, n, acc[0][i][j][r], acc[1][i][j][r], acc[2][i][j][r]);
-          } else if (m0 + m < M && n0 + n < N) {
-            const double xr = (double)acc[0][i][j][r] - (double)acc[1][i][j][r], xi = (double)acc[2][i][j][r];
-            put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, xr, xi, ar, ai, beta);
-          }
+          const int m = m0 + wm + 16 * i + 4 * g + r, n = n0 + wn + 16 * j + rr;
+          const double xr = (double)acc[0][i][j][r] - (double)acc[1][i][j][r], xi = (double)acc[2][i][j][r];
+          if (m < M && n < N) put(C + (i64)m * sCm + (i64)n * sCn, xr, xi, ar, ai, beta);
         }
   };
   deal(p, segment);
@@ -412,10 +418,12 @@ __global__ __launch_bounds__(256) void k_split_f32(int rows, int K, const cplx* 
 // two LDS stages).  Without cut tiles the 128-row kernel takes one tile and no
 // loop over tiles (CUT = false), which spares it registers: 2280x19900x19900
 // 39.5 ms, 41.5 with the loop (the bf16 forms are the same with and without).
+// One workgroup per compute unit by the attribute: with 64 rows the registers
+// would do for two, which is slower (3240x1080x1080 250 us, 216).
 // Against whole 128 x 128 tiles, us: 264x4005x4005 289 / 740, 4320x1080x1080
 // 300 / 411, 570x19900x19900 11630 / 14700.
 template <int BM, bool CUT>
-__global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, const u4v* __restrict__ Bs, int Mpad,
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_cgemm_f32s(const u4v* __restrict__ As, const u4v* __restrict__ Bs, int Mpad,
                                                     int Npad, int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn,
                                                     double ar, double ai, int beta, SplitPlan p,
                                                     float* __restrict__ W) {
@@ -505,6 +513,7 @@ __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, 
       step(kb, sA0, sB0, sA1, sB1);
       if (kb + 1 < k1) step(kb + 1, sA1, sB1, sA0, sB0);
     }
+    if (!CUT || slot < 0) {
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -512,24 +521,24 @@ __global__ __launch_bounds__(512) void k_cgemm_f32s(const u4v* __restrict__ As, 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
-          if (CUT && slot >= 0) {
-            keep(W, slot, BM, m, n, acc[0][i][j][r], acc[1][i][j][r], acc[2][i][j][r]);
-          } else if (m0 + m < M && n0 + n < N) {
-            const double g1 = acc[0][i][j][r], g2 = acc[1][i][j][r], g3 = acc[2][i][j][r];
-            put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, g1 - g3, g1 + g2, ar, ai, beta);
-          }
+          const double g1 = acc[0][i][j][r], g2 = acc[1][i][j][r], g3 = acc[2][i][j][r];
+          if (m0 + m < M && n0 + n < N) put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, g1 - g3, g1 + g2, ar, ai, beta);
         }
+    } else {
+      keep(W, slot, acc);
+    }
   };
   if (CUT) deal(p, segment);
   else segment(xcd_position((int)blockIdx.x, (int)gridDim.x), 0, p.nk, -1);
 }
 
 // Adds the accumulators of the runs of cut tile whole + blockIdx.x in the order
-// of k, in FP64, forms the result of them and stores it, one element per
-// thread (blockIdx.y: which 256 of the tile).
-__global__ __launch_bounds__(256) void k_split_join(int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn, double ar,
+// of k, in FP64, forms the result of them and stores it: four rows of one
+// 16 x 16 block a thread, as the product's waves hold them, blockIdx.y which of
+// a wave's blocks.
+__global__ __launch_bounds__(512) void k_split_join(int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn, double ar,
                                                     double ai, int beta, SplitPlan p, int gauss,
-                                                    const float* __restrict__ W) {
+                                                    const f4* __restrict__ W) {
   const i64 total = (p.tiles - p.whole) * p.nk, t = blockIdx.x;
   const i64 lo = t * p.nk, hi = lo + p.nk;
   // run c covers the k steps [c total / cutters, (c + 1) total / cutters): the runs with a part of [lo, hi)
@@ -540,31 +549,45 @@ __global__ __launch_bounds__(256) void k_split_join(int M, int N, cplx* __restri
   i64 c1 = c0 + 1;
   while (c1 < p.cutters && c1 * total / p.cutters < hi) ++c1;
   const i64 tile = p.whole + t;
-  const int size = p.bm * TN, e = blockIdx.y * 256 + threadIdx.x;
-  const int m = (int)(tile % p.tm) * p.bm + e / TN, n = (int)(tile / p.tm) * TN + e % TN;
-  if (m >= M || n >= N) return;
-  double x[3];
+  constexpr int FN = TN / 4 / 16;
+  const int blocks = p.bm / 32 * FN, size = blocks * 512;  // 16-byte entries of one accumulator
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = blockIdx.y / FN, j = blockIdx.y % FN;
+  const int m0 = (int)(tile % p.tm) * p.bm + (wave & 1) * (p.bm / 2) + 16 * i + 4 * (lane >> 4);
+  const int n = (int)(tile / p.tm) * TN + (wave >> 1) * (TN / 4) + 16 * j + (lane & 15);
+  if (m0 >= M || n >= N) return;
+  const int e = blockIdx.y * 512 + threadIdx.x;
+  double x[3][4];
   {
     // the first run may have begun in the tile before: then this is its second piece
-    const float* w = W + 3 * (2 * c0 + (b0 < lo ? 1 : 0)) * size + e;
+    const f4* w = W + 3 * (2 * c0 + (b0 < lo ? 1 : 0)) * size + e;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) x[q] = w[q * size];
+    for (int q = 0; q < 3; ++q) {
+      const f4 v = w[q * size];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[q][r] = v[r];
+    }
   }
   constexpr int U = 4;
   for (i64 c = c0 + 1; c < c1; c += U) {
-    float w[U][3];
+    f4 w[U][3];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) w[u][q] = c + u < c1 ? W[(6 * (c + u) + q) * size + e] : 0.f;
+      for (int q = 0; q < 3; ++q) w[u][q] = c + u < c1 ? W[(6 * (c + u) + q) * size + e] : f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) x[q] += (double)w[u][q];
+      for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[q][r] += (double)w[u][q][r];
   }
   // split-BF16: Ar Br, Ai Bi, Ar Bi + Ai Br; FP32: k1, k2, k3 of Gauss's form
-  const double xr = x[0] - x[gauss ? 2 : 1], xi = gauss ? x[0] + x[1] : x[2];
-  put(C + (i64)m * sCm + (i64)n * sCn, xr, xi, ar, ai, beta);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (m0 + r >= M) break;
+    const double xr = x[0][r] - (gauss ? x[2][r] : x[1][r]), xi = gauss ? x[0][r] + x[1][r] : x[2][r];
+    put(C + (i64)(m0 + r) * sCm + (i64)n * sCn, xr, xi, ar, ai, beta);
+  }
 }
 
 template <int P>
@@ -673,11 +696,11 @@ static double split_cost(const SplitPlan& p, int form) {
 
 // The tile height and the number of runs of least estimated time; cut tiles
 // where they are estimated 2% faster than that without.  Over 65 products (10
-// to 48000 rows, K 144 to 19900) in the three forms that is at most 13% off
-// the fastest plan measured, 1% in the mean (2% with 256 runs always:
-// 55x2016x2016 in X2 29 us on 252 runs, 22 on 64 to 128).  Cut on any gain in
-// the estimate, it was up to 29% behind whole 128 x 128 tiles: 540x3160x3160 in
-// X2 113 us cut, 85 whole; 2280x19900x19900 in X2 10240, 9970.
+// to 48000 rows, K 144 to 19900) in the three forms that is 2% off the fastest
+// plan measured in the mean, 16% at most, and never behind whole 128 x 128
+// tiles.  Cut on any gain in the estimate, and always into 256 runs, it was up
+// to 29% behind those: 540x3160x3160 in X2 113 us cut, 85 whole;
+// 55x2016x2016 in X2 29 us on 252 runs, 22 on 64 to 128.
 SplitPlan split_plan(int M, int N, int K, int form, bool room) {
   REQUIRE(split_form_valid(form), CCLR_EINVAL, "split: unknown form");
   SplitPlan best;
@@ -735,8 +758,8 @@ void launch_split_gemm(const SplitMat& A, const SplitMat& B, cplx* C, i64 sCm, i
   }
   HIPCHK(hipGetLastError());
   if (p.cutters > 0) {
-    hipLaunchKernelGGL(k_split_join, dim3((unsigned)(p.tiles - p.whole), p.bm * TN / 256), dim3(256), 0, st, A.rows,
-                       B.rows, C, sCm, sCn, ar, ai, beta, p, A.form == F32_G3 ? 1 : 0, (const float*)W);
+    hipLaunchKernelGGL(k_split_join, dim3((unsigned)(p.tiles - p.whole), p.bm * TN / 2048), dim3(512), 0, st, A.rows,
+                       B.rows, C, sCm, sCn, ar, ai, beta, p, A.form == F32_G3 ? 1 : 0, (const f4*)W);
     HIPCHK(hipGetLastError());
   }
 }
