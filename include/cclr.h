@@ -38,9 +38,9 @@
  *   copies of f, the integral blocks, t, lambda and the intermediates and
  *   retains no caller pointer after a call returns.  A context is used by one
  *   host thread at a time; distinct contexts are independent.
- * - Between calls a context keeps work memory: of its last calls' at most half
- *   of the device's memory (what fits under a device_mem_cap), and after
- *   cclr_set_amplitudes at most 4 GiB (none under a cap).  An allocation of
+ * - Between calls a context keeps work memory: at most half of the device's
+ *   memory (what fits under a device_mem_cap); cclr_set_amplitudes raises it to
+ *   4 GiB at most and leaves what is more (none under a cap).  An allocation of
  *   any context on the same device that finds no room gets the idle part of
  *   it back; cclr_destroy frees it.
  * - Return codes: CCLR_OK (0); CCLR_ENOTCONV (> 0: result written, solver

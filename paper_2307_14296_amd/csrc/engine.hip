@@ -184,7 +184,7 @@ void Arena::release_idle() {
     if (used[k] == 0) chunks[k]->release();
 }
 
-// idle arena memory a context keeps after a build (4 GiB: what the build of
+// idle arena memory a context keeps of a build's (4 GiB: what the build of
 // the intermediates and a solve take at o = 12, v = 90), none under a memory
 // cap; any allocation that finds no room gets it back
 size_t arena_keep(const cclr_ctx* c) { return c->opt.device_mem_cap ? 0 : size_t(4) << 30; }

@@ -29,6 +29,7 @@ void build_intermediates(cclr_ctx* c) {
     c->wsplit[w].release();
     c->wsplit_m[w] = SplitMat{};
   }
+  const size_t idle = c->opt.device_mem_cap ? 0 : c->arena.idle();
   Arena::Mark mk = c->arena.mark();
   const cplx one = cx(1.0), mone = cx(-1.0), half = cx(0.5), mhalf = cx(-0.5);
   Ten t1 = ten(c->t1, {o, v});
@@ -235,6 +236,9 @@ void build_intermediates(cclr_ctx* c) {
   // the v^4-sized temporaries of the build are not needed before the next set
   // of amplitudes: released, except for what makes the next build and the
   // solves free of allocations (o = 12, v = 90: 7 ms a build; 18-28 ms when all
-  // is released and two other contexts are alive)
-  c->arena.trim(arena_keep(c));
+  // is released and two other contexts are alive).  What earlier solves left
+  // stays: a program that replaces its amplitudes solves again.  With 4 GiB
+  // kept of the 35 that 12 right-hand sides take at o = 20, v = 200, 2 of 36
+  // jobs took 1 to 2 s longer than their 1.4 s (BF16X3) or 2 s (FP32); none of 72 so.
+  c->arena.trim(std::max(idle, arena_keep(c)));
 }

@@ -499,7 +499,7 @@ int solve_system(cclr_ctx* c, int side, int nr, const cplx* zh, const VecSet& rh
 void merge_conditioning(cclr_solve_info& dst, const cclr_solve_info& src);
 // nvec packed vectors from the arena
 VecSet packed_buf(cclr_ctx* c, int n);
-// idle arena memory (bytes) a context keeps after a build
+// idle arena memory (bytes) a context keeps of a build's, if it had less before
 size_t arena_keep(const cclr_ctx* c);
 // how many of n vectors with the given working memory each fit in free device memory (>= 1)
 int fit_vectors(cclr_ctx* c, double bytes_per_vec, int n);

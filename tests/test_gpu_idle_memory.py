@@ -119,6 +119,21 @@ def test_second_solve_allocates_nothing(lib):
     cc.cclr_destroy(ctx)
 
 
+def test_new_amplitudes_keep_it(lib):
+    # the 5 GB that 300 right-hand sides leave are there for the solve after
+    # new amplitudes, which may then allocate nothing
+    cc, H, (r1, r2), (s1, s2) = lib
+    ctx, n = context(cc, H), 300
+    taken = []
+    for fails in (0, 3):
+        cc.cclr_set_amplitudes(ctx, zeros(O, V), zeros(O, O, V, V))
+        assert cc.lib().cclr_dbg_fail_allocs(ctx, fails) == 0
+        cc.cclr_solve_damped(ctx, cc.CCLR_RIGHT, [0.5] * n, [0.25] * n, r1[:n], r2[:n], s1[:n], s2[:n])
+        taken.append(held(cc, ctx))
+    cc.cclr_destroy(ctx)
+    assert taken[0] > 4 << 30 and taken[1] == taken[0]
+
+
 def test_two_threads(lib):
     # one thread's allocations keep finding no room while the other's transforms run
     cc, H = lib[:2]
