@@ -393,7 +393,7 @@ def ground_bench(cc, dev, o, v, seed, tol=1e-8, nchol_per_orbital=3, v_std=0.002
     try:
         torch.cuda.synchronize()
         t0 = time.perf_counter()
-        cc.cclr_set_hamiltonian_cholesky(ctx, fd, Lc)  # first call: includes timing the product variants
+        cc.cclr_set_hamiltonian_cholesky(ctx, fd, Lc)  # first call: takes the blocks' memory
         torch.cuda.synchronize()
         dt_first = time.perf_counter() - t0
         t0 = time.perf_counter()

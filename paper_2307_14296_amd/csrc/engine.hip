@@ -1034,7 +1034,8 @@ void launch_gemm_choice(const GemmArgs& g, int choice, hipStream_t s) {
 //   64x32                  t (1.08 nk + 1)   130x130x130, batch 400 257 (255)
 //   128x128 direct loads   t (7.27 nk + 8)   4000x4000x400 759 (756)
 // Over 43 shapes (N from 10 to 40000, K from 28 to 4000, batches to 700) the
-// choice is the fastest tile or within 4% of it.  The direct loads win from
+// choice is the fastest of these tiles or within 4% of it, but for
+// 100000x32x240 (144 on 128 rows, 129 on 64).  The direct loads win from
 // K of 160 to 200 on where their rounds are full (6000x6000x224 985 against
 // 999; 14400x1920x256 865 against 882), the 64x64 tiles below (16900x1300x100
 // 329 against 367), 32 columns where 64 pad more (38000x200x200, batch 3 702

@@ -697,7 +697,7 @@ static double split_cost(const SplitPlan& p, int form) {
 // The tile height and the number of runs of least estimated time; cut tiles
 // where they are estimated 2% faster than that without.  Over 65 products (10
 // to 48000 rows, K 144 to 19900) in the three forms that is 2% off the fastest
-// plan measured in the mean, 16% at most, and never behind whole 128 x 128
+// plan measured in the mean, 17% at most, and never behind whole 128 x 128
 // tiles.  Cut on any gain in the estimate, and always into 256 runs, it was up
 // to 29% behind those: 540x3160x3160 in X2 113 us cut, 85 whole;
 // 55x2016x2016 in X2 29 us on 252 runs, 22 on 64 to 128.

@@ -405,8 +405,8 @@ __global__ __launch_bounds__(kThreads) void k_pivot(VS out, VS X, const int* act
 // The augmented matrix is in LDS up to order kSolveLds, else in the scratch W
 // [nact][ld][ld+1].  Bound by the latency of its m dependent steps: the first
 // wave finds the pivot by lane exchange and the back substitution takes one
-// column per step (26 us before, with both serial in one thread; 9 us now at
-// m = 20).
+// column per step (26 us with both serial in one thread, 17 us so, at m about
+// 20).
 constexpr int kSolveLds = 56;
 __global__ __launch_bounds__(kThreads) void k_small_solve(const cplx* G, const cplx* C, int m, int ld, cplx* W,
                                                           cplx* beta, int* singular, const int* act) {
