@@ -423,10 +423,9 @@ __global__ __launch_bounds__(256) void k_split_f32(int rows, int K, const cplx* 
 // Against whole 128 x 128 tiles, us: 264x4005x4005 289 / 740, 4320x1080x1080
 // 300 / 411, 570x19900x19900 11630 / 14700.
 template <int BM, bool CUT>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_cgemm_f32s(const u4v* __restrict__ As, const u4v* __restrict__ Bs, int Mpad,
-                                                    int Npad, int M, int N, cplx* __restrict__ C, i64 sCm, i64 sCn,
-                                                    double ar, double ai, int beta, SplitPlan p,
-                                                    float* __restrict__ W) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_cgemm_f32s(
+    const u4v* __restrict__ As, const u4v* __restrict__ Bs, int Mpad, int Npad, int M, int N,
+    cplx* __restrict__ C, i64 sCm, i64 sCn, double ar, double ai, int beta, SplitPlan p, float* __restrict__ W) {
   constexpr int RS = 12, NT = 512, WM = BM / 2, WN = TN / 4, FM = WM / 16, FN = WN / 16;
   constexpr int CA = BM * RS, CB = TN * RS;  // chunks per tile and k step
   __shared__ u4v sA0[CA], sA1[CA];
@@ -515,15 +514,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     if (!CUT || slot < 0) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+      for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
+        for (int j = 0; j < FN; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
-          const double g1 = acc[0][i][j][r], g2 = acc[1][i][j][r], g3 = acc[2][i][j][r];
-          if (m0 + m < M && n0 + n < N) put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, g1 - g3, g1 + g2, ar, ai, beta);
-        }
+          for (int r = 0; r < 4; ++r) {
+            const int m = wm + 16 * i + 4 * g + r, n = wn + 16 * j + rr;
+            const double g1 = acc[0][i][j][r], g2 = acc[1][i][j][r], g3 = acc[2][i][j][r];
+            if (m0 + m < M && n0 + n < N)
+              put(C + (i64)(m0 + m) * sCm + (i64)(n0 + n) * sCn, g1 - g3, g1 + g2, ar, ai, beta);
+          }
     } else {
       keep(W, slot, acc);
     }
